@@ -129,7 +129,8 @@ def _layer(cfg, normal):
     return w
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """(configuration, layers, latent, the previous step's latent, conditioning, text, conditioning of each step)."""
     cfg = _config(case)
     gen = torch.Generator(device="cuda").manual_seed(int(seed))
 
@@ -158,15 +159,22 @@ def prepare(case, seed):
         text = normal(*lead, T, cfg["cross_dim"]).to(torch.bfloat16 if cfg["dtype"] == "bf16" else torch.float32)
     elif kind in (2, 3):
         text = normal(*lead, T, d)
+    conds = [cond + 0.1 * cond_std * normal(*cond_shape) for _ in range(case["steps"])]
+    return cfg, layers, x, x_prev, cond, text, conds
 
+
+def _dts(case):
+    return [-0.2 / case["steps"]] * case["steps"]
+
+
+def prepare(case, seed):
+    cfg, layers, x, x_prev, cond, text, conds = _inputs(case, seed)
     state = dict(case=case, cond=cond, text=text)
     if case["op"] == "sample":
         per = cfg["n_layers"]
         state["pipe"] = Pipeline(cfg, [layers[i * per:(i + 1) * per] for i in range(case["stages"])])
         state["kv"] = [st.kv.view(st.dt) for st in state["pipe"].stages]
-        state["x"] = x
-        state["conds"] = [cond + 0.1 * cond_std * normal(*cond_shape) for _ in range(case["steps"])]
-        state["dts"] = [-0.2 / case["steps"]] * case["steps"]
+        state["x"], state["conds"], state["dts"] = x, conds, _dts(case)
         return state
     stage = Stage(cfg, layers)
     state["stage"] = stage
@@ -175,7 +183,7 @@ def prepare(case, seed):
         state["x"] = x_prev
         return state
     stage.kv_init(x_prev, cond, text)              # the previous step's K/V: the rows of the other patches stay stale
-    n, p = L // case["patches"], case["patch"]
+    n, p = cfg["seq_img"] // case["patches"], case["patch"]
     state["x"] = x[..., p * n:(p + 1) * n, :].contiguous()
     return state
 
@@ -246,3 +254,162 @@ def tolerance(case):
     # another order) over these cases: at most 2.6e-3 (2-norm) and 2.3e-2 (largest), both in the K/V buffers.  fp32: the
     # path against the float64 oracle: at most 6.6e-7 and 8.2e-6 on one layer, stages of up to three are drawn.
     return {"rel": 5e-6, "max": 6e-5} if case["dtype"] == "f32" else {"rel": 1e-2, "max": 0.1}
+
+
+class _Exact:
+    """One stage in float64 and plain torch: the block of each kind over a K/V buffer that keeps the stale rows."""
+
+    def __init__(self, cfg, layers):
+        self.c = cfg
+        dt = torch.bfloat16 if cfg["dtype"] == "bf16" else torch.float32      # the form in which a stage holds its weights
+
+        def wide(w):
+            return {k: wide(v) if isinstance(v, dict) else torch.from_numpy(v).to("cuda", dt).double() for k, v in w.items()}
+
+        self.layers = [wide(w) for w in layers]
+        B, H, dh, T = cfg["batch"], cfg["n_heads"], cfg["head_dim"], cfg["text_len"]
+        self.joint = cfg["kind"] in (2, 3)
+        self.rows = cfg["seq_img"] + (T if self.joint else 0)
+        self.pad = -(-self.rows // 128) * 128
+        self.tpad = -(-max(T, 1) // 128) * 128
+        self.K = [torch.zeros(B, H, self.pad, dh, dtype=torch.float64, device="cuda") for _ in layers]
+        self.V = [torch.zeros_like(k) for k in self.K]
+        self.KC = [torch.zeros(B, H, self.tpad, dh, dtype=torch.float64, device="cuda") for _ in layers] if cfg["kind"] == 1 else []
+        self.VC = [torch.zeros_like(k) for k in self.KC]
+
+    def kv(self):
+        """The buffers as the stage lays them out: K, V transposed, cross-attention K, V transposed, layer by layer."""
+        parts = []
+        for l in range(len(self.layers)):
+            parts += [self.K[l], self.V[l].transpose(-1, -2)]
+            if self.KC:
+                parts += [self.KC[l], self.VC[l].transpose(-1, -2)]
+        return torch.cat([t.reshape(-1) for t in parts])
+
+    @staticmethod
+    def _lin(x, w, name):
+        return x @ w["w" + name].T + w["b" + name]
+
+    def _ln(self, x, shift, scale):
+        x = x - x.mean(-1, keepdim=True)
+        return x / (x.square().mean(-1, keepdim=True) + 1e-6).sqrt() * (1.0 + scale) + shift
+
+    @staticmethod
+    def _gelu(x):
+        return torch.nn.functional.gelu(x, approximate="tanh")
+
+    def _heads(self, x):
+        return x.unflatten(-1, (self.c["n_heads"], self.c["head_dim"])).transpose(-2, -3)
+
+    def _attend(self, q, K, V):
+        """q [B, H, n, dh] over K, V [B, H, rows, dh], a piece of the queries of one head at a time -> [B, n, H * dh]."""
+        out = torch.empty_like(q)
+        step = max(1, 2 ** 27 // K.shape[2])
+        for b in range(q.shape[0]):
+            for h in range(q.shape[1]):
+                kt, v = (K[b, h].T * q.shape[-1] ** -0.5).contiguous(), V[b, h]
+                for i in range(0, q.shape[2], step):
+                    s = q[b, h, i:i + step] @ kt
+                    s = s.sub_(s.amax(-1, keepdim=True)).exp_()
+                    out[b, h, i:i + step] = (s @ v) / s.sum(-1, keepdim=True)
+        return out.transpose(1, 2).flatten(2)
+
+    def _rotate(self, t, first):
+        """t [B, H, n, dh]: first half of a head's channel pairs turned by the grid row, second half by the column."""
+        n, dh = t.shape[-2:]
+        tok = torch.arange(first, first + n, device="cuda", dtype=torch.float64)
+        freq = 1e4 ** (-4.0 * torch.arange(dh // 4, device="cuda", dtype=torch.float64) / dh)
+        ang = torch.cat([(tok // self.c["grid_w"])[:, None] * freq, (tok % self.c["grid_w"])[:, None] * freq], 1)
+        a, b = t[..., 0::2], t[..., 1::2]
+        return torch.stack([a * ang.cos() - b * ang.sin(), a * ang.sin() + b * ang.cos()], -1).flatten(-2)
+
+    def _project(self, l, h, w, row0, first):
+        """q of rows h, their k and v written to buffer rows from row0; first: image token of the first row, or None."""
+        q, k, v = (self._heads(t) for t in self._lin(h, w, "_qkv").chunk(3, -1))
+        if self.c["qk_norm"]:
+            q, k = (t / (t.square().mean(-1, keepdim=True) + 1e-6).sqrt() * g
+                    for t, g in ((q, w["q_norm_w"]), (k, w["k_norm_w"])))
+        if first is not None and (self.c["kind"] == 3 or self.c["joint_rope"]):
+            q, k = self._rotate(q, first), self._rotate(k, first)
+        self.K[l][:, :, row0:row0 + h.shape[1]] = k
+        self.V[l][:, :, row0:row0 + h.shape[1]] = v
+        return q
+
+    def run(self, x, first, cond, text=None):
+        """x [B, n, d] at image token `first` (and text [B, T, d] of the joint kinds) through every layer."""
+        kind, T = self.c["kind"], self.c["text_len"]
+        x, cond, d = x.double(), cond.double(), self.c["hidden"]
+        row0 = first + (T if self.joint else 0)
+        xt = text.double() if self.joint and text is not None else None
+        for l, w in enumerate(self.layers):
+            K, V = self.K[l][:, :, :self.rows], self.V[l][:, :, :self.rows]
+
+            def modulation(w):
+                m = w["w_mod"].flatten() + cond if kind == 1 else self._lin(torch.nn.functional.silu(cond), w, "_mod")
+                return [t[:, None, :] for t in m.view(x.shape[0], -1, d).unbind(1)]
+
+            streams = [(xt, w.get("txt", w), 0, None)] if xt is not None else []
+            streams.append((x, w, row0, first))
+            mods = [modulation(s[1]) for s in streams]
+            hs = [self._ln(s[0], m[0], m[1]) for s, m in zip(streams, mods)]
+            q = torch.cat([self._project(l, h, s[1], s[2], s[3]) for s, h in zip(streams, hs)], 2)
+            att = self._attend(q, K, V).split([s[0].shape[1] for s in streams], 1)
+            new = []
+            for (xs, ws, _, _), m, h, a in zip(streams, mods, hs, att):
+                if kind == 3:
+                    both = torch.cat([a, self._gelu(self._lin(h, ws, "_up"))], -1)
+                    new.append(xs + m[2] * self._lin(both, ws, "_down"))
+                    continue
+                xs = xs + m[2] * self._lin(a, ws, "_o")
+                if kind == 1:
+                    qc = self._heads(xs @ ws["xattn_wq"].T + ws["xattn_bq"])
+                    xs = xs + self._attend(qc, self.KC[l][:, :, :T], self.VC[l][:, :, :T]) @ ws["xattn_wo"].T + ws["xattn_bo"]
+                u = self._gelu(self._lin(self._ln(xs, m[3], m[4]), ws, "_up"))
+                new.append(xs + m[5] * self._lin(u, ws, "_down"))
+            x, xt = new[-1], new[0] if len(new) == 2 else xt
+        return x, xt
+
+    def warm_up(self, x, cond, text):
+        if self.c["kind"] == 1:
+            T = text.shape[1]
+            for l, w in enumerate(self.layers):
+                k, v = (text.double() @ w["xattn_wkv"].T + w["xattn_bkv"]).chunk(2, -1)
+                self.KC[l][:, :, :T], self.VC[l][:, :, :T] = self._heads(k), self._heads(v)
+        return self.run(x, 0, cond, text)
+
+
+def exact(case, seed):
+    cfg, layers, x, x_prev, cond, text, conds = _inputs(case, seed)
+    n, B = cfg["seq_img"] // case["patches"], cfg["batch"]
+
+    def lead(t):      # every array with its image axis
+        return t if B > 1 or t is None else t[None]
+
+    def back(t):
+        return t if B > 1 else t[0]
+
+    if case["op"] == "sample":
+        per, x = cfg["n_layers"], lead(x).double()
+        stages = [_Exact(cfg, layers[i * per:(i + 1) * per]) for i in range(case["stages"])]
+        for step, (c, dt) in enumerate(zip(conds, _dts(case))):
+            eps = torch.empty_like(x)
+            for p in range(1 if step == 0 else case["patches"]):
+                rows = slice(0, None) if step == 0 else slice(p * n, (p + 1) * n)
+                h, t = x[:, rows], lead(text)
+                for st in stages:
+                    if step == 0:
+                        h, t = st.warm_up(h, lead(c), lead(text) if cfg["kind"] == 1 else t)
+                    else:
+                        h, t = st.run(h, p * n, lead(c), t if p == 0 else None)
+                eps[:, rows] = h
+            x = x + dt * eps
+        return {"x": back(x), "eps": back(eps), "kv": [st.kv() for st in stages]}
+    st = _Exact(cfg, layers)
+    y, text_out = st.warm_up(lead(x_prev), lead(cond), lead(text))
+    if case["op"] == "patch":
+        p = case["patch"]
+        y, text_out = st.run(lead(x)[:, p * n:(p + 1) * n], p * n, lead(cond), lead(text) if case["with_text"] else None)
+    out = {"y": back(y), "kv": st.kv()}
+    if st.joint and text_out is not None:
+        out["text"] = back(text_out)
+    return out
