@@ -1,0 +1,278 @@
+// What the direct-to-LDS MFMA GEMM kernels share (bf16: gemm_mfma_dl.hip, fp32: gemm_mfma_f32.hip): tile loads, the
+// workgroup -> tile map, and the vectorised epilogue over a finished fp32 tile in LDS.
+#pragma once
+#include <type_traits>
+
+#include "common.h"
+#include "epilogue.h"
+#include "ops.h"
+
+namespace pf {
+
+namespace {
+
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// s_waitcnt vmcnt(behind * LPS) for a wave-uniform run-time `behind` in [0, MAXB] (the count is an immediate)
+template <int LPS, int MAXB>
+__device__ __forceinline__ void wait_tiles_behind(int behind) {
+  static_assert(MAXB * LPS <= 63, "vmcnt is a 6-bit counter");
+  if constexpr (MAXB <= 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (behind >= MAXB) wait_vmcnt<MAXB * LPS>();
+    else wait_tiles_behind<LPS, MAXB - 1>(behind);
+  }
+}
+
+// Tile loads are raw-buffer loads into LDS: a wave-uniform resource over the rows of the operand that the tile starts
+// at, a wave-uniform byte offset (the K position) and one 32-bit per-lane byte offset.  Against global loads with a
+// 64-bit address per lane that saves the 64-bit address arithmetic and half the address registers of every load
+// (same-box A/B inside the stages: Flux-scale QKV 141 -> 136 us, MLP-up 173 -> 165 us, long-sequence PixArt QKV 60 ->
+// 53 us).  The resource spans 2 GB from its base and the offsets are built from row indices that are clamped to the
+// matrix, so no load leaves the operand (gemm_mfma_dl_supported keeps the leading dimensions small enough).
+// The type only exists in device code; the host pass sees a stand-in with the same interface.
+#if defined(__HIP_DEVICE_COMPILE__)
+struct TileSource {
+  __amdgpu_buffer_rsrc_t rs;
+  __device__ __forceinline__ explicit TileSource(const void *base)
+      : rs(__builtin_amdgcn_make_buffer_rsrc((void *)base, 0, 0x7ffffff0, 0x00020000)) {}
+  // 16 bytes per lane from base + lane_bytes + uniform_bytes to lds_wave_uniform + 16 * lane
+  __device__ __forceinline__ void load16(unsigned lane_bytes, unsigned uniform_bytes, unsigned char *lds_wave_uniform) const {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)lds_wave_uniform, 16, lane_bytes,
+                                             uniform_bytes, 0, 0);
+  }
+};
+#else
+struct TileSource {
+  __device__ explicit TileSource(const void *) {}
+  __device__ void load16(unsigned, unsigned, unsigned char *) const {}
+};
+#endif
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unrolled(F &&f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unrolled<N, I + 1>(f);
+  }
+}
+
+// Workgroup id -> output tile.  Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2, so XCD x runs
+// the ids x, x + 8, ...  Every XCD gets one rectangular block of the tile grid - the grid is cut gx times along M and
+// 8 / gx times along N - because what an XCD fetches from memory is the A rows of its block plus the W rows of its
+// block: a contiguous run of tiles (a block one tile-column wide and all of M high) makes every XCD fetch all of A
+// (Flux-scale MLP-down: 623 MB fetched per launch for 157 MB of operands).  Inside the block the N index runs
+// fastest (workgroups in flight together share A tiles; measured equal or better than M fastest on every GEMM of the
+// five workloads, up to 12 % on the QKV projections).  Returns false for the surplus ids of the padded grid.
+__host__ __device__ __forceinline__ bool tile_of_id(int id, int tiles_m, int tiles_n, int gx, int &tm, int &tn) {
+  const int gy = 8 / gx;
+  const int bm = (tiles_m + gx - 1) / gx, bn = (tiles_n + gy - 1) / gy;
+  const int x = id & 7, j = id >> 3;
+  if (j >= bm * bn) return false;
+  const int lm = j / bn, ln = j - lm * bn;
+  tm = (x % gx) * bm + lm;
+  tn = (x / gx) * bn + ln;
+  return tm < tiles_m && tn < tiles_n;
+}
+__device__ __forceinline__ bool tile_of_block(int tiles_m, int tiles_n, int gx, int &tm, int &tn) {
+  return tile_of_id(blockIdx.x, tiles_m, tiles_n, gx, tm, tn);
+}
+
+// Residual and gate operands of a mode-1 epilogue, fetched by the thread that will use them before the K loop starts, so
+// that their memory latency runs under the loop instead of after it (the residual rows were written by an earlier
+// kernel and are in no cache).  Only for tiles small enough that a thread owns at most IT 8-column groups.  A tile is
+// read and written by its own workgroup only, so reading R early is safe when the GEMM updates it in place.
+template <int BM, int BN, int NT>
+struct EpiOperands {
+  static constexpr int IT = BM * BN / 8 / NT;
+  float4 r[IT][2], g[IT][2];
+  bool on;
+  template <typename T>
+  __device__ __forceinline__ void fetch(int m0, int n0, int M, int N, const Epilogue<T> &epi, bool vec_ok) {
+    on = vec_ok && epi.mode == 1;
+    if (!on) return;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int grp = threadIdx.x + it * NT;
+      const int row = m0 + grp / (BN / 8), col = n0 + (grp % (BN / 8)) * 8;
+      if (row >= M || col + 8 > N) continue;
+      const float *rp = epi.R + (size_t)row * epi.ldr + col;
+      r[it][0] = *reinterpret_cast<const float4 *>(rp); r[it][1] = *reinterpret_cast<const float4 *>(rp + 4);
+      if (epi.gate) {
+        const float *gp = epi.gate_of(row) + col;
+        g[it][0] = *reinterpret_cast<const float4 *>(gp); g[it][1] = *reinterpret_cast<const float4 *>(gp + 4);
+      }
+    }
+  }
+};
+
+// eight consecutive elements (16-byte aligned) to and from fp32
+__device__ __forceinline__ void load8(const bf16_t *p, float *o) { Vec16<bf16_t>::load(p, o); }
+__device__ __forceinline__ void load8(const float *p, float *o) { Vec16<float>::load(p, o); Vec16<float>::load(p + 4, o + 4); }
+__device__ __forceinline__ void store8(bf16_t *p, const float *o) { Vec16<bf16_t>::store(p, o); }
+__device__ __forceinline__ void store8(float *p, const float *o) { Vec16<float>::store(p, o); Vec16<float>::store(p + 4, o + 4); }
+
+// Epilogue over a finished fp32 tile held row-major in LDS (row stride TLD floats).  PRE: residual / gate operands
+// come from `ops` (fetched earlier) when ops->on.
+template <int BM, int BN, int TLD, int NT = 256, bool PRE = false, typename T>
+__device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0, int M, int N, const Epilogue<T> &epi, bool vec_ok, const EpiOperands<BM, BN, NT> *ops = nullptr) {
+  constexpr int GROUPS = BM * BN / 8;
+  constexpr int IT = (GROUPS + NT - 1) / NT, UNR = PRE ? IT : 1;
+#pragma unroll UNR
+  for (int it = 0; it < IT; ++it) {
+    const int g = threadIdx.x + it * NT;
+    if (GROUPS % NT != 0 && g >= GROUPS) break;
+    const int r = g / (BN / 8), c0 = (g % (BN / 8)) * 8;
+    const int row = m0 + r, col = n0 + c0;
+    if (row >= M || col >= N) continue;
+    const float *src = tile + r * TLD + c0;
+    float4 lo = *reinterpret_cast<const float4 *>(src), hi4 = *reinterpret_cast<const float4 *>(src + 4);
+    float v[8] = {lo.x, lo.y, lo.z, lo.w, hi4.x, hi4.y, hi4.z, hi4.w};
+    if (!vec_ok || col + 8 > N) {
+      for (int e = 0; e < 8 && col + e < N; ++e) epi.apply(row, col + e, v[e]);
+      continue;
+    }
+    if (epi.bias) {
+      float b[8];
+      load8(epi.bias + col, b);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += b[e];
+    }
+    if (epi.mode == 0 && epi.kv.kbuf) {
+      // QKV projection routed into the K / V^T buffers (an 8-column group never straddles q|k|v or two heads)
+      const KvRoute &kv = epi.kv;
+      const int part = col / kv.d, cc = col - part * kv.d;
+      const int hh = cc / kv.dh, ch = cc - hh * kv.dh;
+      const int img = kv.seg > 0 ? row / kv.seg : 0;
+      const int lrow = row - img * kv.seg;           // row inside its image
+      if (kv.rope && part < 2) {
+        const float2 *tab = kv.rope + (size_t)lrow * (kv.dh >> 1) + (ch >> 1);
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          float2 cs = tab[e >> 1];
+          float a0 = v[e], b0 = v[e + 1];
+          v[e] = a0 * cs.x - b0 * cs.y;
+          v[e + 1] = a0 * cs.y + b0 * cs.x;
+        }
+      }
+      if (part == 0 && kv.q_scale != 0.f) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] *= kv.q_scale;
+      }
+      if (part == 0) {
+        store8(reinterpret_cast<T *>(epi.C) + (size_t)row * epi.ldc + col, v);
+      } else if (part == 1) {
+        const int brow = lrow < kv.split ? kv.row0a + lrow : kv.row0b + (lrow - kv.split);
+        store8(reinterpret_cast<T *>(kv.kbuf) + (size_t)img * kv.img_stride + ((size_t)hh * kv.Lp + brow) * kv.dh + ch, v);
+      }
+      // part 2 (v) is written by the transposed pass below
+    } else if (epi.mode == 0) {
+      if (col + 8 > epi.gelu_from) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (col + e >= epi.gelu_from) v[e] = gelu_f(v[e], epi.gelu_tanh);
+      }
+      store8(reinterpret_cast<T *>(epi.C) + (size_t)row * epi.ldc + col, v);
+    } else {
+      float4 r0, r1, g0, g1;
+      bool have = false;
+      if constexpr (PRE) {
+        if (ops->on) { r0 = ops->r[it][0]; r1 = ops->r[it][1]; g0 = ops->g[it][0]; g1 = ops->g[it][1]; have = true; }
+      }
+      if (!have) {
+        const float *rp = epi.R + (size_t)row * epi.ldr + col;
+        r0 = *reinterpret_cast<const float4 *>(rp); r1 = *reinterpret_cast<const float4 *>(rp + 4);
+        if (epi.gate) {
+          const float *gp = epi.gate_of(row) + col;
+          g0 = *reinterpret_cast<const float4 *>(gp); g1 = *reinterpret_cast<const float4 *>(gp + 4);
+        }
+      }
+      float x[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
+      if (epi.gate) {
+        float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] += gg[e] * v[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] += v[e];
+      }
+      float *xp = reinterpret_cast<float *>(epi.C) + (size_t)row * epi.ldc + col;
+      *reinterpret_cast<float4 *>(xp) = make_float4(x[0], x[1], x[2], x[3]);
+      *reinterpret_cast<float4 *>(xp + 4) = make_float4(x[4], x[5], x[6], x[7]);
+      if (epi.C2) store8(epi.C2 + (size_t)row * epi.ldc2 + col, x);
+    }
+  }
+  // v columns of a routed QKV projection: V^T[h][c][buffer row].  The tile is walked column-wise, eight consecutive
+  // rows per thread and consecutive threads along the rows, so that the stores run along V^T's contiguous axis.
+  if (epi.mode == 0 && epi.kv.kbuf && n0 + BN > 2 * epi.kv.d) {
+    const KvRoute &kv = epi.kv;
+    constexpr int RG = BM / 8;
+    for (int u = threadIdx.x; u < RG * BN; u += NT) {
+      const int rg = u % RG, cl = u / RG;
+      const int col = n0 + cl, row = m0 + rg * 8;
+      if (col >= N || col < 2 * kv.d || row >= M) continue;
+      const int cc = col - 2 * kv.d;
+      const float b = epi.bias ? (float)epi.bias[col] : 0.f;
+      float o[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = tile[(rg * 8 + e) * TLD + cl] + b;
+      T *vt = reinterpret_cast<T *>(kv.vtbuf) + (size_t)cc * kv.Lp;   // cc = h*dh + c; image 0
+      const int img = kv.seg > 0 ? row / kv.seg : 0;
+      const int lrow = row - img * kv.seg;
+      const int brow = lrow < kv.split ? kv.row0a + lrow : kv.row0b + (lrow - kv.split);
+      const bool whole = row + 8 <= M && (kv.seg <= 0 || lrow + 8 <= kv.seg) && (lrow >= kv.split || lrow + 8 <= kv.split);
+      if (whole && (brow & 7) == 0) {
+        store8(vt + (size_t)img * kv.img_stride + brow, o);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int r2 = row + e;
+          if (r2 >= M) break;
+          const int i2 = kv.seg > 0 ? r2 / kv.seg : 0;
+          const int l2 = r2 - i2 * kv.seg;
+          vt[(size_t)i2 * kv.img_stride + (l2 < kv.split ? kv.row0a + l2 : kv.row0b + (l2 - kv.split))] = (T)o[e];
+        }
+      }
+    }
+  }
+}
+
+// Cut of the tile grid over the 8 XCDs (see tile_of_block): the gx in {1, 2, 4, 8} for which an XCD's block needs the
+// fewest operand rows; a cut that pads the grid by more than an eighth is priced four times.  *grid receives the
+// workgroup count.
+inline int xcd_cut(const GemmArgs &a, int BM, int BN, unsigned *grid) {
+  const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
+  int best = 1;
+  double best_cost = 1e300;
+  const int64_t T = (int64_t)tiles_m * tiles_n;
+  for (int gx = 1; gx <= 8; gx *= 2) {
+    const int gy = 8 / gx;
+    const int bm = (tiles_m + gx - 1) / gx, bn = (tiles_n + gy - 1) / gy;
+    const int64_t padded = 8LL * bm * bn;
+    double cost = (double)bm * BM + (double)bn * BN;          // operand rows per XCD (both operands have K columns)
+    if (padded * 8 > T * 9) cost *= 4.0;                       // too many idle workgroup slots
+    if (cost < best_cost) { best_cost = cost; best = gx; }
+  }
+  const int gy = 8 / best;
+  const int bm = (tiles_m + best - 1) / best, bn = (tiles_n + gy - 1) / gy;
+  *grid = (unsigned)(8 * bm * bn);
+  return best;
+}
+
+inline bool vec_epilogue_ok(const GemmArgs &a) {
+  auto al = [](const void *p, uintptr_t n) { return ((uintptr_t)p % n) == 0; };
+  bool ok = (!a.bias || al(a.bias, 16));
+  if (a.epilogue == 0) return ok && al(a.C, 16) && a.ldc % 8 == 0;
+  ok = ok && al(a.C, 16) && a.ldc % 4 == 0 && al(a.R, 16) && a.ldr % 4 == 0 && (!a.gate || (al(a.gate, 16) && a.gate_stride % 4 == 0));
+  if (a.C2) ok = ok && al(a.C2, 16) && a.ldc2 % 8 == 0;
+  return ok;
+}
+
+}  // namespace
+
+}  // namespace pf

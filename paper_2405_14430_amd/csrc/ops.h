@@ -74,7 +74,7 @@ struct GemmArgs {
   int tile;            // 0: the tile heuristic picks; 1 .. gemm_mfma_dl_tile_count(): that tile configuration, this launch only
 };
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
-bool gemm_kv_route_supported(const GemmArgs &a);   // the fused QKV -> K/V^T write needs the vectorised bf16 epilogue
+bool gemm_kv_route_supported(const GemmArgs &a);   // the fused QKV -> K/V^T write needs an MFMA kernel's vectorised epilogue
 
 // (cos, sin) of the RoPE angles for the rows of a call: rows [0, n_text) are text (no rotation), row n_text + i is image
 // token tok0 + i on a grid of width grid_w.  tab is float2 [rows][dh/2].
@@ -105,7 +105,7 @@ struct AttnArgs {
                        // batch x n_heads heads, image-major; the workspace is sized for n_heads * batch heads
 };
 size_t attention_ws_bytes(int nq, int n_heads, int head_dim, int splits);
-hipError_t launch_attention(const AttnArgs &a, hipStream_t s, bool *used_combine);
+hipError_t launch_attention(const AttnArgs &a, hipStream_t s);   // the partial results of a split launch await launch_attn_combine
 
 hipError_t launch_axpby(const float *x, const float *y, float a, float b, float *out, int64_t n, hipStream_t s);
 hipError_t launch_mfma_loop(float *out, int workgroups, int iters, hipStream_t s);   // measurement aid (probe.hip)
@@ -126,7 +126,12 @@ bool attn_mfma2_supported(const AttnArgs &a);              // direct-to-LDS vari
 hipError_t launch_attn_mfma2(const AttnArgs &a, hipStream_t s);
 int attn_mfma2_qtile(int nq);                              // queries per workgroup it will use for nq query rows per image
 bool attn_mfma2_takes_prescaled_q(int head_dim);           // its kernel for this head size has a prescaled-q variant
-hipError_t launch_attn_bf16(const AttnArgs &a, hipStream_t s);   // picks between the two
+bool gemm_mfma_f32_supported(const GemmArgs &a);           // fp32 MFMA GEMM (K % 32 == 0, aligned operand rows)
+hipError_t launch_gemm_mfma_f32(const GemmArgs &a, hipStream_t s);
+const char *gemm_mfma_f32_variant_name(const GemmArgs &a);
+bool attn_mfma_f32_head_size(int head_dim);                // fp32 MFMA attention: head sizes 64 / 72 / 128
+bool attn_mfma_f32_supported(const AttnArgs &a);
+hipError_t launch_attn_mfma_f32(const AttnArgs &a, hipStream_t s);
 hipError_t launch_attn_combine(const AttnArgs &a, hipStream_t s);
 
 }  // namespace pf

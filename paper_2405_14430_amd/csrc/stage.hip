@@ -82,7 +82,7 @@ Derived derive(const pf_config *c) {
   return d;
 }
 
-int use_path(const pf_config *c) { return (c->dtype == PF_BF16 && c->kernel_path == PF_PATH_AUTO) ? PATH_AUTO : PATH_SIMT; }
+int use_path(const pf_config *c) { return c->kernel_path == PF_PATH_AUTO ? PATH_AUTO : PATH_SIMT; }
 
 // Split of the key range of an attention launch.  The chip holds 512 attention workgroups of 128 queries at a time (two
 // per CU; 256 of the 256-query kind), so a launch runs in ceil(workgroups / 512) rounds; the split count is picked to minimise a small cost model in units of
@@ -90,14 +90,18 @@ int use_path(const pf_config *c) { return (c->dtype == PF_BF16 && c->kernel_path
 // a single workgroup (no second wave per SIMD to overlap with), and the combine pass that grows with the split count.
 // Measured on MI355X: Flux-scale patch (384 blocks) 4 splits 478 us vs 2 splits 503 us vs none 583 us; SD3-scale patch
 // (96 blocks) 5 splits 34 us vs 6 splits 38 us.
-int choose_splits(int path, int nq, int H, int kv_rows, int head_dim) {
-  const bool gen2 = path != PATH_SIMT && pf::g_attn_variant == 0 && (head_dim == 64 || head_dim == 72 || head_dim == 128);
-  const int qtile = path == PATH_SIMT ? 64 : (gen2 ? attn_mfma2_qtile(nq) : 128);
+// fp32 launches are counted in 64-query workgroups and 32-key tiles; a tile of their MFMA kernel takes about a microsecond,
+// so a split is worth its combine pass from two tiles on (64 queries x 6 heads over 256 keys: 4 splits of 2 tiles).
+int choose_splits(int path, int dt, int nq, int H, int kv_rows, int head_dim) {
+  const bool f32 = dt == PF_F32, simt = path == PATH_SIMT || f32;
+  const bool gen2 = !simt && pf::g_attn_variant == 0 && (head_dim == 64 || head_dim == 72 || head_dim == 128);
+  const int qtile = simt ? 64 : (gen2 ? attn_mfma2_qtile(nq) : 128);
   const int resident = qtile == 256 ? 256 : 512;   // workgroups the chip holds at a time
-  const int ktile = path == PATH_SIMT ? 32 : 64;
+  const int ktile = simt ? 32 : 64;
   const int64_t blocks = (int64_t)((nq + qtile - 1) / qtile) * H;
   const int tiles = (kv_rows + ktile - 1) / ktile;
-  int cap = tiles / 4;  // at least four tiles per split
+  // at least four tiles per split (fp32 MFMA: two)
+  int cap = f32 && path != PATH_SIMT && attn_mfma_f32_head_size(head_dim) ? tiles / 2 : tiles / 4;
   if (cap > 16) cap = 16;
   if (g_force_splits > 0) return g_force_splits < (cap < 1 ? 1 : cap) ? g_force_splits : (cap < 1 ? 1 : cap);
   int best = 1;
@@ -155,10 +159,10 @@ WsLayout ws_layout(const pf_config *c, const Derived &d) {
   int shapes[5] = {d.n, d.n + d.Tj, d.Lkv, d.Tj > 0 ? d.Tj : d.n, c->seq_img};
   const int HB = c->n_heads * d.B;
   for (int nq : shapes) {
-    size_t b = attention_ws_bytes(nq, HB, c->head_dim, choose_splits(path, nq, HB, d.Lkv, c->head_dim));
+    size_t b = attention_ws_bytes(nq, HB, c->head_dim, choose_splits(path, c->dtype, nq, HB, d.Lkv, c->head_dim));
     if (b > ab) ab = b;
     if (c->kind == PF_BLOCK_ADALN_SINGLE_XATTN) {
-      b = attention_ws_bytes(nq, HB, c->head_dim, choose_splits(path, nq, HB, d.T, c->head_dim));
+      b = attention_ws_bytes(nq, HB, c->head_dim, choose_splits(path, c->dtype, nq, HB, d.T, c->head_dim));
       if (b > ab) ab = b;
     }
   }
@@ -263,7 +267,7 @@ hipError_t gemm(pf_stage *s, int cls, const void *A, int64_t lda, const void *W,
 int plan_splits(const pf_stage *s, int nq, int kv_rows) {
   const int path = use_path(&s->cfg);
   const int HB = s->cfg.n_heads * s->d.B;
-  int splits = choose_splits(path, nq, HB, kv_rows, s->cfg.head_dim);
+  int splits = choose_splits(path, s->cfg.dtype, nq, HB, kv_rows, s->cfg.head_dim);
   while (splits > 1 && attention_ws_bytes(nq, HB, s->cfg.head_dim, splits) > s->w.attn_bytes) --splits;
   return splits;
 }
@@ -278,7 +282,7 @@ hipError_t attention(pf_stage *s, int cls, const void *q, int64_t ldq, const voi
   a.q_prescaled = q_prescaled ? 1 : 0;
   a.splits = plan_splits(s, nq, kv_rows);
   a.ws = (float *)(s->ws + s->w.attn);
-  hipError_t e = run(s, cls, [&] { return a.path == PATH_SIMT ? launch_attn_simt(a, s->stream) : launch_attn_bf16(a, s->stream); });
+  hipError_t e = run(s, cls, [&] { return launch_attention(a, s->stream); });
   if (e != hipSuccess) return e;
   if (a.splits > 1) e = run(s, PF_KC_ATTN_COMBINE, [&] { return launch_attn_combine(a, s->stream); });
   return e;
@@ -431,7 +435,7 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
   const int row0_img = d.Tj + img_off;   // buffer row of the first image row of this call
   // The bf16 attention kernel has a variant that takes q already multiplied by log2(e) / sqrt(dh); the factor is folded
   // into the fp32 step that writes q (GEMM epilogue, or the scatter kernel when it normalises / rotates).
-  const bool pre_ok = use_path(&c) == PATH_AUTO && pf::g_attn_variant == 0 && attn_mfma2_takes_prescaled_q(c.head_dim) &&
+  const bool pre_ok = dt == PF_BF16 && use_path(&c) == PATH_AUTO && pf::g_attn_variant == 0 && attn_mfma2_takes_prescaled_q(c.head_dim) &&
                       g_fold_q_scale;
   const float q_fold = 1.4426950408889634f / sqrtf((float)c.head_dim);
   bool q_pre = false;
@@ -776,7 +780,7 @@ pf_status pf_op_gemm_tile(int tile, int dtype, int path, const void *A, int64_t 
   if (epilogue == 1 && ldr < N) return PF_ERR_SHAPE;
   if (C2 && ldc2 < N) return PF_ERR_SHAPE;
   GemmArgs g{};
-  g.dt = dtype; g.path = (dtype == PF_BF16 && path == PF_PATH_AUTO) ? PATH_AUTO : PATH_SIMT;
+  g.dt = dtype; g.path = path == PF_PATH_AUTO ? PATH_AUTO : PATH_SIMT;
   g.A = A; g.lda = lda; g.W = W; g.ldw = ldw; g.bias = bias; g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K;
   g.epilogue = epilogue; g.gelu_from = gelu_from; g.gelu_tanh = gelu_tanh; g.gate = gate; g.R = R; g.ldr = ldr; g.C2 = C2; g.ldc2 = ldc2;
   g.tile = tile;
@@ -816,13 +820,16 @@ pf_status pf_op_axpby(const float *x, const float *y, float a, float b, float *o
 
 const char *pf_gemm_kernel_name(int dtype, int path, int M, int N, int K) {
   GemmArgs g{};
-  g.dt = dtype; g.path = (dtype == PF_BF16 && path == PF_PATH_AUTO) ? PATH_AUTO : PATH_SIMT; g.M = M; g.N = N; g.K = K;
-  if (g.path == PATH_SIMT || dtype != PF_BF16) return "gemm_simt_kernel";
+  g.dt = dtype; g.path = path == PF_PATH_AUTO ? PATH_AUTO : PATH_SIMT; g.M = M; g.N = N; g.K = K;
+  g.lda = g.ldw = K;   // dense operands at aligned addresses
+  if (dtype == PF_F32) return gemm_mfma_f32_supported(g) ? gemm_mfma_f32_variant_name(g) : "gemm_simt_kernel";
+  if (g.path == PATH_SIMT) return "gemm_simt_kernel";
   return gemm_mfma_dl_supported(g) ? gemm_mfma_dl_variant_name(g) : "gemm_mfma_kernel";
 }
 
 const char *pf_attention_kernel_name(int dtype, int path, int head_dim, int nq, int q_prescaled) {
-  if (dtype != PF_BF16 || path != PF_PATH_AUTO) return "attn_simt_kernel";
+  if (path != PF_PATH_AUTO) return "attn_simt_kernel";
+  if (dtype == PF_F32) return attn_mfma_f32_head_size(head_dim) ? "attn_mfma_f32_kernel" : "attn_simt_kernel";
   if (pf::g_attn_variant != 0 || !(head_dim == 64 || head_dim == 72 || head_dim == 128)) return "attn_mfma_kernel";
   static thread_local char name[64];
   const bool wide = attn_mfma2_qtile(nq) == 256;
@@ -859,13 +866,13 @@ static pf_status attention_launch(int dtype, int path, const void *q, int64_t ld
                                   int splits, float *ws, hipStream_t st) {
   AttnArgs a{};
   const bool prescaled = path == PF_PATH_AUTO_PRESCALED_Q;
-  a.dt = dtype; a.path = (dtype == PF_BF16 && (path == PF_PATH_AUTO || prescaled)) ? PATH_AUTO : PATH_SIMT;
+  a.dt = dtype; a.path = path == PF_PATH_AUTO || prescaled ? PATH_AUTO : PATH_SIMT;
   a.q_prescaled = prescaled ? 1 : 0;
   a.q = q; a.ldq = ldq; a.kbuf = kbuf; a.vtbuf = vtbuf; a.kv_rows = kv_rows; a.rows_padded = rows_padded; a.n_heads = n_heads;
   a.head_dim = head_dim; a.out = out; a.ldo = ldo; a.nq = nq; a.splits = splits; a.ws = ws;
   if (prescaled && (dtype != PF_BF16 || !pf::attn_mfma2_takes_prescaled_q(head_dim) || !pf::attn_mfma2_supported(a) || pf::g_attn_variant != 0))
     return fail(nullptr, PF_ERR_SHAPE, "PF_PATH_AUTO_PRESCALED_Q needs bf16 and head_dim 64, 72 or 128");
-  hipError_t e = a.path == PATH_SIMT ? launch_attn_simt(a, st) : launch_attn_bf16(a, st);
+  hipError_t e = launch_attention(a, st);
   if (e == hipSuccess && splits > 1) e = launch_attn_combine(a, st);
   return e == hipSuccess ? PF_OK : PF_ERR_DEVICE;
 }
@@ -932,11 +939,15 @@ pf_status pf_op_attention_static(int dtype, int path, const void *q, int64_t ldq
 }  // extern "C"
 
 namespace pf {
-hipError_t launch_attn_bf16(const AttnArgs &a, hipStream_t s) {
+hipError_t launch_attention(const AttnArgs &a, hipStream_t s) {
+  if (a.path == PATH_SIMT) return launch_attn_simt(a, s);
+  if (a.dt == DT_F32) return attn_mfma_f32_supported(a) ? launch_attn_mfma_f32(a, s) : launch_attn_simt(a, s);
   return (g_attn_variant == 0 && attn_mfma2_supported(a)) ? launch_attn_mfma2(a, s) : launch_attn_mfma(a, s);
 }
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s) {
-  if (a.path == PATH_SIMT || a.dt != DT_BF16) return launch_gemm_simt(a, s);
+  if (a.M <= 0 || a.N <= 0) return hipSuccess;
+  if (a.path == PATH_SIMT) return launch_gemm_simt(a, s);
+  if (a.dt == DT_F32) return gemm_mfma_f32_supported(a) ? launch_gemm_mfma_f32(a, s) : launch_gemm_simt(a, s);
   return gemm_mfma_dl_supported(a) ? launch_gemm_mfma_dl(a, s) : launch_gemm_mfma(a, s);
 }
 }  // namespace pf
