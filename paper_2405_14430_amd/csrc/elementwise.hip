@@ -102,19 +102,24 @@ hipError_t launch_modulation(int dt, const void *w, const void *b, const float *
 // is only that many waves) are split over two or four waves each, which exchange their partial sums through LDS.
 // NC = float4 chunks per lane; d <= NC * 256 * WPR.
 // ------------------------------------------------------------------------------------------------
-template <typename T, int NC, int WPR>
-__global__ __launch_bounds__(256) void ln_modulate_kernel(const float *__restrict__ x, int64_t ldx,
-                                                          const float *__restrict__ shift,
-                                                          const float *__restrict__ scale, float eps,
-                                                          T *__restrict__ out, int64_t ldo, int rows, int d,
-                                                          int normalize, int seg_rows, int64_t seg_stride) {
-  // rows are image-major, seg_rows per image; image b uses shift + b * seg_stride, scale + b * seg_stride
+template <typename T, int NC, int WPR, bool PAIR>
+__global__ __launch_bounds__(256) void ln_modulate_kernel(LnRows ra, LnRows rb, int64_t ldx, float eps, int64_t ldo, int d,
+                                                          int normalize, int64_t seg_stride) {
+  // rows [0, ra.rows) are ra's, the rest rb's; each set is image-major, seg_rows per image, and image b uses
+  // shift + b * seg_stride, scale + b * seg_stride
   constexpr int RPB = 4 / WPR;                       // rows per block
   __shared__ float part[2][4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wir = wave % WPR;                        // this wave's index inside its row
-  const int row = blockIdx.x * RPB + wave / WPR;
-  const bool live = row < rows;                      // (waves of a dead row still meet the barriers)
+  const int grow = blockIdx.x * RPB + wave / WPR;
+  const bool live = grow < ra.rows + (PAIR ? rb.rows : 0);        // (waves of a dead row still meet the barriers)
+  const bool in_b = PAIR && live && grow >= ra.rows;
+  const int row = in_b ? grow - ra.rows : grow;
+  const float *__restrict__ x = in_b ? rb.x : ra.x;
+  const float *__restrict__ shift = in_b ? rb.shift : ra.shift;
+  const float *__restrict__ scale = in_b ? rb.scale : ra.scale;
+  T *__restrict__ out = reinterpret_cast<T *>(in_b ? rb.out : ra.out);
+  const int seg_rows = in_b ? rb.seg_rows : ra.seg_rows;
   if (live && seg_rows > 0) {
     const int64_t o = (int64_t)(row / seg_rows) * seg_stride;
     shift += o;
@@ -184,44 +189,41 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float *__restric
   }
 }
 
-template <typename T, int NC, int WPR>
-static void ln_launch(const float *x, int64_t ldx, const float *shift, const float *scale, float eps, void *out,
-                      int64_t ldo, int rows, int d, int normalize, int seg_rows, int64_t seg_stride, hipStream_t s) {
-  constexpr int RPB = 4 / WPR;
-  ln_modulate_kernel<T, NC, WPR><<<dim3((rows + RPB - 1) / RPB), 256, 0, s>>>(x, ldx, shift, scale, eps, (T *)out, ldo, rows, d,
-                                                                          normalize, seg_rows, seg_stride);
-}
-
 template <typename T, int WPR>
-static hipError_t ln_dispatch_wpr(const float *x, int64_t ldx, const float *shift, const float *scale, float eps,
-                                  void *out, int64_t ldo, int rows, int d, int normalize, int seg_rows, int64_t seg_stride,
-                                  hipStream_t s) {
-  int need = (d + 256 * WPR - 1) / (256 * WPR);
+static hipError_t ln_dispatch_wpr(const LnRows &a, const LnRows &b, int64_t ldx, float eps, int64_t ldo, int d, int normalize,
+                                  int64_t seg_stride, hipStream_t s) {
+  constexpr int RPB = 4 / WPR;
+  const dim3 grid((a.rows + b.rows + RPB - 1) / RPB);
+  const int need = (d + 256 * WPR - 1) / (256 * WPR);
 #define PF_LN_CASE(NC) \
-  if (need <= NC) { ln_launch<T, NC, WPR>(x, ldx, shift, scale, eps, out, ldo, rows, d, normalize, seg_rows, seg_stride, s); return hipGetLastError(); }
+  if (need <= NC) { \
+    if (b.rows > 0) ln_modulate_kernel<T, NC, WPR, true><<<grid, 256, 0, s>>>(a, b, ldx, eps, ldo, d, normalize, seg_stride); \
+    else ln_modulate_kernel<T, NC, WPR, false><<<grid, 256, 0, s>>>(a, b, ldx, eps, ldo, d, normalize, seg_stride); \
+    return hipGetLastError(); \
+  }
   PF_LN_CASE(1) PF_LN_CASE(2) PF_LN_CASE(3) PF_LN_CASE(4) PF_LN_CASE(5) PF_LN_CASE(6) PF_LN_CASE(8) PF_LN_CASE(12) PF_LN_CASE(16) PF_LN_CASE(32)
 #undef PF_LN_CASE
   return hipErrorInvalidValue;  // d > 8192 is rejected by the caller
 }
 
 template <typename T>
-static hipError_t ln_dispatch(const float *x, int64_t ldx, const float *shift, const float *scale, float eps,
-                              void *out, int64_t ldo, int rows, int d, int normalize, int seg_rows, int64_t seg_stride,
-                              hipStream_t s) {
+static hipError_t ln_dispatch(const LnRows &a, const LnRows &b, int64_t ldx, float eps, int64_t ldo, int d, int normalize,
+                              int64_t seg_stride, hipStream_t s) {
   // one wave per row needs about 8192 rows to keep every CU busy with memory requests (32 waves per CU); below that
   // the rows are split (a row of fewer than 512 floats is not worth splitting)
+  const int rows = a.rows + b.rows;
   const int wpr = (rows >= 8192 || d < 512) ? 1 : ((rows >= 4096 || d < 1024) ? 2 : 4);
-  if (wpr == 4) return ln_dispatch_wpr<T, 4>(x, ldx, shift, scale, eps, out, ldo, rows, d, normalize, seg_rows, seg_stride, s);
-  if (wpr == 2) return ln_dispatch_wpr<T, 2>(x, ldx, shift, scale, eps, out, ldo, rows, d, normalize, seg_rows, seg_stride, s);
-  return ln_dispatch_wpr<T, 1>(x, ldx, shift, scale, eps, out, ldo, rows, d, normalize, seg_rows, seg_stride, s);
+  if (wpr == 4) return ln_dispatch_wpr<T, 4>(a, b, ldx, eps, ldo, d, normalize, seg_stride, s);
+  if (wpr == 2) return ln_dispatch_wpr<T, 2>(a, b, ldx, eps, ldo, d, normalize, seg_stride, s);
+  return ln_dispatch_wpr<T, 1>(a, b, ldx, eps, ldo, d, normalize, seg_stride, s);
 }
 
-hipError_t launch_ln_modulate(int dt, const float *x, int64_t ldx, const float *shift, const float *scale,
-                              float eps, void *out, int64_t ldo, int rows, int d, int normalize, hipStream_t s,
-                              int seg_rows, int64_t seg_stride) {
-  if (rows <= 0) return hipSuccess;
-  return dt == DT_BF16 ? ln_dispatch<bf16_t>(x, ldx, shift, scale, eps, out, ldo, rows, d, normalize, seg_rows, seg_stride, s)
-                       : ln_dispatch<float>(x, ldx, shift, scale, eps, out, ldo, rows, d, normalize, seg_rows, seg_stride, s);
+hipError_t launch_ln_modulate(int dt, const LnRows &a, const LnRows *pb, int64_t ldx, float eps, int64_t ldo, int d, int normalize,
+                              int64_t seg_stride, hipStream_t s) {
+  const LnRows b = pb ? *pb : LnRows{};
+  if (a.rows + b.rows <= 0) return hipSuccess;
+  return dt == DT_BF16 ? ln_dispatch<bf16_t>(a, b, ldx, eps, ldo, d, normalize, seg_stride, s)
+                       : ln_dispatch<float>(a, b, ldx, eps, ldo, d, normalize, seg_stride, s);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -3,7 +3,7 @@
 //   mode 1: X[row][col] (fp32)  = R[row][col] + gate[col] * (acc + bias[col]); optional rounded copy in C2
 // A mode-0 launch that is a QKV projection may carry a KvRoute: its k and v columns then go straight into a layer's
 // K / V^T buffers at the patch's rows (the write-before-attend step of PipeFusion Sec. 3.3) instead of into C, and
-// q and k are rotated with a precomputed (cos, sin) table when the stage uses RoPE.  Only the vectorised LDS-staged
+// q and k are normalised per head and rotated with a precomputed (cos, sin) table when the stage does so.  Only the vectorised LDS-staged
 // epilogue of the direct-to-LDS GEMM kernels implements the route.
 #pragma once
 #include "common.h"
@@ -20,6 +20,8 @@ struct KvRoute {
   int seg;                     // > 0: GEMM rows are image-major, seg rows per image; mapping applies inside the image
   int64_t img_stride;          // elements between consecutive images' K (and V^T) buffers
   float q_scale;               // != 0: q columns are multiplied by it (the attention kernel's log2(e) / sqrt(dh))
+  const void *q_norm, *k_norm; // [dh] scales of the per-head RMSNorm of q and k (bias included, before RoPE), or nullptr;
+  float norm_eps;              // needs tiles a whole number of heads wide
 };
 
 template <typename T>
@@ -55,7 +57,8 @@ template <typename T, typename Args>
 inline Epilogue<T> make_epilogue(const Args &a) {
   Epilogue<T> e;
   e.kv = KvRoute{a.kvr.kbuf, a.kvr.vtbuf, a.kvr.Lp, a.kvr.dh, a.kvr.d, a.kvr.split, a.kvr.row0a, a.kvr.row0b,
-                 (const float2 *)a.kvr.rope, a.kvr.seg, a.kvr.img_stride, a.kvr.q_scale};
+                 (const float2 *)a.kvr.rope, a.kvr.seg, a.kvr.img_stride, a.kvr.q_scale,
+                 a.kvr.q_norm, a.kvr.k_norm, a.kvr.norm_eps};
   e.bias = (const T *)a.bias; e.C = a.C; e.ldc = a.ldc; e.mode = a.epilogue; e.gelu_from = a.gelu_from;
   e.gelu_tanh = a.gelu_tanh; e.gate = a.gate; e.gate_seg = a.gate_seg; e.gate_stride = a.gate_stride; e.R = a.R; e.ldr = a.ldr; e.C2 = (T *)a.C2; e.ldc2 = a.ldc2;
   return e;

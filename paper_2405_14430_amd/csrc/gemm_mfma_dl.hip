@@ -30,10 +30,15 @@ constexpr int ROW_BYTES = BK * 2;  // 128
 // ------------------------------------------------------------------------------------------------------------------
 // WGM x WGN wavefronts on one shared tile
 // ------------------------------------------------------------------------------------------------------------------
-template <int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, int KB = 64, bool SPREAD_LOADS = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(const bf16_t *__restrict__ A, int64_t lda,
-                                                        const bf16_t *__restrict__ W, int64_t ldw, int M, int N, int K,
-                                                        Epilogue<bf16_t> epi, int vec_ok, int xcd_gx) {
+template <int NP, int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, int KB = 64, bool SPREAD_LOADS = false>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf16_t, NP> L) {
+  const bool second = NP == 2 && blockIdx.x >= L.grid0;
+  const GemmProblem<bf16_t> &prob = L.p[second ? 1 : 0];
+  const bf16_t *__restrict__ A = prob.A, *__restrict__ W = prob.W;
+  const int64_t lda = prob.lda, ldw = prob.ldw;
+  const int M = prob.M, N = L.N, K = L.K;
+  const Epilogue<bf16_t> &epi = prob.epi;
+  const int vec_ok = prob.vec_ok;
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int MI = WM / 32, NI = WN / 32;
@@ -53,7 +58,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(const bf16_t 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   int tm, tn;
-  if (!tile_of_block((M + BM - 1) / BM, (N + BN - 1) / BN, xcd_gx, tm, tn)) return;
+  if (!tile_of_id((int)(blockIdx.x - (second ? L.grid0 : 0)), (M + BM - 1) / BM, (N + BN - 1) / BN, prob.xcd_gx, tm, tn)) return;
   const int m0 = tm * BM, n0 = tn * BN;
 
   // per-lane byte offsets of this wave's load instructions inside the tile's rows (rows past the matrix repeat its last row)
@@ -71,9 +76,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(const bf16_t 
     int c = (lane % CPR) ^ key(r);
     pw[i] = (unsigned)(((size_t)min(r, N - 1 - n0) * ldw + c * 8) * 2);
   }
-  auto issue = [&](int stage, int kt) {
+  const int nk = K / KB, k0 = L.kshift ? tn % nk : 0;   // first K tile (see GemmLaunch)
+  auto issue = [&](int stage, int kt0) {
     unsigned char *sa = smem + stage * STAGE_BYTES;
     unsigned char *sw = sa + BM * RBY;
+    const int kt = kt0 + k0 >= nk ? kt0 + k0 - nk : kt0 + k0;
     const unsigned koff = (unsigned)kt * (KB * 2);
 #pragma unroll
     for (int i = 0; i < LA; ++i) srcA.load16(pa[i], koff, sa + (i * NW + wave) * 1024);
@@ -81,8 +88,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(const bf16_t 
     for (int i = 0; i < LW; ++i) srcW.load16(pw[i], koff, sw + (i * NW + wave) * 1024);
   };
   // load instruction `idx` (A instructions first, then W) of this wave for K tile kt
-  auto issue_one = [&](auto idx_c, int stage, int kt) __attribute__((always_inline)) {
+  auto issue_one = [&](auto idx_c, int stage, int kt0) __attribute__((always_inline)) {
     constexpr int idx = decltype(idx_c)::value;
+    const int kt = kt0 + k0 >= nk ? kt0 + k0 - nk : kt0 + k0;
     unsigned char *sa = smem + stage * STAGE_BYTES;
     const unsigned koff = (unsigned)kt * (KB * 2);
     if constexpr (idx < LA) srcA.load16(pa[idx], koff, sa + (idx * NW + wave) * 1024);
@@ -102,7 +110,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(const bf16_t 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int nk = K / KB;
 #pragma unroll
   for (int s = 0; s < NSTAGE - 1; ++s)
     if (s < nk) issue(s, s);
@@ -206,10 +213,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(const bf16_t 
 // ------------------------------------------------------------------------------------------------------------------
 // four wavefronts split K; each owns a private two-stage ring for its own BM x BN x 64 tiles
 // ------------------------------------------------------------------------------------------------------------------
-template <int BM, int BN>
-__global__ __launch_bounds__(256) void gemm_wavek_kernel(const bf16_t *__restrict__ A, int64_t lda,
-                                                         const bf16_t *__restrict__ W, int64_t ldw, int M, int N, int K,
-                                                         Epilogue<bf16_t> epi, int vec_ok, int xcd_gx) {
+template <int NP, int BM, int BN>
+__global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> L) {
+  const bool second = NP == 2 && blockIdx.x >= L.grid0;
+  const GemmProblem<bf16_t> &prob = L.p[second ? 1 : 0];
+  const bf16_t *__restrict__ A = prob.A, *__restrict__ W = prob.W;
+  const int64_t lda = prob.lda, ldw = prob.ldw;
+  const int M = prob.M, N = L.N, K = L.K;
+  const Epilogue<bf16_t> &epi = prob.epi;
+  const int vec_ok = prob.vec_ok;
   constexpr int MI = BM / 32, NI = BN / 32;
   constexpr int LA = BM / 8, LW = BN / 8;   // load instructions per wave per stage (a wave loads whole tiles)
   constexpr int LPS = LA + LW;
@@ -224,7 +236,7 @@ __global__ __launch_bounds__(256) void gemm_wavek_kernel(const bf16_t *__restric
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tm, tn;
-  if (!tile_of_block((M + BM - 1) / BM, (N + BN - 1) / BN, xcd_gx, tm, tn)) return;
+  if (!tile_of_id((int)(blockIdx.x - (second ? L.grid0 : 0)), (M + BM - 1) / BM, (N + BN - 1) / BN, prob.xcd_gx, tm, tn)) return;
   const int m0 = tm * BM, n0 = tn * BN;
   unsigned char *ring = smem + wave * WAVE_BYTES;
 
@@ -348,35 +360,50 @@ bool gemm_tile_map(int M, int N, int BM, int BN, unsigned id, unsigned *grid, in
 namespace {
 
 template <int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, int KB = 64, bool SPREAD = false>
-hipError_t launch_tile(const GemmArgs &a, hipStream_t s) {
+hipError_t launch_tile(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   // the stage ring, or the fp32 tile (row stride BN + 4) that replaces it for the epilogue, whichever is larger
   constexpr int ring = NSTAGE * (BM + BN) * KB * 2, tile = BM * (BN + 4) * 4;
   constexpr int smem = (tile > ring && tile <= 96 * 1024) ? tile : ring;   // larger tiles finish in row passes
-  if (hipError_t e = allow_dynamic_lds<&gemm_tile_kernel<BM, BN, NSTAGE, WGM, WGN, KB, SPREAD>, smem>(); e != hipSuccess) return e;
-  unsigned grid = 0;
-  const int gx = xcd_cut(a, BM, BN, &grid);
-  dim3 g(grid);
-  gemm_tile_kernel<BM, BN, NSTAGE, WGM, WGN, KB, SPREAD><<<g, 64 * WGM * WGN, smem, s>>>((const bf16_t *)a.A, a.lda, (const bf16_t *)a.W, a.ldw, a.M, a.N,
-                                                       a.K, make_epilogue<bf16_t>(a), vec_epilogue_ok(a) ? 1 : 0, gx);
-  return hipGetLastError();
+  auto go = [&](auto np) -> hipError_t {
+    constexpr int NP = decltype(np)::value;
+    constexpr auto kernel = &gemm_tile_kernel<NP, BM, BN, NSTAGE, WGM, WGN, KB, SPREAD>;
+    if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
+    GemmLaunch<bf16_t, NP> L;
+    // Tile columns start at different K positions for the mid-size K where that was measured to help (operand rows of 6 KB:
+    // workgroups in step would all ask the memory side for the same 128-byte columns): 2048x9216x3072 123 -> 115 us,
+    // 2048x12288x3072 161 -> 153, 2560x9216x3072 153 -> 139, 16896x9216x3072 852 -> 838; nothing to gain at K = 1152 and at
+    // K = 15360, where it costs up to 1 %.
+    const unsigned grid = make_launch(a, b, BM, BN, &L, a.K >= 2048 && a.K <= 8192 ? 1 : 0);
+    kernel<<<grid, 64 * WGM * WGN, smem, s>>>(L);
+    return hipGetLastError();
+  };
+  return b ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
 }
 
 template <int BM, int BN>
-hipError_t launch_wavek(const GemmArgs &a, hipStream_t s) {
+hipError_t launch_wavek(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   constexpr int smem = 4 * 2 * (BM + BN) * ROW_BYTES;
-  if (hipError_t e = allow_dynamic_lds<&gemm_wavek_kernel<BM, BN>, smem>(); e != hipSuccess) return e;
-  unsigned grid = 0;
-  const int gx = xcd_cut(a, BM, BN, &grid);
-  dim3 g(grid);
-  gemm_wavek_kernel<BM, BN><<<g, 256, smem, s>>>((const bf16_t *)a.A, a.lda, (const bf16_t *)a.W, a.ldw, a.M, a.N, a.K,
-                                                make_epilogue<bf16_t>(a), vec_epilogue_ok(a) ? 1 : 0, gx);
-  return hipGetLastError();
+  auto go = [&](auto np) -> hipError_t {
+    constexpr int NP = decltype(np)::value;
+    constexpr auto kernel = &gemm_wavek_kernel<NP, BM, BN>;
+    if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
+    GemmLaunch<bf16_t, NP> L;
+    const unsigned grid = make_launch(a, b, BM, BN, &L);
+    kernel<<<grid, 256, smem, s>>>(L);
+    return hipGetLastError();
+  };
+  return b ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
 }
 
 }  // namespace
 
 bool gemm_kv_route_supported(const GemmArgs &a) {
   const bool kernel = a.dt == DT_BF16 ? a.path != PATH_SIMT && a.K % BK == 0 && a.K >= BK : gemm_mfma_f32_supported(a);
+  // per-head norm: bf16 tiles come in widths of 64 and 128 columns (pick_variant sees to it); the lanes of a head exchange
+  // their sums, so its groups of eight channels have to be a power of two; the scales are read sixteen bytes at a time
+  const int groups = a.kvr.dh / 8;
+  if (a.kvr.q_norm && (a.dt != DT_BF16 || groups > 16 || (groups & (groups - 1)) || (((uintptr_t)a.kvr.q_norm | (uintptr_t)a.kvr.k_norm) & 15)))
+    return false;
   return kernel && a.epilogue == 0 && a.N % 8 == 0 && vec_epilogue_ok(a) && a.kvr.dh % 8 == 0 && a.kvr.d % 8 == 0 && a.N == 3 * a.kvr.d;
 }
 
@@ -386,127 +413,145 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
   return a.K % BK == 0 && a.K >= BK && a.M >= 1 && a.N >= 1 && (256 * ld + a.K) * 2 < 0x7ffffff0LL;
 }
 
-// Tile heuristic, from A/B runs inside the stage on MI355X (weights come from HBM there, not from a warm L2, which
-// favours deeper rings than an isolated GEMM loop suggests):
-//  * the 8-wave 256x256 / 256x128 tiles need the fewest L1 bytes per flop and win once they fill the chip;
-//    256x128 runs best with 32-wide K stages and three of them; long-K GEMMs with few tiles (Flux-scale MLP-down:
-//    192 tiles, K = 15360) prefer it too, with 64-wide stages;
-//  * 128x128 (two workgroups per CU) from about 1.5 workgroups per CU, then 128x64;
-//  * skinny GEMMs (n = 512 patch rows): 64x64 tiles, four stages while every workgroup is resident at once (two per CU:
-//    up to 512 tiles), two stages (five per CU) beyond - the three-stage ring that used to sit between them lost its
-//    edge once the stage's weights stayed in the memory-side cache (SD3-scale MLP-up, 768 tiles: 21.9 -> 20.9 us) -
-//    and the K-splitting kernel when K is long and tiles are few;
-//  * 192-wide tiles (three 32-column blocks per wave) when they cut the output into a whole number of 256-workgroup
-//    rounds, which power-of-two tiles cannot do for widths that are multiples of 3 * 1024 (Flux-scale stage, patch of
-//    2048 rows: QKV 171 -> 144 us with 768 tiles of 128x192, MLP-up 178 -> 172 us with 512 tiles of 256x192, MLP-down
-//    241 -> 214 us with 256 tiles of 128x192 and three stages); not for K = 1152, where the two-stage ring is exposed.
-//  * the three-stage 128x192 tile (long K, few tiles) issues its prefetch loads one at a time between the MFMAs of the
-//    tile instead of in a burst after the barrier (isolated GEMM, interleaved A/B rounds: 2048x3072x15360 204 -> 183 us,
-//    4096x1152x4608 65 -> 55 us; inside the Flux-scale stage 225 -> 193 us).  The other tiles keep the burst: the
-//    two-stage 128x192 tile gains alone (2048x9216x3072 129 -> 122 us) but not inside the stage (150 -> 154 us), the
-//    8-wave tiles and the 64x64 tiles lose (256x192: 152 -> 171 us, 256x256 at 8192^3: 995 -> 1063 us, 64x64: 15.2 ->
-//    17.7 us).
+// Tile choice.
+//
+// Launches with enough tiles to fill the chip (512 of 128x64, or long K and 128 of 256x128): the candidate with the least
+//   rounds x tile area / rate x (K tiles + fill) / K tiles
+// rounds = ceil(tiles / 256 CUs); rate = what a CU does on the tile in steady state, relative to 128x192 (1.0 PFLOP/s on
+// the chip); fill = K tiles' worth of time that the start and the epilogue of a workgroup cost, 2 when a second workgroup of
+// the CU covers them, 8 when the CU holds one.  Measured (us, isolated GEMMs with cold weights; 256x256 | 256x192 | 256x128 |
+// 128x192 | 128x128, * = chosen; the rule before took three-stage 256x128 tiles with 32-wide K tiles from 512 of them on):
+//    2560 x  9216 x  3072   157 | 139* | 148 | 142 | 144    (198 before)
+//    2560 x 12288 x  3072   183* | 209 | 206 | 193 | 203    (272 before)
+//    2560 x  3072 x 15360   374 | 339 | 235* | 296 | 250
+//   16896 x  9216 x  3072   837* | 878 | 964 | 1031 | 1068
+//   16896 x  3072 x 15360  1562* | 1728 | 1662 | 1633 | 1696 (2140 before)
+//    4096 x  4608 x  1152    86 | 68 | 74 | 61* | 71, 128x64 63
+//    4096 x  1152 x  4608   116 | 106 | 70 | 61* | 72, 128x64 70
+// 128x192 takes three stages and issues its prefetch loads one at a time between the MFMAs (instead of in a burst behind the
+// barrier) for long K with at most one tile per CU: 2048x3072x15360 204 -> 183 us, 4096x1152x4608 65 -> 55 us; every other
+// tile loses by it or keeps nothing of the gain inside a stage.
+//
+// Fewer tiles (patches of a few hundred rows), by counts of 64x64 tiles:
+//  * the wave-split-K kernel, one workgroup per CU (128 KB of LDS): up to one tile per CU, from K = 1024 on.  512x1152x1152
+//    8.2 us (four-stage 64x64: 8.9), 512x1152x4608 19.8 (23.6), 512x1536x6144 25.5 (31.5); with more tiles than CUs it loses:
+//    1024x1152x4608 34.3 (29.4).
+//  * 64x64 with four stages while every workgroup is resident at once (two per CU), 375x4608x1536 14.0 us (two stages 19.6);
+//  * beyond, 64x128 with three stages under the same condition: 1024x3456x1152 16.9 -> 15.2 us, 512x6144x1536 22.8 -> 22.0,
+//    512x4608x1536 20.3 -> 18.7 against two-stage 64x64 tiles, which take what is left.
 enum { V_256x256 = 0, V_256x128_K32S3, V_256x128_S3, V_128x128, V_128x64, V_WAVEK, V_64x64_S4, V_64x64_S3, V_64x64_S2,
-       V_128x192_S2, V_256x192_S2, V_128x192_S3, V_COUNT };
+       V_128x192_S2, V_256x192_S2, V_128x192_S3, V_64x128_S3, V_COUNT };
 
-static int pick_variant(const GemmArgs &a) {
-  auto tiles = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
-  if (a.N % 192 == 0 && a.M % 128 == 0) {
-    const int64_t t192 = tiles(128, 192);
-    if (a.K >= 4096 && t192 >= 128 && t192 <= 256) return V_128x192_S3;
-    // shorter K: only with enough rounds that the two-stage ring's exposed start is amortised (PixArt MLP-up on a
-    // 4096-row patch, 768 tiles: 104 -> 89 us)
-    if (a.K >= 1024 && a.K < 2048 && t192 % 256 == 0 && t192 >= 512 && t192 <= 1024) return V_128x192_S2;
-    if (a.K >= 2048 && t192 % 256 == 0 && t192 <= 1024) {
-      const int64_t t2 = a.M % 256 == 0 ? tiles(256, 192) : 0;
-      return (t2 >= 512 && t2 % 256 == 0) ? V_256x192_S2 : V_128x192_S2;
+static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
+  auto tiles = [&](int bm, int bn) { return launch_tiles(a, b, bm, bn); };
+  // per-head norm in the epilogue: heads of 128 channels need tiles of 128 or 256 columns
+  const bool wide_heads = a.kvr.q_norm && a.kvr.dh > 64;
+  if (tiles(128, 64) >= 512 || (a.K >= 4096 && tiles(256, 128) >= 128)) {
+    struct Candidate { int v, bm, bn, per_cu; double rate; };
+    static constexpr Candidate cand[] = {{V_256x256, 256, 256, 1, 1.2}, {V_256x192_S2, 256, 192, 1, 1.1}, {V_256x128_S3, 256, 128, 1, 1.03},
+                                         {V_128x192_S2, 128, 192, 2, 1.0}, {V_128x128, 128, 128, 2, 0.95}, {V_128x64, 128, 64, 3, 0.85}};
+    const double nk = a.K / BK;
+    int best = V_128x128;
+    double best_cost = 1e300;
+    for (const Candidate &c : cand) {
+      if (wide_heads && c.bn % 128) continue;
+      const int64_t t = tiles(c.bm, c.bn);
+      const double fill = c.per_cu > 1 && t > 256 ? 2.0 : 8.0;
+      const double cost = (double)((t + 255) / 256) * c.bm * c.bn / c.rate * (nk + fill) / nk;
+      if (cost < best_cost) { best_cost = cost; best = c.v; }
     }
+    return best == V_128x192_S2 && a.K >= 4096 && tiles(128, 192) <= 256 ? V_128x192_S3 : best;
   }
-  if (tiles(256, 256) >= 1024) return V_256x256;
-  if (tiles(256, 128) >= 512) return V_256x128_K32S3;
-  if (a.K >= 8192 && tiles(256, 128) >= 128) return V_256x128_S3;
-  if (tiles(128, 128) >= 384) return V_128x128;
-  if (tiles(128, 64) >= 512) return V_128x64;
+  if (wide_heads) return V_64x128_S3;
   const int64_t t64 = tiles(64, 64);
-  if (t64 < g_wavek_max_tiles && a.K >= g_wavek_min_k) return V_WAVEK;
-  // one tile per CU at most (the d x d projections of a 512-row patch): the wave-split-K kernel from K = 1024 on
-  // (inside the stage: PixArt-scale cross projections 9.3 -> 8.6 us, SD3-scale out-projection 11.8 -> 10.8 us; with
-  // more tiles than CUs it loses: PixArt-scale QKV 13.2 -> 17.9 us)
-  if (t64 <= 256 && a.K >= 1024) return V_WAVEK;
+  if (t64 <= g_wavek_max_tiles && a.K >= g_wavek_min_k) return V_WAVEK;
   if (t64 <= 512) return V_64x64_S4;
-  return V_64x64_S2;
+  return tiles(64, 128) <= 512 ? V_64x128_S3 : V_64x64_S2;
 }
 
-static hipError_t launch_variant(int v, const GemmArgs &a, hipStream_t s) {
+static hipError_t launch_variant(int v, const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   switch (v) {
-    case V_256x256: return launch_tile<256, 256, 2, 4, 2>(a, s);
-    case V_256x128_K32S3: return launch_tile<256, 128, 3, 4, 2, 32>(a, s);
-    case V_256x128_S3: return launch_tile<256, 128, 3, 4, 2>(a, s);
-    case V_128x128: return launch_tile<128, 128, 2>(a, s);
-    case V_128x64: return launch_tile<128, 64, 2>(a, s);
-    case V_WAVEK: return launch_wavek<64, 64>(a, s);
-    case V_64x64_S4: return launch_tile<64, 64, 4>(a, s);
-    case V_64x64_S3: return launch_tile<64, 64, 3>(a, s);
-    case V_128x192_S2: return launch_tile<128, 192, 2>(a, s);
-    case V_256x192_S2: return launch_tile<256, 192, 2, 4, 2>(a, s);
-    case V_128x192_S3: return launch_tile<128, 192, 3, 2, 2, 64, true>(a, s);
-    default: return launch_tile<64, 64, 2>(a, s);
+    case V_256x256: return launch_tile<256, 256, 2, 4, 2>(a, b, s);
+    case V_256x128_K32S3: return launch_tile<256, 128, 3, 4, 2, 32>(a, b, s);
+    case V_256x128_S3: return launch_tile<256, 128, 3, 4, 2>(a, b, s);
+    case V_128x128: return launch_tile<128, 128, 2>(a, b, s);
+    case V_128x64: return launch_tile<128, 64, 2>(a, b, s);
+    case V_WAVEK: return launch_wavek<64, 64>(a, b, s);
+    case V_64x64_S4: return launch_tile<64, 64, 4>(a, b, s);
+    case V_64x64_S3: return launch_tile<64, 64, 3>(a, b, s);
+    case V_128x192_S2: return launch_tile<128, 192, 2>(a, b, s);
+    case V_256x192_S2: return launch_tile<256, 192, 2, 4, 2>(a, b, s);
+    case V_64x128_S3: return launch_tile<64, 128, 3>(a, b, s);
+    case V_128x192_S3: return launch_tile<128, 192, 3, 2, 2, 64, true>(a, b, s);
+    default: return launch_tile<64, 64, 2>(a, b, s);
   }
 }
 
 int gemm_mfma_dl_tile_count() { return V_COUNT; }
 
-hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s) {
+hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s, const GemmArgs *b) {
 #ifdef PF_TUNING
   // tile configurations outside the heuristic's set, for sweeps
   switch (g_gemm_tile_override) {
-    case 1: return launch_tile<256, 128, 3>(a, s);
-    case 2: return launch_tile<128, 128, 3>(a, s);
-    case 3: return launch_tile<128, 128, 2>(a, s);
-    case 4: return launch_tile<128, 64, 4>(a, s);
-    case 5: return launch_tile<64, 64, 4>(a, s);
-    case 6: return launch_tile<256, 128, 2>(a, s);
-    case 7: return launch_tile<128, 64, 2>(a, s);
-    case 8: return launch_tile<64, 64, 2>(a, s);
-    case 9: return launch_gemm_mfma(a, s);
-    case 10: return launch_wavek<64, 64>(a, s);
-    case 14: return launch_tile<256, 128, 3, 4, 2>(a, s);
-    case 15: return launch_tile<256, 256, 2, 4, 2>(a, s);
-    case 16: return launch_tile<128, 256, 3, 2, 4>(a, s);
-    case 17: return launch_tile<256, 128, 2, 4, 2>(a, s);
-    case 22: return launch_tile<256, 128, 3, 4, 2, 32>(a, s);
-    case 26: return launch_tile<64, 64, 3>(a, s);
-    case 27: return launch_tile<128, 64, 3>(a, s);
-    case 28: return launch_tile<128, 192, 2>(a, s);
-    case 29: return launch_tile<256, 192, 2, 4, 2>(a, s);
-    case 30: return launch_tile<128, 192, 3>(a, s);
-    case 40: return launch_tile<128, 192, 2, 2, 2, 64, true>(a, s);
-    case 41: return launch_tile<256, 192, 2, 4, 2, 64, true>(a, s);
-    case 42: return launch_tile<128, 192, 3, 2, 2, 64, true>(a, s);
-    case 43: return launch_tile<256, 256, 2, 4, 2, 64, true>(a, s);
-    case 44: return launch_tile<256, 128, 3, 4, 2, 64, true>(a, s);
-    case 45: return launch_tile<128, 128, 2, 2, 2, 64, true>(a, s);
-    case 46: return launch_tile<128, 192, 4, 2, 2, 64, true>(a, s);
-    case 47: return launch_tile<128, 128, 3, 2, 2, 64, true>(a, s);
-    case 48: return launch_tile<128, 128, 4, 2, 2, 64, true>(a, s);
-    case 49: return launch_tile<128, 64, 4, 2, 2, 64, true>(a, s);
-    case 50: return launch_tile<64, 64, 4, 2, 2, 64, true>(a, s);
-    case 51: return launch_tile<128, 256, 3, 2, 2, 64, true>(a, s);
-    case 52: return launch_tile<128, 192, 3, 2, 2, 64, false>(a, s);
+    case 1: return launch_tile<256, 128, 3>(a, b, s);
+    case 2: return launch_tile<128, 128, 3>(a, b, s);
+    case 3: return launch_tile<128, 128, 2>(a, b, s);
+    case 4: return launch_tile<128, 64, 4>(a, b, s);
+    case 5: return launch_tile<64, 64, 4>(a, b, s);
+    case 6: return launch_tile<256, 128, 2>(a, b, s);
+    case 7: return launch_tile<128, 64, 2>(a, b, s);
+    case 8: return launch_tile<64, 64, 2>(a, b, s);
+    case 10: return launch_wavek<64, 64>(a, b, s);
+    case 14: return launch_tile<256, 128, 3, 4, 2>(a, b, s);
+    case 15: return launch_tile<256, 256, 2, 4, 2>(a, b, s);
+    case 16: return launch_tile<128, 256, 3, 2, 4>(a, b, s);
+    case 17: return launch_tile<256, 128, 2, 4, 2>(a, b, s);
+    case 22: return launch_tile<256, 128, 3, 4, 2, 32>(a, b, s);
+    case 26: return launch_tile<64, 64, 3>(a, b, s);
+    case 27: return launch_tile<128, 64, 3>(a, b, s);
+    case 28: return launch_tile<128, 192, 2>(a, b, s);
+    case 29: return launch_tile<256, 192, 2, 4, 2>(a, b, s);
+    case 30: return launch_tile<128, 192, 3>(a, b, s);
+    case 40: return launch_tile<128, 192, 2, 2, 2, 64, true>(a, b, s);
+    case 41: return launch_tile<256, 192, 2, 4, 2, 64, true>(a, b, s);
+    case 42: return launch_tile<128, 192, 3, 2, 2, 64, true>(a, b, s);
+    case 43: return launch_tile<256, 256, 2, 4, 2, 64, true>(a, b, s);
+    case 44: return launch_tile<256, 128, 3, 4, 2, 64, true>(a, b, s);
+    case 45: return launch_tile<128, 128, 2, 2, 2, 64, true>(a, b, s);
+    case 46: return launch_tile<128, 192, 4, 2, 2, 64, true>(a, b, s);
+    case 47: return launch_tile<128, 128, 3, 2, 2, 64, true>(a, b, s);
+    case 48: return launch_tile<128, 128, 4, 2, 2, 64, true>(a, b, s);
+    case 49: return launch_tile<128, 64, 4, 2, 2, 64, true>(a, b, s);
+    case 50: return launch_tile<64, 64, 4, 2, 2, 64, true>(a, b, s);
+    case 51: return launch_tile<128, 256, 3, 2, 2, 64, true>(a, b, s);
+    case 70: return launch_tile<128, 64, 6, 4, 1>(a, b, s);
+    case 71: return launch_tile<128, 96, 5, 4, 1>(a, b, s);
+    case 72: return launch_tile<128, 128, 4, 2, 2>(a, b, s);
+    case 73: return launch_tile<128, 128, 4, 4, 2>(a, b, s);
+    case 74: return launch_tile<64, 64, 8, 2, 2>(a, b, s);
+    case 75: return launch_tile<64, 64, 5, 2, 2>(a, b, s);
+    case 76: return launch_tile<64, 128, 6, 2, 2>(a, b, s);
+    case 77: return launch_tile<128, 64, 6, 2, 2>(a, b, s);
+    case 78: return launch_tile<128, 64, 6, 4, 2>(a, b, s);
+    case 79: return launch_tile<64, 128, 3, 2, 2>(a, b, s);
+    case 80: return launch_tile<64, 64, 9, 2, 2>(a, b, s);
+    case 81: return launch_tile<96, 128, 5, 1, 4>(a, b, s);
+    case 52: return launch_tile<128, 192, 3, 2, 2, 64, false>(a, b, s);
     default: break;
   }
 #endif
-  if (a.tile >= 1 && a.tile <= V_COUNT) return launch_variant(a.tile - 1, a, s);
-  return launch_variant(pick_variant(a), a, s);
+  if (a.tile >= 1 && a.tile <= V_COUNT) return launch_variant(a.tile - 1, a, b, s);
+  return launch_variant(pick_variant(a, b), a, b, s);
 }
 
 const char *gemm_mfma_dl_variant_name(const GemmArgs &a) {
-  static const char *names[V_COUNT] = {"gemm_tile_kernel<256,256,2,4,2,64,false>", "gemm_tile_kernel<256,128,3,4,2,32,false>",
-                                       "gemm_tile_kernel<256,128,3,4,2,64,false>", "gemm_tile_kernel<128,128,2,2,2,64,false>",
-                                       "gemm_tile_kernel<128,64,2,2,2,64,false>", "gemm_wavek_kernel<64,64>",
-                                       "gemm_tile_kernel<64,64,4,2,2,64,false>", "gemm_tile_kernel<64,64,3,2,2,64,false>",
-                                       "gemm_tile_kernel<64,64,2,2,2,64,false>", "gemm_tile_kernel<128,192,2,2,2,64,false>",
-                                       "gemm_tile_kernel<256,192,2,4,2,64,false>", "gemm_tile_kernel<128,192,3,2,2,64,true>"};
+  static const char *names[V_COUNT] = {"gemm_tile_kernel<1,256,256,2,4,2,64,false>", "gemm_tile_kernel<1,256,128,3,4,2,32,false>",
+                                       "gemm_tile_kernel<1,256,128,3,4,2,64,false>", "gemm_tile_kernel<1,128,128,2,2,2,64,false>",
+                                       "gemm_tile_kernel<1,128,64,2,2,2,64,false>", "gemm_wavek_kernel<1,64,64>",
+                                       "gemm_tile_kernel<1,64,64,4,2,2,64,false>", "gemm_tile_kernel<1,64,64,3,2,2,64,false>",
+                                       "gemm_tile_kernel<1,64,64,2,2,2,64,false>", "gemm_tile_kernel<1,128,192,2,2,2,64,false>",
+                                       "gemm_tile_kernel<1,256,192,2,4,2,64,false>", "gemm_tile_kernel<1,128,192,3,2,2,64,true>",
+                                       "gemm_tile_kernel<1,64,128,3,2,2,64,false>"};
   return names[(a.tile >= 1 && a.tile <= V_COUNT) ? a.tile - 1 : pick_variant(a)];
 }
 

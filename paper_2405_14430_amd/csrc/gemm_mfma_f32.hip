@@ -29,10 +29,15 @@ __device__ __forceinline__ void mma8(const f32x4 (&a)[N], const f32x4 &w, f32x16
     for (int i = 0; i < N; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], w[e], acc[i], 0, 0, 0);
 }
 
-template <int BM, int BN, int NSTAGE, int WGM, int WGN>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_tile_kernel(const float *__restrict__ A, int64_t lda,
-                                                                       const float *__restrict__ W, int64_t ldw, int M, int N,
-                                                                       int K, Epilogue<float> epi, int vec_ok, int xcd_gx) {
+template <int NP, int BM, int BN, int NSTAGE, int WGM, int WGN>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_tile_kernel(GemmLaunch<float, NP> L) {
+  const bool second = NP == 2 && blockIdx.x >= L.grid0;
+  const GemmProblem<float> &prob = L.p[second ? 1 : 0];
+  const float *__restrict__ A = prob.A, *__restrict__ W = prob.W;
+  const int64_t lda = prob.lda, ldw = prob.ldw;
+  const int M = prob.M, N = L.N, K = L.K;
+  const Epilogue<float> &epi = prob.epi;
+  const int vec_ok = prob.vec_ok;
   constexpr int NW = WGM * WGN, WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NI = WN / 32;
   constexpr int LA = BM / 8 / NW, LW = BN / 8 / NW, LPS = LA + LW;   // load instructions (8 rows each) per wave and K tile
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "tile rows must split evenly over the waves' load instructions");
@@ -41,7 +46,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_tile_kernel(const flo
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   int tm, tn;
-  if (!tile_of_block((M + BM - 1) / BM, (N + BN - 1) / BN, xcd_gx, tm, tn)) return;
+  if (!tile_of_id((int)(blockIdx.x - (second ? L.grid0 : 0)), (M + BM - 1) / BM, (N + BN - 1) / BN, prob.xcd_gx, tm, tn)) return;
   const int m0 = tm * BM, n0 = tn * BN;
 
   const TileSource srcA(A + (size_t)m0 * lda), srcW(W + (size_t)n0 * ldw);
@@ -122,17 +127,22 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_tile_kernel(const flo
   tile_epilogue<BM, BN, TLD, 64 * NW>(tile, m0, n0, M, N, epi, vec_ok != 0);
 }
 
-template <int BM, int BN, int NW>
-__global__ __launch_bounds__(64 * NW) void gemm_f32_wavek_kernel(const float *__restrict__ A, int64_t lda,
-                                                                 const float *__restrict__ W, int64_t ldw, int M, int N, int K,
-                                                                 Epilogue<float> epi, int vec_ok, int xcd_gx) {
+template <int NP, int BM, int BN, int NW>
+__global__ __launch_bounds__(64 * NW) void gemm_f32_wavek_kernel(GemmLaunch<float, NP> L) {
+  const bool second = NP == 2 && blockIdx.x >= L.grid0;
+  const GemmProblem<float> &prob = L.p[second ? 1 : 0];
+  const float *__restrict__ A = prob.A, *__restrict__ W = prob.W;
+  const int64_t lda = prob.lda, ldw = prob.ldw;
+  const int M = prob.M, N = L.N, K = L.K;
+  const Epilogue<float> &epi = prob.epi;
+  const int vec_ok = prob.vec_ok;
   constexpr int MI = BM / 32, NI = BN / 32, LA = BM / 8, LW = BN / 8, LPS = LA + LW;   // a wave loads whole tiles
   constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES, WAVE_BYTES = 2 * STAGE_BYTES, TLD = BN + 4, NT = 64 * NW;
   static_assert(WAVE_BYTES >= BM * TLD * 4, "a wave's partial tile must fit in its own ring");
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int tm, tn;
-  if (!tile_of_block((M + BM - 1) / BM, (N + BN - 1) / BN, xcd_gx, tm, tn)) return;
+  if (!tile_of_id((int)(blockIdx.x - (second ? L.grid0 : 0)), (M + BM - 1) / BM, (N + BN - 1) / BN, prob.xcd_gx, tm, tn)) return;
   const int m0 = tm * BM, n0 = tn * BN;
   unsigned char *ring = smem + wave * WAVE_BYTES;
   const int nk = K / KB, my_nk = (nk - wave + NW - 1) / NW;   // K tiles wave, wave + NW, ...
@@ -223,25 +233,33 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_wavek_kernel(const float *__
 }
 
 template <int BM, int BN, int NSTAGE, int WGM, int WGN>
-hipError_t launch_tile(const GemmArgs &a, hipStream_t s) {
+hipError_t launch_tile(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   constexpr int ring = NSTAGE * (BM + BN) * ROW_BYTES, tile = BM * (BN + 4) * 4, smem = tile > ring ? tile : ring;
-  if (hipError_t e = allow_dynamic_lds<&gemm_f32_tile_kernel<BM, BN, NSTAGE, WGM, WGN>, smem>(); e != hipSuccess) return e;
-  unsigned grid = 0;
-  const int gx = xcd_cut(a, BM, BN, &grid);
-  gemm_f32_tile_kernel<BM, BN, NSTAGE, WGM, WGN><<<dim3(grid), 64 * WGM * WGN, smem, s>>>(
-      (const float *)a.A, a.lda, (const float *)a.W, a.ldw, a.M, a.N, a.K, make_epilogue<float>(a), vec_epilogue_ok(a) ? 1 : 0, gx);
-  return hipGetLastError();
+  auto go = [&](auto np) -> hipError_t {
+    constexpr int NP = decltype(np)::value;
+    constexpr auto kernel = &gemm_f32_tile_kernel<NP, BM, BN, NSTAGE, WGM, WGN>;
+    if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
+    GemmLaunch<float, NP> L;
+    const unsigned grid = make_launch(a, b, BM, BN, &L);
+    kernel<<<grid, 64 * WGM * WGN, smem, s>>>(L);
+    return hipGetLastError();
+  };
+  return b ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
 }
 
 template <int BM, int BN, int NW>
-hipError_t launch_wavek(const GemmArgs &a, hipStream_t s) {
+hipError_t launch_wavek(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   constexpr int smem = NW * 2 * (BM + BN) * ROW_BYTES;
-  if (hipError_t e = allow_dynamic_lds<&gemm_f32_wavek_kernel<BM, BN, NW>, smem>(); e != hipSuccess) return e;
-  unsigned grid = 0;
-  const int gx = xcd_cut(a, BM, BN, &grid);
-  gemm_f32_wavek_kernel<BM, BN, NW><<<dim3(grid), 64 * NW, smem, s>>>(
-      (const float *)a.A, a.lda, (const float *)a.W, a.ldw, a.M, a.N, a.K, make_epilogue<float>(a), vec_epilogue_ok(a) ? 1 : 0, gx);
-  return hipGetLastError();
+  auto go = [&](auto np) -> hipError_t {
+    constexpr int NP = decltype(np)::value;
+    constexpr auto kernel = &gemm_f32_wavek_kernel<NP, BM, BN, NW>;
+    if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
+    GemmLaunch<float, NP> L;
+    const unsigned grid = make_launch(a, b, BM, BN, &L);
+    kernel<<<grid, 64 * NW, smem, s>>>(L);
+    return hipGetLastError();
+  };
+  return b ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
 }
 
 enum { F_64x64 = 0, F_WAVEK4, F_WAVEK8, F_COUNT };
@@ -255,8 +273,8 @@ enum { F_64x64 = 0, F_WAVEK4, F_WAVEK8, F_COUNT };
 //    256x3072x15360 313 | 252 | 207, 375x1536x6144 129 | 88.5 | 86.
 // The plain kernel (gemm_simt.hip) took 85 us for 512x3456x1152 and 129 us on average for the four 512-row GEMMs into 1152
 // columns of a PixArt-scale block.
-int pick_variant(const GemmArgs &a) {
-  auto tiles = [&](int bm, int bn) { return (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
+  auto tiles = [&](int bm, int bn) { return launch_tiles(a, b, bm, bn); };
   if (tiles(64, 64) >= 384) return F_64x64;
   return tiles(32, 32) > 256 && a.K < 6144 ? F_WAVEK4 : F_WAVEK8;
 }
@@ -272,16 +290,16 @@ bool gemm_mfma_f32_supported(const GemmArgs &a) {
 }
 
 const char *gemm_mfma_f32_variant_name(const GemmArgs &a) {
-  static const char *names[F_COUNT] = {"gemm_f32_tile_kernel<64,64,3,2,2>", "gemm_f32_wavek_kernel<32,32,4>",
-                                       "gemm_f32_wavek_kernel<32,32,8>"};
+  static const char *names[F_COUNT] = {"gemm_f32_tile_kernel<1,64,64,3,2,2>", "gemm_f32_wavek_kernel<1,32,32,4>",
+                                       "gemm_f32_wavek_kernel<1,32,32,8>"};
   return names[pick_variant(a)];
 }
 
-hipError_t launch_gemm_mfma_f32(const GemmArgs &a, hipStream_t s) {
-  switch (pick_variant(a)) {
-    case F_64x64: return launch_tile<64, 64, 3, 2, 2>(a, s);
-    case F_WAVEK4: return launch_wavek<32, 32, 4>(a, s);
-    default: return launch_wavek<32, 32, 8>(a, s);
+hipError_t launch_gemm_mfma_f32(const GemmArgs &a, hipStream_t s, const GemmArgs *b) {
+  switch (pick_variant(a, b)) {
+    case F_64x64: return launch_tile<64, 64, 3, 2, 2>(a, b, s);
+    case F_WAVEK4: return launch_wavek<32, 32, 4>(a, b, s);
+    default: return launch_wavek<32, 32, 8>(a, b, s);
   }
 }
 

@@ -62,6 +62,28 @@ __device__ __forceinline__ void unrolled(F &&f) {
   }
 }
 
+// What a launch computes: one GEMM, or two that share N and K (the text and the image stream of a two-stream block: own
+// operands and own rows).  Workgroups [0, grid0) belong to the first, the rest to the second; grid0 is a multiple of 8, so
+// the second one's ids fall on the XCDs like the first one's.  154 text rows alone are 72 - 288 workgroups of 64x64 tiles:
+// as launches of their own they took 8 - 19 us each, four a layer, of an SD3-scale call (637 -> 530 us with shared launches).
+// The kernels are compiled for either count: one problem read through the two-problem form costs a 10 us launch 0.3 us
+// (twice the kernel arguments, addressed at run time).
+template <typename T>
+struct GemmProblem {
+  const T *A; int64_t lda;
+  const T *W; int64_t ldw;
+  int M;
+  int vec_ok, xcd_gx;
+  Epilogue<T> epi;
+};
+template <typename T, int NP>
+struct GemmLaunch {
+  GemmProblem<T> p[NP];
+  int N, K;
+  int kshift;     // != 0: the tiles of column tn start their K loop at K tile tn and wrap around
+  unsigned grid0;
+};
+
 // Workgroup id -> output tile.  Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2, so XCD x runs
 // the ids x, x + 8, ...  Every XCD gets one rectangular block of the tile grid - the grid is cut gx times along M and
 // 8 / gx times along N - because what an XCD fetches from memory is the A rows of its block plus the W rows of its
@@ -78,9 +100,6 @@ __host__ __device__ __forceinline__ bool tile_of_id(int id, int tiles_m, int til
   tm = (x % gx) * bm + lm;
   tn = (x / gx) * bn + ln;
   return tm < tiles_m && tn < tiles_n;
-}
-__device__ __forceinline__ bool tile_of_block(int tiles_m, int tiles_n, int gx, int &tm, int &tn) {
-  return tile_of_id(blockIdx.x, tiles_m, tiles_n, gx, tm, tn);
 }
 
 // Residual and gate operands of a mode-1 epilogue, fetched by the thread that will use them before the K loop starts, so
@@ -150,6 +169,17 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
       const int hh = cc / kv.dh, ch = cc - hh * kv.dh;
       const int img = kv.seg > 0 ? row / kv.seg : 0;
       const int lrow = row - img * kv.seg;           // row inside its image
+      if (kv.q_norm && part < 2) {
+        // a head's dh / 8 groups of the row are consecutive, aligned lanes (the tile is a whole number of heads wide)
+        float ss = 0.f, wn[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss = fmaf(v[e], v[e], ss);
+        for (int m = 1; m < kv.dh >> 3; m <<= 1) ss += __shfl_xor(ss, m, kWave);
+        const float rinv = rsqrtf(ss / (float)kv.dh + kv.norm_eps);
+        load8(reinterpret_cast<const T *>(part == 0 ? kv.q_norm : kv.k_norm) + ch, wn);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = v[e] * rinv * wn[e];
+      }
       if (kv.rope && part < 2) {
         const float2 *tab = kv.rope + (size_t)lrow * (kv.dh >> 1) + (ch >> 1);
 #pragma unroll
@@ -271,6 +301,27 @@ inline bool vec_epilogue_ok(const GemmArgs &a) {
   ok = ok && al(a.C, 16) && a.ldc % 4 == 0 && al(a.R, 16) && a.ldr % 4 == 0 && (!a.gate || (al(a.gate, 16) && a.gate_stride % 4 == 0));
   if (a.C2) ok = ok && al(a.C2, 16) && a.ldc2 % 8 == 0;
   return ok;
+}
+
+// Fills the launch of `a` and, for NP = 2, `b` (same N and K) with BM x BN tiles; returns the workgroup count.
+template <typename T, int NP>
+inline unsigned make_launch(const GemmArgs &a, const GemmArgs *b, int BM, int BN, GemmLaunch<T, NP> *L, int kshift = 0) {
+  unsigned total = 0;
+  for (int i = 0; i < NP; ++i) {
+    const GemmArgs &g = i ? *b : a;
+    unsigned grid = 0;
+    const int gx = xcd_cut(g, BM, BN, &grid);
+    L->p[i] = GemmProblem<T>{(const T *)g.A, g.lda, (const T *)g.W, g.ldw, g.M, vec_epilogue_ok(g) ? 1 : 0, gx, make_epilogue<T>(g)};
+    if (i == 0) L->grid0 = grid;
+    total += grid;
+  }
+  L->N = a.N; L->K = a.K; L->kshift = kshift;
+  return total;
+}
+
+// tiles of a launch of one or two GEMMs
+inline int64_t launch_tiles(const GemmArgs &a, const GemmArgs *b, int bm, int bn) {
+  return (int64_t)((a.M + bm - 1) / bm + (b ? (b->M + bm - 1) / bm : 0)) * ((a.N + bn - 1) / bn);
 }
 
 }  // namespace

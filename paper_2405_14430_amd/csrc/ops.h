@@ -28,8 +28,8 @@ PF_PLAN_CONST(g_force_splits, 0);       // > 0 replaces the split heuristic's co
 PF_PLAN_CONST(g_fuse_kv_route, 1);      // K/V written by the QKV GEMM epilogue (1) or by the scatter kernel (0)
 PF_PLAN_CONST(g_fold_q_scale, 1);       // q reaches the attention kernel with its exponent factor folded in
 PF_PLAN_CONST(g_gemm_tile_override, 0); // 0 = tile heuristic, else a fixed tile configuration for every launch
-PF_PLAN_CONST(g_wavek_min_k, 2048);     // smallest K the wave-split-K GEMM kernel takes
-PF_PLAN_CONST(g_wavek_max_tiles, 512);  // it takes GEMMs with fewer 64 x 64 tiles than this
+PF_PLAN_CONST(g_wavek_min_k, 1024);     // smallest K the wave-split-K GEMM kernel takes
+PF_PLAN_CONST(g_wavek_max_tiles, 256);  // it takes GEMMs with up to this many 64 x 64 tiles
 
 hipError_t launch_modulation(int dt, const void *w, const void *b, const float *c, float *mod, int out_dim,
                              int in_dim, int table_mode, hipStream_t s);
@@ -45,17 +45,24 @@ struct ModBatch {
 };
 hipError_t launch_modulation_batch(int dt, const ModBatch &mb, int out_dim, int in_dim, int table_mode, hipStream_t s);
 
-// seg_rows > 0: rows are image-major with seg_rows rows per image and image b reads its shift / scale vectors
-// seg_stride floats after image 0's.
-hipError_t launch_ln_modulate(int dt, const float *x, int64_t ldx, const float *shift, const float *scale,
-                              float eps, void *out, int64_t ldo, int rows, int d, int normalize,
-                              hipStream_t s, int seg_rows = 0, int64_t seg_stride = 0);
+// LayerNorm + modulate over rows of d floats.  seg_rows > 0: rows are image-major with seg_rows rows per image and image b
+// reads its shift / scale vectors seg_stride floats after image 0's.
+struct LnRows {
+  const float *x;
+  const float *shift, *scale;
+  void *out;
+  int rows;
+  int seg_rows;
+};
+// b != nullptr: a second set of rows (the other stream of a two-stream block) in the same launch
+hipError_t launch_ln_modulate(int dt, const LnRows &a, const LnRows *b, int64_t ldx, float eps, int64_t ldo, int d, int normalize,
+                              int64_t seg_stride, hipStream_t s);
 
 struct KvRoute;   // epilogue.h
 // seg > 0: GEMM rows are image-major, seg per image; image b writes into kbuf / vtbuf + b * img_stride elements and
 // the row mapping (split, row0a, row0b, rope row) applies to the row index inside the image.
 struct GemmArgsKv { void *kbuf, *vtbuf; int Lp, dh, d, split, row0a, row0b; const void *rope; int seg; int64_t img_stride;
-                    float q_scale; };   // q_scale != 0: the q columns are multiplied by it before they are rounded
+                    float q_scale; const void *q_norm, *k_norm; float norm_eps; };   // q_norm: per-head RMSNorm scales; q_scale != 0: the q columns are multiplied by it before they are rounded
 
 struct GemmArgs {
   int dt, path;
@@ -74,6 +81,8 @@ struct GemmArgs {
   int tile;            // 0: the tile heuristic picks; 1 .. gemm_mfma_dl_tile_count(): that tile configuration, this launch only
 };
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
+// two GEMMs of one type and path that do not depend on each other; one launch where N, K and the kernel family agree
+hipError_t launch_gemm_pair(const GemmArgs &a, const GemmArgs &b, hipStream_t s);
 bool gemm_kv_route_supported(const GemmArgs &a);   // the fused QKV -> K/V^T write needs an MFMA kernel's vectorised epilogue
 
 // (cos, sin) of the RoPE angles for the rows of a call: rows [0, n_text) are text (no rotation), row n_text + i is image
@@ -116,7 +125,7 @@ hipError_t launch_gemm_simt(const GemmArgs &a, hipStream_t s);
 hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s);
 bool gemm_tile_map(int M, int N, int BM, int BN, unsigned id, unsigned *grid, int *tm, int *tn);   // host view of the tile map
 bool gemm_mfma_dl_supported(const GemmArgs &a);            // direct-to-LDS multi-stage variant (K % 64 == 0)
-hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s);
+hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s, const GemmArgs *b = nullptr);   // b: a second GEMM of the same N and K
 const char *gemm_mfma_dl_variant_name(const GemmArgs &a);   // kernel instance the tile heuristic picks for this shape
 int gemm_mfma_dl_tile_count();                              // tile configurations the heuristic chooses from
 hipError_t launch_attn_simt(const AttnArgs &a, hipStream_t s);
@@ -127,7 +136,7 @@ hipError_t launch_attn_mfma2(const AttnArgs &a, hipStream_t s);
 int attn_mfma2_qtile(int nq);                              // queries per workgroup it will use for nq query rows per image
 bool attn_mfma2_takes_prescaled_q(int head_dim);           // its kernel for this head size has a prescaled-q variant
 bool gemm_mfma_f32_supported(const GemmArgs &a);           // fp32 MFMA GEMM (K % 32 == 0, aligned operand rows)
-hipError_t launch_gemm_mfma_f32(const GemmArgs &a, hipStream_t s);
+hipError_t launch_gemm_mfma_f32(const GemmArgs &a, hipStream_t s, const GemmArgs *b = nullptr);
 const char *gemm_mfma_f32_variant_name(const GemmArgs &a);
 bool attn_mfma_f32_head_size(int head_dim);                // fp32 MFMA attention: head sizes 64 / 72 / 128
 bool attn_mfma_f32_supported(const AttnArgs &a);

@@ -248,7 +248,7 @@ hipError_t run(pf_stage *s, int cls, Fn &&fn) {
       return fail(s, PF_ERR_DEVICE, std::string(#expr) + ": " + hipGetErrorString(e__));   \
   } while (0)
 
-hipError_t gemm(pf_stage *s, int cls, const void *A, int64_t lda, const void *W, int64_t ldw, const void *bias,
+GemmArgs gemm_args(const pf_stage *s, const void *A, int64_t lda, const void *W, int64_t ldw, const void *bias,
                 void *C, int64_t ldc, int M, int N, int K, int epilogue, int gelu_from, const float *gate,
                 const float *R, int64_t ldr, void *C2, int64_t ldc2, const GemmArgsKv *kvr = nullptr, int gate_seg = 0) {
   GemmArgs g{};
@@ -258,7 +258,15 @@ hipError_t gemm(pf_stage *s, int cls, const void *A, int64_t lda, const void *W,
   g.A = A; g.lda = lda; g.W = W; g.ldw = ldw; g.bias = bias; g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K;
   g.epilogue = epilogue; g.gelu_from = gelu_from; g.gelu_tanh = s->cfg.gelu_tanh; g.gate = gate; g.R = R; g.ldr = ldr;
   g.C2 = C2; g.ldc2 = ldc2;
+  return g;
+}
+
+hipError_t gemm(pf_stage *s, int cls, const GemmArgs &g) {
   return run(s, cls, [&] { return launch_gemm(g, s->stream); });
+}
+// the same GEMM of one stream, or of both in one launch
+hipError_t gemm(pf_stage *s, int cls, const GemmArgs *g, int n) {
+  return n == 1 ? gemm(s, cls, g[0]) : run(s, cls, [&] { return launch_gemm_pair(g[0], g[1], s->stream); });
 }
 
 // (nq = query rows per image; every launch covers all images of the call)
@@ -304,42 +312,57 @@ int qkv_route(const pf_stage *s, const void *hs, const pf_layer_weights &lw, con
   probe.bias = lw.b_qkv; probe.C = (void *)qs; probe.ldc = 3 * D; probe.M = 1; probe.N = 3 * D; probe.K = D; probe.epilogue = 0;
   probe.gelu_from = 3 * D;
   probe.kvr = GemmArgsKv{(void *)qs, (void *)qs, s->d.Lp, c.head_dim, D, 0, 0, 0, nullptr, 0, 0, 0.f};
-  if (g_fuse_kv_route && !c.qk_norm && gemm_kv_route_supported(probe)) return ROUTE_FUSED;   // the fused route has no q / k RMSNorm
+  if (c.qk_norm) { probe.kvr.q_norm = lw.q_norm_w; probe.kvr.k_norm = lw.k_norm_w; }
+  if (g_fuse_kv_route && gemm_kv_route_supported(probe)) return ROUTE_FUSED;
   return (rope || c.qk_norm) ? ROUTE_SCATTER_REWRITE : ROUTE_SCATTER_PLAIN;
 }
 
+// One stream's part of a QKV projection: seg rows per image at hs, the projection at qs, the row mapping, and the RoPE of the
+// rows (tok0 is the image token of row `split`).
+struct QkvPart {
+  const void *hs;
+  const pf_layer_weights *lw;
+  char *qs;
+  int seg, split, row0a, row0b, tok0;
+  bool rope;
+};
+
+// QKV projection of one or two streams, in one launch where they share a route.
 // q_scale != 0: q is to leave this function multiplied by it (folded into whichever fp32 step writes q; the caller only
 // asks for it when every q row of the coming attention launch goes through such a step).
-pf_status qkv_project(pf_stage *s, const void *hs, const pf_layer_weights &lw, char *qs, int seg, char *kb, char *vb,
-                      int split, int row0a, int row0b, const void *rope_tab, int tok0, bool rope, float q_scale) {
+pf_status qkv_project(pf_stage *s, const QkvPart *parts, int np, char *kb, char *vb, const void *rope_tab, float q_scale) {
   const pf_config &c = s->cfg;
   const Derived &d = s->d;
   const int D = c.hidden;
-  const int rows = seg * d.B;
-  GemmArgsKv kvr{kb, vb, d.Lp, c.head_dim, D, split, row0a, row0b, rope ? rope_tab : nullptr, d.B > 1 ? seg : 0,
-                 (int64_t)s->img_elems(), q_scale};
-  if (qkv_route(s, hs, lw, qs, rope) == ROUTE_FUSED) {
-    PF_TRY(gemm(s, PF_KC_GEMM_QKV, hs, D, lw.w_qkv, D, lw.b_qkv, qs, 3 * D, rows, 3 * D, D, 0, 3 * D, nullptr, nullptr, 0,
-                nullptr, 0, &kvr));
-    return PF_OK;
+  GemmArgs g[2];
+  bool fused[2];
+  for (int i = 0; i < np; ++i) {
+    const QkvPart &p = parts[i];
+    GemmArgsKv kvr{kb, vb, d.Lp, c.head_dim, D, p.split, p.row0a, p.row0b, p.rope ? rope_tab : nullptr, d.B > 1 ? p.seg : 0,
+                   (int64_t)s->img_elems(), q_scale};
+    if (c.qk_norm) { kvr.q_norm = p.lw->q_norm_w; kvr.k_norm = p.lw->k_norm_w; kvr.norm_eps = c.ln_eps; }
+    fused[i] = qkv_route(s, p.hs, *p.lw, p.qs, p.rope) == ROUTE_FUSED;
+    g[i] = gemm_args(s, p.hs, D, p.lw->w_qkv, D, p.lw->b_qkv, p.qs, 3 * D, p.seg * d.B, 3 * D, D, 0, 3 * D, nullptr, nullptr, 0,
+                     nullptr, 0, fused[i] ? &kvr : nullptr);
   }
-  PF_TRY(gemm(s, PF_KC_GEMM_QKV, hs, D, lw.w_qkv, D, lw.b_qkv, qs, 3 * D, rows, 3 * D, D, 0, 3 * D, nullptr, nullptr, 0,
-              nullptr, 0));
+  PF_TRY(gemm(s, PF_KC_GEMM_QKV, g, np));
   hipStream_t st = s->stream;
-  for (int b = 0; b < d.B; ++b) {
-    char *qb = qs + (size_t)b * seg * 3 * D * d.esz;
-    char *kbb = kb + (size_t)b * s->img_elems() * d.esz, *vbb = vb + (size_t)b * s->img_elems() * d.esz;
-    if (split > 0) {
-      ScatterArgs sa{c.dtype, qb, 3 * D, kbb, vbb, d.Lp, c.n_heads, c.head_dim, row0a, split, rope ? 1 : 0, -1, c.grid_w, c.rope_theta};
-      if (c.qk_norm) { sa.q_norm_w = lw.q_norm_w; sa.k_norm_w = lw.k_norm_w; sa.norm_eps = c.ln_eps; }
-      sa.q_scale = q_scale;
-      PF_TRY(run(s, PF_KC_KV_SCATTER, [&] { return launch_kv_scatter(sa, st); }));
+  for (int i = 0; i < np; ++i) {
+    if (fused[i]) continue;
+    const QkvPart &p = parts[i];
+    for (int b = 0; b < d.B; ++b) {
+      char *qb = p.qs + (size_t)b * p.seg * 3 * D * d.esz;
+      char *kbb = kb + (size_t)b * s->img_elems() * d.esz, *vbb = vb + (size_t)b * s->img_elems() * d.esz;
+      auto scatter = [&](int first, int rows, int row0, int tok0) -> hipError_t {
+        ScatterArgs sa{c.dtype, qb + (size_t)first * 3 * D * d.esz, 3 * D, kbb, vbb, d.Lp, c.n_heads, c.head_dim, row0, rows,
+                       p.rope ? 1 : 0, tok0, c.grid_w, c.rope_theta};
+        if (c.qk_norm) { sa.q_norm_w = p.lw->q_norm_w; sa.k_norm_w = p.lw->k_norm_w; sa.norm_eps = c.ln_eps; }
+        sa.q_scale = q_scale;
+        return run(s, PF_KC_KV_SCATTER, [&] { return launch_kv_scatter(sa, st); });
+      };
+      if (p.split > 0) PF_TRY(scatter(0, p.split, p.row0a, -1));
+      PF_TRY(scatter(p.split, p.seg - p.split, p.row0b, p.tok0));
     }
-    ScatterArgs sb{c.dtype, qb + (size_t)split * 3 * D * d.esz, 3 * D, kbb, vbb, d.Lp, c.n_heads, c.head_dim, row0b, seg - split,
-                   rope ? 1 : 0, tok0, c.grid_w, c.rope_theta};
-    if (c.qk_norm) { sb.q_norm_w = lw.q_norm_w; sb.k_norm_w = lw.k_norm_w; sb.norm_eps = c.ln_eps; }
-    sb.q_scale = q_scale;
-    PF_TRY(run(s, PF_KC_KV_SCATTER, [&] { return launch_kv_scatter(sb, st); }));
   }
   return PF_OK;
 }
@@ -374,20 +397,26 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
   float *xres = (float *)(ws + w.xres);
   char *h = ws + w.h, *qkv = ws + w.qkv, *a = ws + w.a, *u = ws + w.u;
 
-  // Residual rows.  With text rows riding along they are gathered in the workspace.  Without, nothing is copied: the
-  // first layer reads x_img directly, the first residual GEMM writes into the output buffer (or the workspace when
-  // the caller wants no output) and everything after that runs in place there.
-  float *xbuf = xres;          // where updated residual rows live
-  const float *xsrc = xres;    // where the current residual rows are read from (x_img until the first update)
-  // text block / image block of the residual rows: first row and distance between images, in rows
+  // Residual rows.  The single-stream kind runs text and image rows through one weight set, so with text they are gathered
+  // in the workspace.  Otherwise nothing is copied: the first layer reads the caller's rows, the first residual GEMM of a
+  // stream writes into its output (or the workspace when the caller wants none) and everything after that runs in place.
+  // (With text, rows of a caller that are not 16-byte aligned are gathered too: the copy takes any address.)
+  float *xbuf = xres;          // where updated image rows live
+  const float *xsrc = xres;    // where the current image rows are read from (x_img until the first update)
+  float *tbuf = xres;          // the same of the MMDiT kind's text rows
+  const float *tsrc = text;
+  // first row of the text / image rows in the workspace buffers and the distance between images, in rows
   const size_t t_row0 = 0, i_row0 = single ? (size_t)Tt : (size_t)B * Tt;
   const size_t t_pitch = single ? (size_t)R : (size_t)Tt, i_pitch = single ? (size_t)R : (size_t)n_img;
-  if (Tt) {
+  const bool gather = Tt && (single || (((uintptr_t)text | (uintptr_t)text_out | (uintptr_t)x_img | (uintptr_t)y_img) & 15));
+  if (gather) {
+    if (!single) tsrc = xres, xsrc = xbuf = xres + i_row0 * D;
     PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(xres + t_row0 * D, t_pitch * D, text, (size_t)Tt * D, (size_t)Tt * D, B, st); }));
     PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(xres + i_row0 * D, i_pitch * D, x_img, (size_t)n_img * D, (size_t)n_img * D, B, st); }));
   } else {
     xsrc = x_img;
-    if (y_img) xbuf = y_img;
+    xbuf = y_img ? y_img : xres + i_row0 * D;
+    if (Tt && text_out) tbuf = text_out;
   }
 
   // a0: modulation vectors of every layer, stream and image, one launch per 16 of them
@@ -451,48 +480,53 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
       const pf_layer_weights &lw = s->img[l];
       const float *m = s->mod(0, l);
       const int RT = B * R;
-      PF_TRY(run(s, PF_KC_LN_MODULATE, [&] { return launch_ln_modulate(dt, xsrc, D, m, m + D, c.ln_eps, h, D, RT, D, 1, st, B > 1 ? R : 0, mstride); }));
+      PF_TRY(run(s, PF_KC_LN_MODULATE, [&] { return launch_ln_modulate(dt, LnRows{xsrc, m, m + D, h, RT, B > 1 ? R : 0}, nullptr, D, c.ln_eps, D, D, 1, mstride, st); }));
       {
         const bool pre = pre_ok && qkv_route(s, h, lw, qkv, true) != ROUTE_SCATTER_PLAIN;
-        pf_status qs_ = qkv_project(s, h, lw, qkv, R, kb, vb, Tt, 0, row0_img, ws + w.rope, img_off, true, pre ? q_fold : 0.f);
+        const QkvPart part{h, &lw, qkv, R, Tt, 0, row0_img, img_off, true};
+        pf_status qs_ = qkv_project(s, &part, 1, kb, vb, ws + w.rope, pre ? q_fold : 0.f);
         if (qs_ != PF_OK) return qs_;
         q_pre = pre;
       }
       // MLP branch runs in parallel with attention: GELU(h W_up^T + b) lands right of the attention columns
-      PF_TRY(gemm(s, PF_KC_GEMM_UP, h, D, lw.w_up, D, lw.b_up, a + (size_t)D * e, D + F, RT, F, D, 0, 0, nullptr, nullptr, 0, nullptr, 0));
+      PF_TRY(gemm(s, PF_KC_GEMM_UP, gemm_args(s, h, D, lw.w_up, D, lw.b_up, a + (size_t)D * e, D + F, RT, F, D, 0, 0, nullptr, nullptr, 0, nullptr, 0)));
       PF_TRY(attention(s, PF_KC_ATTENTION, qkv, 3 * D, kb, vb, d.Lkv, d.Lp, a, D + F, R, q_pre));
-      PF_TRY(gemm(s, PF_KC_GEMM_DOWN, a, D + F, lw.w_down, D + F, lw.b_down, xbuf, D, RT, D, D + F, 1, 0, m + 2 * D, xsrc, D, nullptr, 0, nullptr, R));
+      PF_TRY(gemm(s, PF_KC_GEMM_DOWN, gemm_args(s, a, D + F, lw.w_down, D + F, lw.b_down, xbuf, D, RT, D, D + F, 1, 0, m + 2 * D, xsrc, D, nullptr, 0, nullptr, R)));
       xsrc = xbuf;
       continue;
     }
 
-    // kinds 0, 1, 2: streams = [text (kind 2, if present), image]; r0 = first residual row, seg = rows per image
-    struct Stream { const pf_layer_weights *lw; const float *m; size_t r0; int seg, brow0; };
+    // kinds 0, 1, 2: streams = [text (kind 2, if present), image]; r0 = first row in the workspace buffers, seg = rows per
+    // image, xin / xout = residual rows before and after this layer's first update.  The streams' GEMMs and norms are
+    // independent of each other and share their shapes up to the row count: each pair is one launch.
+    struct Stream { const pf_layer_weights *lw; const float *m; size_t r0; int seg, brow0; const float *xin; float *xout; };
     Stream streams[2];
     int ns = 0;
-    if (c.kind == PF_BLOCK_MMDIT_JOINT && Tt) streams[ns++] = Stream{&s->txt[l], s->mod(0, l), t_row0, Tt, 0};
-    streams[ns++] = Stream{&s->img[l], s->mod(d.n_streams - 1, l), Tt ? i_row0 : 0, n_img, row0_img};
+    if (c.kind == PF_BLOCK_MMDIT_JOINT && Tt) streams[ns++] = Stream{&s->txt[l], s->mod(0, l), t_row0, Tt, 0, tsrc, tbuf};
+    streams[ns++] = Stream{&s->img[l], s->mod(d.n_streams - 1, l), Tt ? i_row0 : 0, n_img, row0_img, xsrc, xbuf};
 
     // final joint block: the text rows (first stream) are projected to keys and values and nothing else
     const bool txt_kv_only = c.txt_pre_only_last && l == c.n_layers - 1 && ns == 2;
+    auto ln = [&](const Stream *sm, int n, bool second) -> hipError_t {
+      LnRows rows[2];
+      for (int i = 0; i < n; ++i) {
+        const float *x = second ? sm[i].xout : sm[i].xin, *m = sm[i].m + (second ? 3 * D : 0);
+        rows[i] = LnRows{x, m, m + D, h + sm[i].r0 * D * e, B * sm[i].seg, B > 1 ? sm[i].seg : 0};
+      }
+      return run(s, PF_KC_LN_MODULATE, [&] { return launch_ln_modulate(dt, rows[0], n == 2 ? &rows[1] : nullptr, D, c.ln_eps, D, D, 1, mstride, st); });
+    };
     // q is handed over with the attention kernel's factor folded in only if every stream's projection rewrites q in fp32
     q_pre = pre_ok;
-    for (int si = 0; si < ns && q_pre; ++si) {
-      const Stream &sm = streams[si];
-      const bool rot = d.rope && sm.lw == &s->img[l];
-      q_pre = qkv_route(s, h + sm.r0 * D * e, *sm.lw, qkv + sm.r0 * 3 * D * e, rot) != ROUTE_SCATTER_PLAIN;
-    }
+    QkvPart parts[2];
     for (int si = 0; si < ns; ++si) {
       const Stream &sm = streams[si];
-      const float *xs = xsrc + sm.r0 * D;
-      char *hs = h + sm.r0 * D * e;
-      char *qs = qkv + sm.r0 * 3 * D * e;
-      PF_TRY(run(s, PF_KC_LN_MODULATE, [&] { return launch_ln_modulate(dt, xs, D, sm.m, sm.m + D, c.ln_eps, hs, D, B * sm.seg, D, 1, st, B > 1 ? sm.seg : 0, mstride); }));
       const bool rot = d.rope && sm.lw == &s->img[l];   // image stream of a rotating two-stream block
-      pf_status qs_ = qkv_project(s, hs, *sm.lw, qs, sm.seg, kb, vb, 0, 0, sm.brow0, rot ? ws + w.rope : nullptr,
-                                  rot ? img_off : -1, rot, q_pre ? q_fold : 0.f);
-      if (qs_ != PF_OK) return qs_;
+      parts[si] = QkvPart{h + sm.r0 * D * e, sm.lw, qkv + sm.r0 * 3 * D * e, sm.seg, 0, 0, sm.brow0, rot ? img_off : -1, rot};
+      q_pre = q_pre && qkv_route(s, parts[si].hs, *sm.lw, parts[si].qs, rot) != ROUTE_SCATTER_PLAIN;
     }
+    PF_TRY(ln(streams, ns, false));
+    pf_status qs_ = qkv_project(s, parts, ns, kb, vb, ws + w.rope, q_pre ? q_fold : 0.f);
+    if (qs_ != PF_OK) return qs_;
     if (B == 1 && !txt_kv_only) {
       // one image: the text and image rows are adjacent, one launch covers both
       PF_TRY(attention(s, PF_KC_ATTENTION, qkv, 3 * D, kb, vb, d.Lkv, d.Lp, a, D, R, q_pre));
@@ -501,34 +535,48 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
         PF_TRY(attention(s, PF_KC_ATTENTION, qkv + streams[si].r0 * 3 * D * e, 3 * D, kb, vb, d.Lkv, d.Lp,
                          a + streams[si].r0 * D * e, D, streams[si].seg, q_pre));
     }
-    for (int si = txt_kv_only ? 1 : 0; si < ns; ++si) {
-      const Stream &sm = streams[si];
-      const int nr = B * sm.seg;
-      float *xs = xbuf + sm.r0 * D;
-      const float *xs_in = xsrc + sm.r0 * D;   // differs from xs only before the first update
-      char *hs = h + sm.r0 * D * e;
-      char *as = a + sm.r0 * D * e;
-      char *us = u + sm.r0 * F * e;
-      const bool xattn = c.kind == PF_BLOCK_ADALN_SINGLE_XATTN;
-      char *xb = xattn ? ws + w.xb : nullptr;
-      PF_TRY(gemm(s, PF_KC_GEMM_OUT, as, D, sm.lw->w_o, D, sm.lw->b_o, xs, D, nr, D, D, 1, 0, sm.m + 2 * D, xs_in, D, xb, D, nullptr, sm.seg));
-      if (xattn) {
-        char *qc = ws + w.qc;
-        PF_TRY(gemm(s, PF_KC_GEMM_XATTN, xb, D, sm.lw->xattn_wq, D, sm.lw->xattn_bq, qc, D, nr, D, D, 0, D, nullptr, nullptr, 0, nullptr, 0));
-        PF_TRY(attention(s, PF_KC_XATTN, qc, D, s->kcptr(l), s->vcptr(l), d.T, d.Tp, as, D, sm.seg));
-        PF_TRY(gemm(s, PF_KC_GEMM_XATTN, as, D, sm.lw->xattn_wo, D, sm.lw->xattn_bo, xs, D, nr, D, D, 1, 0, nullptr, xs, D, nullptr, 0));
-      }
-      PF_TRY(run(s, PF_KC_LN_MODULATE, [&] { return launch_ln_modulate(dt, xs, D, sm.m + 3 * D, sm.m + 4 * D, c.ln_eps, hs, D, nr, D, 1, st, B > 1 ? sm.seg : 0, mstride); }));
-      PF_TRY(gemm(s, PF_KC_GEMM_UP, hs, D, sm.lw->w_up, D, sm.lw->b_up, us, F, nr, F, D, 0, 0, nullptr, nullptr, 0, nullptr, 0));
-      PF_TRY(gemm(s, PF_KC_GEMM_DOWN, us, F, sm.lw->w_down, F, sm.lw->b_down, xs, D, nr, D, F, 1, 0, sm.m + 5 * D, xs, D, nullptr, 0, nullptr, sm.seg));
+    const Stream *live = streams + (txt_kv_only ? 1 : 0);   // streams with an output projection and an MLP
+    const int nl = ns - (txt_kv_only ? 1 : 0);
+    const bool xattn = c.kind == PF_BLOCK_ADALN_SINGLE_XATTN;
+    char *xb = xattn ? ws + w.xb : nullptr;
+    GemmArgs g[2];
+    for (int i = 0; i < nl; ++i) {
+      const Stream &sm = live[i];
+      g[i] = gemm_args(s, a + sm.r0 * D * e, D, sm.lw->w_o, D, sm.lw->b_o, sm.xout, D, B * sm.seg, D, D, 1, 0, sm.m + 2 * D, sm.xin, D, xb, D, nullptr, sm.seg);
     }
-    xsrc = xbuf;   // every stream of this layer has written its rows
+    PF_TRY(gemm(s, PF_KC_GEMM_OUT, g, nl));
+    if (xattn) {   // (one stream, whose rows start the workspace buffers)
+      char *qc = ws + w.qc;
+      const Stream &sm = live[0];
+      const int nr = B * sm.seg;
+      PF_TRY(gemm(s, PF_KC_GEMM_XATTN, gemm_args(s, xb, D, sm.lw->xattn_wq, D, sm.lw->xattn_bq, qc, D, nr, D, D, 0, D, nullptr, nullptr, 0, nullptr, 0)));
+      PF_TRY(attention(s, PF_KC_XATTN, qc, D, s->kcptr(l), s->vcptr(l), d.T, d.Tp, a, D, sm.seg));
+      PF_TRY(gemm(s, PF_KC_GEMM_XATTN, gemm_args(s, a, D, sm.lw->xattn_wo, D, sm.lw->xattn_bo, sm.xout, D, nr, D, D, 1, 0, nullptr, sm.xout, D, nullptr, 0)));
+    }
+    PF_TRY(ln(live, nl, true));
+    for (int i = 0; i < nl; ++i) {
+      const Stream &sm = live[i];
+      g[i] = gemm_args(s, h + sm.r0 * D * e, D, sm.lw->w_up, D, sm.lw->b_up, u + sm.r0 * F * e, F, B * sm.seg, F, D, 0, 0, nullptr, nullptr, 0, nullptr, 0);
+    }
+    PF_TRY(gemm(s, PF_KC_GEMM_UP, g, nl));
+    for (int i = 0; i < nl; ++i) {
+      const Stream &sm = live[i];
+      g[i] = gemm_args(s, u + sm.r0 * F * e, F, sm.lw->w_down, F, sm.lw->b_down, sm.xout, D, B * sm.seg, D, F, 1, 0, sm.m + 5 * D, sm.xout, D, nullptr, 0, nullptr, sm.seg);
+    }
+    PF_TRY(gemm(s, PF_KC_GEMM_DOWN, g, nl));
+    xsrc = xbuf;   // the live streams have written their rows
+    if (nl == 2) tsrc = tbuf;
   }
 
-  if (y_img && xbuf != y_img)
-    PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(y_img, (size_t)n_img * D, xres + i_row0 * D, i_pitch * D, (size_t)n_img * D, B, st); }));
-  if (Tt && text_out)
-    PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(text_out, (size_t)Tt * D, xres + t_row0 * D, t_pitch * D, (size_t)Tt * D, B, st); }));
+  if (gather) {
+    if (y_img)
+      PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(y_img, (size_t)n_img * D, xres + i_row0 * D, i_pitch * D, (size_t)n_img * D, B, st); }));
+    if (text_out)
+      PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(text_out, (size_t)Tt * D, xres + t_row0 * D, t_pitch * D, (size_t)Tt * D, B, st); }));
+  } else if (Tt && text_out && tsrc != text_out) {
+    // a stack of one final joint block passes its text rows through
+    PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(text_out, (size_t)Tt * D, tsrc, (size_t)Tt * D, (size_t)Tt * D, B, st); }));
+  }
   return PF_OK;
 }
 
@@ -609,8 +657,8 @@ pf_status pf_kv_init(pf_stage *s, const float *x_prev, const pf_cond *cp, float 
     for (int l = 0; l < c.n_layers; ++l) {
       const pf_layer_weights &lw = s->img[l];
       // text features of all images, [B][T][cross_dim], in one GEMM; then one scatter per image
-      PF_TRY(gemm(s, PF_KC_GEMM_XATTN, cp->text, c.cross_dim, lw.xattn_wkv, c.cross_dim, lw.xattn_bkv, qkv + (size_t)D * d.esz,
-                  3 * D, d.B * d.T, 2 * D, c.cross_dim, 0, 2 * D, nullptr, nullptr, 0, nullptr, 0));
+      PF_TRY(gemm(s, PF_KC_GEMM_XATTN, gemm_args(s, cp->text, c.cross_dim, lw.xattn_wkv, c.cross_dim, lw.xattn_bkv, qkv + (size_t)D * d.esz,
+                                                 3 * D, d.B * d.T, 2 * D, c.cross_dim, 0, 2 * D, nullptr, nullptr, 0, nullptr, 0)));
       for (int b = 0; b < d.B; ++b) {
         ScatterArgs sa{c.dtype, qkv + (size_t)b * d.T * 3 * D * d.esz, 3 * D, s->kcptr(l) + b * s->ximg_elems() * d.esz,
                        s->vcptr(l) + b * s->ximg_elems() * d.esz, d.Tp, c.n_heads, c.head_dim, 0, d.T, 0, -1, c.grid_w, c.rope_theta};
@@ -748,7 +796,7 @@ pf_status pf_op_ln_modulate(int dtype, const float *x, int64_t ldx, const float 
   if (!x || !out || (normalize && (!shift || !scale))) return PF_ERR_NULL;
   if (!dt_ok(dtype)) return PF_ERR_DTYPE;
   if (rows < 0 || d < 8 || d % 8 || d > 8192 || ldx < d || ldo < d || ldx % 4 || ldo % 4 || !al16(x) || !al16(out)) return PF_ERR_SHAPE;
-  return launch_ln_modulate(dtype, x, ldx, shift, scale, eps, out, ldo, rows, d, normalize, (hipStream_t)stream) == hipSuccess ? PF_OK : PF_ERR_DEVICE;
+  return launch_ln_modulate(dtype, LnRows{x, shift, scale, out, rows, 0}, nullptr, ldx, eps, ldo, d, normalize, 0, (hipStream_t)stream) == hipSuccess ? PF_OK : PF_ERR_DEVICE;
 }
 
 int pf_gemm_tile_map(int M, int N, int tile_m, int tile_n, unsigned workgroup, unsigned *grid, int *tm, int *tn) {
@@ -949,5 +997,13 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s) {
   if (a.path == PATH_SIMT) return launch_gemm_simt(a, s);
   if (a.dt == DT_F32) return gemm_mfma_f32_supported(a) ? launch_gemm_mfma_f32(a, s) : launch_gemm_simt(a, s);
   return gemm_mfma_dl_supported(a) ? launch_gemm_mfma_dl(a, s) : launch_gemm_mfma(a, s);
+}
+hipError_t launch_gemm_pair(const GemmArgs &a, const GemmArgs &b, hipStream_t s) {
+  if (a.path != PATH_SIMT && a.N == b.N && a.K == b.K && a.dt == b.dt) {
+    if (a.dt == DT_F32 && gemm_mfma_f32_supported(a) && gemm_mfma_f32_supported(b)) return launch_gemm_mfma_f32(a, s, &b);
+    if (a.dt == DT_BF16 && gemm_mfma_dl_supported(a) && gemm_mfma_dl_supported(b)) return launch_gemm_mfma_dl(a, s, &b);
+  }
+  if (hipError_t e = launch_gemm(a, s); e != hipSuccess) return e;
+  return launch_gemm(b, s);
 }
 }  // namespace pf

@@ -6,7 +6,7 @@
 #ifdef PF_TUNING
 namespace pf {
 int g_attn_variant = 0, g_attn_stages = 0, g_attn_wide = 0, g_force_splits = 0, g_fuse_kv_route = 1, g_fold_q_scale = 1;
-int g_gemm_tile_override = 0, g_wavek_min_k = 2048, g_wavek_max_tiles = 512;
+int g_gemm_tile_override = 0, g_wavek_min_k = 1024, g_wavek_max_tiles = 256;
 }  // namespace pf
 
 extern "C" void pf_tune(int id) {
