@@ -30,7 +30,7 @@ constexpr int ROW_BYTES = BK * 2;  // 128
 // ------------------------------------------------------------------------------------------------------------------
 // WGM x WGN wavefronts on one shared tile
 // ------------------------------------------------------------------------------------------------------------------
-template <int NP, int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, int KB = 64, bool SPREAD_LOADS = false>
+template <int NP, int EM, int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, int KB = 64, bool SPREAD_LOADS = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf16_t, NP> L) {
   const bool second = NP == 2 && blockIdx.x >= L.grid0;
   const GemmProblem<bf16_t> &prob = L.p[second ? 1 : 0];
@@ -76,11 +76,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
     int c = (lane % CPR) ^ key(r);
     pw[i] = (unsigned)(((size_t)min(r, N - 1 - n0) * ldw + c * 8) * 2);
   }
-  const int nk = K / KB, k0 = L.kshift ? tn % nk : 0;   // first K tile (see GemmLaunch)
-  auto issue = [&](int stage, int kt0) {
+  const int nk = K / KB;
+  auto issue = [&](int stage, int kt) {
     unsigned char *sa = smem + stage * STAGE_BYTES;
     unsigned char *sw = sa + BM * RBY;
-    const int kt = kt0 + k0 >= nk ? kt0 + k0 - nk : kt0 + k0;
     const unsigned koff = (unsigned)kt * (KB * 2);
 #pragma unroll
     for (int i = 0; i < LA; ++i) srcA.load16(pa[i], koff, sa + (i * NW + wave) * 1024);
@@ -88,9 +87,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
     for (int i = 0; i < LW; ++i) srcW.load16(pw[i], koff, sw + (i * NW + wave) * 1024);
   };
   // load instruction `idx` (A instructions first, then W) of this wave for K tile kt
-  auto issue_one = [&](auto idx_c, int stage, int kt0) __attribute__((always_inline)) {
+  auto issue_one = [&](auto idx_c, int stage, int kt) __attribute__((always_inline)) {
     constexpr int idx = decltype(idx_c)::value;
-    const int kt = kt0 + k0 >= nk ? kt0 + k0 - nk : kt0 + k0;
     unsigned char *sa = smem + stage * STAGE_BYTES;
     const unsigned koff = (unsigned)kt * (KB * 2);
     if constexpr (idx < LA) srcA.load16(pa[idx], koff, sa + (idx * NW + wave) * 1024);
@@ -98,7 +96,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
   };
 
   // small tiles: the epilogue's residual / gate operands are requested first, ahead of every tile load
-  constexpr bool EPRE = BM * BN / 8 / (64 * NW) <= 2;
+  constexpr bool EPRE = EM == EM_RESIDUAL && BM * BN / 8 / (64 * NW) <= 2;
   EpiOperands<BM, BN, 64 * NW> eops;
   if constexpr (EPRE) eops.fetch(m0, n0, M, N, epi, vec_ok != 0);
 
@@ -205,15 +203,15 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
           tile[(rbase - pass * RB + 8 * (r >> 2) + 4 * hi + (r & 3)) * TLD + wn * WN + j * 32 + l32] = acc[i][j][r];
     }
     __syncthreads();
-    if constexpr (EPRE && RB == BM) tile_epilogue<BM, BN, TLD, 64 * NW, true>(tile, m0, n0, M, N, epi, vec_ok != 0, &eops);
-    else tile_epilogue<RB, BN, TLD, 64 * NW>(tile, m0 + pass * RB, n0, M, N, epi, vec_ok != 0);
+    if constexpr (EPRE && RB == BM) tile_epilogue<EM, BM, BN, TLD, 64 * NW, true>(tile, m0, n0, M, N, epi, vec_ok != 0, &eops);
+    else tile_epilogue<EM, RB, BN, TLD, 64 * NW>(tile, m0 + pass * RB, n0, M, N, epi, vec_ok != 0);
   }
 }
 
 // ------------------------------------------------------------------------------------------------------------------
 // four wavefronts split K; each owns a private two-stage ring for its own BM x BN x 64 tiles
 // ------------------------------------------------------------------------------------------------------------------
-template <int NP, int BM, int BN>
+template <int NP, int EM, int BM, int BN>
 __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> L) {
   const bool second = NP == 2 && blockIdx.x >= L.grid0;
   const GemmProblem<bf16_t> &prob = L.p[second ? 1 : 0];
@@ -277,7 +275,7 @@ __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> 
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  constexpr bool EPRE = BM * BN / 8 / 256 <= 2 && BM * BN / 8 >= 256;
+  constexpr bool EPRE = EM == EM_RESIDUAL && BM * BN / 8 / 256 <= 2 && BM * BN / 8 >= 256;
   EpiOperands<BM, BN, 256> eops;
   if constexpr (EPRE) eops.fetch(m0, n0, M, N, epi, vec_ok != 0);
 
@@ -341,8 +339,8 @@ __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> 
     *reinterpret_cast<float4 *>(p0 + r * TLD + c) = s0;
   }
   __syncthreads();
-  if constexpr (EPRE) tile_epilogue<BM, BN, TLD, 256, true>(p0, m0, n0, M, N, epi, vec_ok != 0, &eops);
-  else tile_epilogue<BM, BN, TLD>(p0, m0, n0, M, N, epi, vec_ok != 0);
+  if constexpr (EPRE) tile_epilogue<EM, BM, BN, TLD, 256, true>(p0, m0, n0, M, N, epi, vec_ok != 0, &eops);
+  else tile_epilogue<EM, BM, BN, TLD>(p0, m0, n0, M, N, epi, vec_ok != 0);
 }
 
 }  // namespace
@@ -364,35 +362,31 @@ hipError_t launch_tile(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   // the stage ring, or the fp32 tile (row stride BN + 4) that replaces it for the epilogue, whichever is larger
   constexpr int ring = NSTAGE * (BM + BN) * KB * 2, tile = BM * (BN + 4) * 4;
   constexpr int smem = (tile > ring && tile <= 96 * 1024) ? tile : ring;   // larger tiles finish in row passes
-  auto go = [&](auto np) -> hipError_t {
-    constexpr int NP = decltype(np)::value;
-    constexpr auto kernel = &gemm_tile_kernel<NP, BM, BN, NSTAGE, WGM, WGN, KB, SPREAD>;
+  auto go = [&](auto np, auto em) -> hipError_t {
+    constexpr int NP = decltype(np)::value, EM = decltype(em)::value;
+    constexpr auto kernel = &gemm_tile_kernel<NP, EM, BM, BN, NSTAGE, WGM, WGN, KB, SPREAD>;
     if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
     GemmLaunch<bf16_t, NP> L;
-    // Tile columns start at different K positions for the mid-size K where that was measured to help (operand rows of 6 KB:
-    // workgroups in step would all ask the memory side for the same 128-byte columns): 2048x9216x3072 123 -> 115 us,
-    // 2048x12288x3072 161 -> 153, 2560x9216x3072 153 -> 139, 16896x9216x3072 852 -> 838; nothing to gain at K = 1152 and at
-    // K = 15360, where it costs up to 1 %.
-    const unsigned grid = make_launch(a, b, BM, BN, &L, a.K >= 2048 && a.K <= 8192 ? 1 : 0);
+    const unsigned grid = make_launch(a, b, BM, BN, &L);
     kernel<<<grid, 64 * WGM * WGN, smem, s>>>(L);
     return hipGetLastError();
   };
-  return b ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
+  return for_launch_form(a, b, go);
 }
 
 template <int BM, int BN>
 hipError_t launch_wavek(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   constexpr int smem = 4 * 2 * (BM + BN) * ROW_BYTES;
-  auto go = [&](auto np) -> hipError_t {
-    constexpr int NP = decltype(np)::value;
-    constexpr auto kernel = &gemm_wavek_kernel<NP, BM, BN>;
+  auto go = [&](auto np, auto em) -> hipError_t {
+    constexpr int NP = decltype(np)::value, EM = decltype(em)::value;
+    constexpr auto kernel = &gemm_wavek_kernel<NP, EM, BM, BN>;
     if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
     GemmLaunch<bf16_t, NP> L;
     const unsigned grid = make_launch(a, b, BM, BN, &L);
     kernel<<<grid, 256, smem, s>>>(L);
     return hipGetLastError();
   };
-  return b ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
+  return for_launch_form(a, b, go);
 }
 
 }  // namespace
@@ -419,15 +413,16 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 //   rounds x tile area / rate x (K tiles + fill) / K tiles
 // rounds = ceil(tiles / 256 CUs); rate = what a CU does on the tile in steady state, relative to 128x192 (1.0 PFLOP/s on
 // the chip); fill = K tiles' worth of time that the start and the epilogue of a workgroup cost, 2 when a second workgroup of
-// the CU covers them, 8 when the CU holds one.  Measured (us, isolated GEMMs with cold weights; 256x256 | 256x192 | 256x128 |
+// the CU covers them, 9 when the CU holds one.  Measured (us, isolated GEMMs with cold weights; 256x256 | 256x192 | 256x128 |
 // 128x192 | 128x128, * = chosen; the rule before took three-stage 256x128 tiles with 32-wide K tiles from 512 of them on):
-//    2560 x  9216 x  3072   157 | 139* | 148 | 142 | 144    (198 before)
-//    2560 x 12288 x  3072   183* | 209 | 206 | 193 | 203    (272 before)
-//    2560 x  3072 x 15360   374 | 339 | 235* | 296 | 250
-//   16896 x  9216 x  3072   837* | 878 | 964 | 1031 | 1068
-//   16896 x  3072 x 15360  1562* | 1728 | 1662 | 1633 | 1696 (2140 before)
+//    2560 x  9216 x  3072   164 | 152* | 155 | 145 | 158    (198 before)
+//    2560 x 12288 x  3072   184* | 233 | 218 | 203 | 221    (272 before)
+//    2560 x  3072 x 15360   374 | 339 | 235* | 301 | 257
+//   16896 x  9216 x  3072   852* | 903 | 972 | 1032 | 1088
+//   16896 x  3072 x 15360  1562* | 1728 | 1662 | 1646 | 1696 (2140 before)
 //    4096 x  4608 x  1152    86 | 68 | 74 | 61* | 71, 128x64 63
 //    4096 x  1152 x  4608   116 | 106 | 70 | 61* | 72, 128x64 70
+//    4096 x  3456 x  1152    38 | 52 | 41 | 46 | 41*, 128x64 48
 // 128x192 takes three stages and issues its prefetch loads one at a time between the MFMAs (instead of in a burst behind the
 // barrier) for long K with at most one tile per CU: 2048x3072x15360 204 -> 183 us, 4096x1152x4608 65 -> 55 us; every other
 // tile loses by it or keeps nothing of the gain inside a stage.
@@ -437,8 +432,10 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 //    8.2 us (four-stage 64x64: 8.9), 512x1152x4608 19.8 (23.6), 512x1536x6144 25.5 (31.5); with more tiles than CUs it loses:
 //    1024x1152x4608 34.3 (29.4).
 //  * 64x64 with four stages while every workgroup is resident at once (two per CU), 375x4608x1536 14.0 us (two stages 19.6);
-//  * beyond, 64x128 with three stages under the same condition: 1024x3456x1152 16.9 -> 15.2 us, 512x6144x1536 22.8 -> 22.0,
-//    512x4608x1536 20.3 -> 18.7 against two-stage 64x64 tiles, which take what is left.
+//  * beyond, 64x128 with three stages under the same condition, where its rounds (of 256 tiles) are no more work than those
+//    of 64x64 tiles or K is long enough to pay for it: 1024x3456x1152 16.9 -> 15.2 us, 512x6144x1536 22.8 -> 22.0,
+//    512x4608x1536 20.3 -> 18.7 against two-stage 64x64 tiles, which take what is left (512x4608x1152 inside a stage: 15.8
+//    us, with 64x128 17.3).
 enum { V_256x256 = 0, V_256x128_K32S3, V_256x128_S3, V_128x128, V_128x64, V_WAVEK, V_64x64_S4, V_64x64_S3, V_64x64_S2,
        V_128x192_S2, V_256x192_S2, V_128x192_S3, V_64x128_S3, V_COUNT };
 
@@ -448,15 +445,15 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
   const bool wide_heads = a.kvr.q_norm && a.kvr.dh > 64;
   if (tiles(128, 64) >= 512 || (a.K >= 4096 && tiles(256, 128) >= 128)) {
     struct Candidate { int v, bm, bn, per_cu; double rate; };
-    static constexpr Candidate cand[] = {{V_256x256, 256, 256, 1, 1.2}, {V_256x192_S2, 256, 192, 1, 1.1}, {V_256x128_S3, 256, 128, 1, 1.03},
-                                         {V_128x192_S2, 128, 192, 2, 1.0}, {V_128x128, 128, 128, 2, 0.95}, {V_128x64, 128, 64, 3, 0.85}};
+    static constexpr Candidate cand[] = {{V_256x256, 256, 256, 1, 1.25}, {V_256x192_S2, 256, 192, 1, 1.15}, {V_256x128_S3, 256, 128, 1, 1.03},
+                                         {V_128x192_S2, 128, 192, 2, 1.0}, {V_128x128, 128, 128, 2, 0.95}, {V_128x64, 128, 64, 3, 0.78}};
     const double nk = a.K / BK;
     int best = V_128x128;
     double best_cost = 1e300;
     for (const Candidate &c : cand) {
       if (wide_heads && c.bn % 128) continue;
       const int64_t t = tiles(c.bm, c.bn);
-      const double fill = c.per_cu > 1 && t > 256 ? 2.0 : 8.0;
+      const double fill = c.per_cu > 1 && t > 256 ? 2.0 : 9.0;
       const double cost = (double)((t + 255) / 256) * c.bm * c.bn / c.rate * (nk + fill) / nk;
       if (cost < best_cost) { best_cost = cost; best = c.v; }
     }
@@ -466,7 +463,9 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
   const int64_t t64 = tiles(64, 64);
   if (t64 <= g_wavek_max_tiles && a.K >= g_wavek_min_k) return V_WAVEK;
   if (t64 <= 512) return V_64x64_S4;
-  return tiles(64, 128) <= 512 ? V_64x128_S3 : V_64x64_S2;
+  const int64_t t128 = tiles(64, 128);
+  const bool even = (t128 + 255) / 256 * 2 <= (t64 + 255) / 256;
+  return t128 <= 512 && (even || a.K >= 1536) ? V_64x128_S3 : V_64x64_S2;
 }
 
 static hipError_t launch_variant(int v, const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
@@ -545,13 +544,13 @@ hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s, const GemmArgs 
 }
 
 const char *gemm_mfma_dl_variant_name(const GemmArgs &a) {
-  static const char *names[V_COUNT] = {"gemm_tile_kernel<1,256,256,2,4,2,64,false>", "gemm_tile_kernel<1,256,128,3,4,2,32,false>",
-                                       "gemm_tile_kernel<1,256,128,3,4,2,64,false>", "gemm_tile_kernel<1,128,128,2,2,2,64,false>",
-                                       "gemm_tile_kernel<1,128,64,2,2,2,64,false>", "gemm_wavek_kernel<1,64,64>",
-                                       "gemm_tile_kernel<1,64,64,4,2,2,64,false>", "gemm_tile_kernel<1,64,64,3,2,2,64,false>",
-                                       "gemm_tile_kernel<1,64,64,2,2,2,64,false>", "gemm_tile_kernel<1,128,192,2,2,2,64,false>",
-                                       "gemm_tile_kernel<1,256,192,2,4,2,64,false>", "gemm_tile_kernel<1,128,192,3,2,2,64,true>",
-                                       "gemm_tile_kernel<1,64,128,3,2,2,64,false>"};
+  static const char *names[V_COUNT] = {"gemm_tile_kernel<256,256,2,4,2,64,false>", "gemm_tile_kernel<256,128,3,4,2,32,false>",
+                                       "gemm_tile_kernel<256,128,3,4,2,64,false>", "gemm_tile_kernel<128,128,2,2,2,64,false>",
+                                       "gemm_tile_kernel<128,64,2,2,2,64,false>", "gemm_wavek_kernel<64,64>",
+                                       "gemm_tile_kernel<64,64,4,2,2,64,false>", "gemm_tile_kernel<64,64,3,2,2,64,false>",
+                                       "gemm_tile_kernel<64,64,2,2,2,64,false>", "gemm_tile_kernel<128,192,2,2,2,64,false>",
+                                       "gemm_tile_kernel<256,192,2,4,2,64,false>", "gemm_tile_kernel<128,192,3,2,2,64,true>",
+                                       "gemm_tile_kernel<64,128,3,2,2,64,false>"};
   return names[(a.tile >= 1 && a.tile <= V_COUNT) ? a.tile - 1 : pick_variant(a)];
 }
 

@@ -29,7 +29,7 @@ __device__ __forceinline__ void mma8(const f32x4 (&a)[N], const f32x4 &w, f32x16
     for (int i = 0; i < N; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], w[e], acc[i], 0, 0, 0);
 }
 
-template <int NP, int BM, int BN, int NSTAGE, int WGM, int WGN>
+template <int NP, int EM, int BM, int BN, int NSTAGE, int WGM, int WGN>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_tile_kernel(GemmLaunch<float, NP> L) {
   const bool second = NP == 2 && blockIdx.x >= L.grid0;
   const GemmProblem<float> &prob = L.p[second ? 1 : 0];
@@ -124,10 +124,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_tile_kernel(GemmLaunc
       for (int r = 0; r < 16; ++r)
         tile[(wm * WM + i * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)) * TLD + wn * WN + j * 32 + l32] = acc[j][i][r];
   __syncthreads();
-  tile_epilogue<BM, BN, TLD, 64 * NW>(tile, m0, n0, M, N, epi, vec_ok != 0);
+  tile_epilogue<EM, BM, BN, TLD, 64 * NW>(tile, m0, n0, M, N, epi, vec_ok != 0);
 }
 
-template <int NP, int BM, int BN, int NW>
+template <int NP, int EM, int BM, int BN, int NW>
 __global__ __launch_bounds__(64 * NW) void gemm_f32_wavek_kernel(GemmLaunch<float, NP> L) {
   const bool second = NP == 2 && blockIdx.x >= L.grid0;
   const GemmProblem<float> &prob = L.p[second ? 1 : 0];
@@ -229,37 +229,37 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_wavek_kernel(GemmLaunch<floa
     *reinterpret_cast<float4 *>(p0 + r * TLD + c) = s0;
   }
   __syncthreads();
-  tile_epilogue<BM, BN, TLD, NT>(p0, m0, n0, M, N, epi, vec_ok != 0);
+  tile_epilogue<EM, BM, BN, TLD, NT>(p0, m0, n0, M, N, epi, vec_ok != 0);
 }
 
 template <int BM, int BN, int NSTAGE, int WGM, int WGN>
 hipError_t launch_tile(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   constexpr int ring = NSTAGE * (BM + BN) * ROW_BYTES, tile = BM * (BN + 4) * 4, smem = tile > ring ? tile : ring;
-  auto go = [&](auto np) -> hipError_t {
-    constexpr int NP = decltype(np)::value;
-    constexpr auto kernel = &gemm_f32_tile_kernel<NP, BM, BN, NSTAGE, WGM, WGN>;
+  auto go = [&](auto np, auto em) -> hipError_t {
+    constexpr int NP = decltype(np)::value, EM = decltype(em)::value;
+    constexpr auto kernel = &gemm_f32_tile_kernel<NP, EM, BM, BN, NSTAGE, WGM, WGN>;
     if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
     GemmLaunch<float, NP> L;
     const unsigned grid = make_launch(a, b, BM, BN, &L);
     kernel<<<grid, 64 * WGM * WGN, smem, s>>>(L);
     return hipGetLastError();
   };
-  return b ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
+  return for_launch_form(a, b, go);
 }
 
 template <int BM, int BN, int NW>
 hipError_t launch_wavek(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   constexpr int smem = NW * 2 * (BM + BN) * ROW_BYTES;
-  auto go = [&](auto np) -> hipError_t {
-    constexpr int NP = decltype(np)::value;
-    constexpr auto kernel = &gemm_f32_wavek_kernel<NP, BM, BN, NW>;
+  auto go = [&](auto np, auto em) -> hipError_t {
+    constexpr int NP = decltype(np)::value, EM = decltype(em)::value;
+    constexpr auto kernel = &gemm_f32_wavek_kernel<NP, EM, BM, BN, NW>;
     if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
     GemmLaunch<float, NP> L;
     const unsigned grid = make_launch(a, b, BM, BN, &L);
     kernel<<<grid, 64 * NW, smem, s>>>(L);
     return hipGetLastError();
   };
-  return b ? go(std::integral_constant<int, 2>{}) : go(std::integral_constant<int, 1>{});
+  return for_launch_form(a, b, go);
 }
 
 enum { F_64x64 = 0, F_WAVEK4, F_WAVEK8, F_COUNT };
@@ -290,8 +290,8 @@ bool gemm_mfma_f32_supported(const GemmArgs &a) {
 }
 
 const char *gemm_mfma_f32_variant_name(const GemmArgs &a) {
-  static const char *names[F_COUNT] = {"gemm_f32_tile_kernel<1,64,64,3,2,2>", "gemm_f32_wavek_kernel<1,32,32,4>",
-                                       "gemm_f32_wavek_kernel<1,32,32,8>"};
+  static const char *names[F_COUNT] = {"gemm_f32_tile_kernel<64,64,3,2,2>", "gemm_f32_wavek_kernel<32,32,4>",
+                                       "gemm_f32_wavek_kernel<32,32,8>"};
   return names[pick_variant(a)];
 }
 

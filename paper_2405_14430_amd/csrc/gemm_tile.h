@@ -80,7 +80,6 @@ template <typename T, int NP>
 struct GemmLaunch {
   GemmProblem<T> p[NP];
   int N, K;
-  int kshift;     // != 0: the tiles of column tn start their K loop at K tile tn and wrap around
   unsigned grid0;
 };
 
@@ -113,7 +112,7 @@ struct EpiOperands {
   bool on;
   template <typename T>
   __device__ __forceinline__ void fetch(int m0, int n0, int M, int N, const Epilogue<T> &epi, bool vec_ok) {
-    on = vec_ok && epi.mode == 1;
+    on = vec_ok;
     if (!on) return;
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
@@ -136,9 +135,13 @@ __device__ __forceinline__ void load8(const float *p, float *o) { Vec16<float>::
 __device__ __forceinline__ void store8(bf16_t *p, const float *o) { Vec16<bf16_t>::store(p, o); }
 __device__ __forceinline__ void store8(float *p, const float *o) { Vec16<float>::store(p, o); Vec16<float>::store(p + 4, o + 4); }
 
+// Which epilogue a kernel is compiled for.  Compiled for all of them the kernels are four to five times the code they run,
+// and a launch of ten microseconds feels every instruction-cache line it has to fetch.
+enum { EM_STORE = 0, EM_RESIDUAL = 1, EM_KV_ROUTE = 2 };
+
 // Epilogue over a finished fp32 tile held row-major in LDS (row stride TLD floats).  PRE: residual / gate operands
 // come from `ops` (fetched earlier) when ops->on.
-template <int BM, int BN, int TLD, int NT = 256, bool PRE = false, typename T>
+template <int EM, int BM, int BN, int TLD, int NT = 256, bool PRE = false, typename T>
 __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0, int M, int N, const Epilogue<T> &epi, bool vec_ok, const EpiOperands<BM, BN, NT> *ops = nullptr) {
   constexpr int GROUPS = BM * BN / 8;
   constexpr int IT = (GROUPS + NT - 1) / NT, UNR = PRE ? IT : 1;
@@ -162,7 +165,7 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] += b[e];
     }
-    if (epi.mode == 0 && epi.kv.kbuf) {
+    if constexpr (EM == EM_KV_ROUTE) {
       // QKV projection routed into the K / V^T buffers (an 8-column group never straddles q|k|v or two heads)
       const KvRoute &kv = epi.kv;
       const int part = col / kv.d, cc = col - part * kv.d;
@@ -201,7 +204,7 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
         store8(reinterpret_cast<T *>(kv.kbuf) + (size_t)img * kv.img_stride + ((size_t)hh * kv.Lp + brow) * kv.dh + ch, v);
       }
       // part 2 (v) is written by the transposed pass below
-    } else if (epi.mode == 0) {
+    } else if constexpr (EM == EM_STORE) {
       if (col + 8 > epi.gelu_from) {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
@@ -239,7 +242,8 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
   }
   // v columns of a routed QKV projection: V^T[h][c][buffer row].  The tile is walked column-wise, eight consecutive
   // rows per thread and consecutive threads along the rows, so that the stores run along V^T's contiguous axis.
-  if (epi.mode == 0 && epi.kv.kbuf && n0 + BN > 2 * epi.kv.d) {
+  if constexpr (EM != EM_KV_ROUTE) return;
+  if (n0 + BN > 2 * epi.kv.d) {
     const KvRoute &kv = epi.kv;
     constexpr int RG = BM / 8;
     for (int u = threadIdx.x; u < RG * BN; u += NT) {
@@ -305,7 +309,7 @@ inline bool vec_epilogue_ok(const GemmArgs &a) {
 
 // Fills the launch of `a` and, for NP = 2, `b` (same N and K) with BM x BN tiles; returns the workgroup count.
 template <typename T, int NP>
-inline unsigned make_launch(const GemmArgs &a, const GemmArgs *b, int BM, int BN, GemmLaunch<T, NP> *L, int kshift = 0) {
+inline unsigned make_launch(const GemmArgs &a, const GemmArgs *b, int BM, int BN, GemmLaunch<T, NP> *L) {
   unsigned total = 0;
   for (int i = 0; i < NP; ++i) {
     const GemmArgs &g = i ? *b : a;
@@ -315,8 +319,16 @@ inline unsigned make_launch(const GemmArgs &a, const GemmArgs *b, int BM, int BN
     if (i == 0) L->grid0 = grid;
     total += grid;
   }
-  L->N = a.N; L->K = a.K; L->kshift = kshift;
+  L->N = a.N; L->K = a.K;
   return total;
+}
+
+// go(number of problems, epilogue), both as integral constants
+template <typename F>
+inline hipError_t for_launch_form(const GemmArgs &a, const GemmArgs *b, F &&go) {
+  auto with = [&](auto em) { return b ? go(std::integral_constant<int, 2>{}, em) : go(std::integral_constant<int, 1>{}, em); };
+  if (a.kvr.kbuf) return with(std::integral_constant<int, EM_KV_ROUTE>{});
+  return a.epilogue == 0 ? with(std::integral_constant<int, EM_STORE>{}) : with(std::integral_constant<int, EM_RESIDUAL>{});
 }
 
 // tiles of a launch of one or two GEMMs
