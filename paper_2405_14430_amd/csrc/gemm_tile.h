@@ -137,7 +137,7 @@ __device__ __forceinline__ void store8(float *p, const float *o) { Vec16<float>:
 
 // Which epilogue a kernel is compiled for.  Compiled for all of them the kernels are four to five times the code they run,
 // and a launch of ten microseconds feels every instruction-cache line it has to fetch.
-enum { EM_STORE = 0, EM_RESIDUAL = 1, EM_KV_ROUTE = 2 };
+enum { EM_STORE = 0, EM_RESIDUAL = 1, EM_KV_ROUTE = 2, EM_STORE_ERF = 3 };   // (store: plain columns or tanh GELU)
 
 // Epilogue over a finished fp32 tile held row-major in LDS (row stride TLD floats).  PRE: residual / gate operands
 // come from `ops` (fetched earlier) when ops->on.
@@ -156,7 +156,8 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
     float4 lo = *reinterpret_cast<const float4 *>(src), hi4 = *reinterpret_cast<const float4 *>(src + 4);
     float v[8] = {lo.x, lo.y, lo.z, lo.w, hi4.x, hi4.y, hi4.z, hi4.w};
     if (!vec_ok || col + 8 > N) {
-      for (int e = 0; e < 8 && col + e < N; ++e) epi.apply(row, col + e, v[e]);
+#pragma unroll 1
+      for (int e = 0; e < 8 && col + e < N; ++e) epi.apply(row, col + e, src[e]);   // (rare: small code, not fast code)
       continue;
     }
     if (epi.bias) {
@@ -204,11 +205,11 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
         store8(reinterpret_cast<T *>(kv.kbuf) + (size_t)img * kv.img_stride + ((size_t)hh * kv.Lp + brow) * kv.dh + ch, v);
       }
       // part 2 (v) is written by the transposed pass below
-    } else if constexpr (EM == EM_STORE) {
+    } else if constexpr (EM == EM_STORE || EM == EM_STORE_ERF) {
       if (col + 8 > epi.gelu_from) {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-          if (col + e >= epi.gelu_from) v[e] = gelu_f(v[e], epi.gelu_tanh);
+          if (col + e >= epi.gelu_from) v[e] = gelu_f(v[e], EM != EM_STORE_ERF);
       }
       store8(reinterpret_cast<T *>(epi.C) + (size_t)row * epi.ldc + col, v);
     } else {
@@ -263,13 +264,14 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
       if (whole && (brow & 7) == 0) {
         store8(vt + (size_t)img * kv.img_stride + brow, o);
       } else {
-#pragma unroll
+#pragma unroll 1
         for (int e = 0; e < 8; ++e) {
           const int r2 = row + e;
           if (r2 >= M) break;
           const int i2 = kv.seg > 0 ? r2 / kv.seg : 0;
           const int l2 = r2 - i2 * kv.seg;
-          vt[(size_t)i2 * kv.img_stride + (l2 < kv.split ? kv.row0a + l2 : kv.row0b + (l2 - kv.split))] = (T)o[e];
+          vt[(size_t)i2 * kv.img_stride + (l2 < kv.split ? kv.row0a + l2 : kv.row0b + (l2 - kv.split))] =
+              (T)(tile[(rg * 8 + e) * TLD + cl] + b);
         }
       }
     }
@@ -328,7 +330,8 @@ template <typename F>
 inline hipError_t for_launch_form(const GemmArgs &a, const GemmArgs *b, F &&go) {
   auto with = [&](auto em) { return b ? go(std::integral_constant<int, 2>{}, em) : go(std::integral_constant<int, 1>{}, em); };
   if (a.kvr.kbuf) return with(std::integral_constant<int, EM_KV_ROUTE>{});
-  return a.epilogue == 0 ? with(std::integral_constant<int, EM_STORE>{}) : with(std::integral_constant<int, EM_RESIDUAL>{});
+  if (a.epilogue != 0) return with(std::integral_constant<int, EM_RESIDUAL>{});
+  return a.gelu_tanh || a.gelu_from >= a.N ? with(std::integral_constant<int, EM_STORE>{}) : with(std::integral_constant<int, EM_STORE_ERF>{});
 }
 
 // tiles of a launch of one or two GEMMs
