@@ -413,7 +413,8 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 //   rounds x tile area / rate x (K tiles + fill) / K tiles
 // rounds = ceil(tiles / 256 CUs); rate = what a CU does on the tile in steady state, relative to 128x192 (1.0 PFLOP/s on
 // the chip); fill = K tiles' worth of time that the start and the epilogue of a workgroup cost, 2 when a second workgroup of
-// the CU covers them, 9 when the CU holds one.  Measured (us, isolated GEMMs with cold weights; 256x256 | 256x192 | 256x128 |
+// the CU covers them, 9 for tiles that
+// fill a CU by themselves, 14 for those of the two-workgroup kernels that find no second one.  Measured (us, isolated GEMMs with cold weights; 256x256 | 256x192 | 256x128 |
 // 128x192 | 128x128, * = chosen; the rule before took three-stage 256x128 tiles with 32-wide K tiles from 512 of them on):
 //    2560 x  9216 x  3072   164 | 152* | 155 | 145 | 158    (198 before)
 //    2560 x 12288 x  3072   184* | 233 | 218 | 203 | 221    (272 before)
@@ -453,7 +454,7 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
     for (const Candidate &c : cand) {
       if (wide_heads && c.bn % 128) continue;
       const int64_t t = tiles(c.bm, c.bn);
-      const double fill = c.per_cu > 1 && t > 256 ? 2.0 : 9.0;
+      const double fill = c.per_cu == 1 ? 9.0 : (t > 256 ? 2.0 : 14.0);
       const double cost = (double)((t + 255) / 256) * c.bm * c.bn / c.rate * (nk + fill) / nk;
       if (cost < best_cost) { best_cost = cost; best = c.v; }
     }

@@ -96,7 +96,12 @@ int choose_splits(int path, int dt, int nq, int H, int kv_rows, int head_dim) {
   const bool f32 = dt == PF_F32, simt = path == PATH_SIMT || f32;
   const bool gen2 = !simt && pf::g_attn_variant == 0 && (head_dim == 64 || head_dim == 72 || head_dim == 128);
   const int qtile = simt ? 64 : (gen2 ? attn_mfma2_qtile(nq) : 128);
-  const int resident = qtile == 256 ? 256 : 512;   // workgroups the chip holds at a time
+  // workgroups the chip holds at a time (fp32, head sizes up to 72: three per CU; 512 queries x 16 heads x 4096 keys 134 ->
+  // 122 us with 6 splits instead of 4)
+  const int resident = qtile == 256 ? 256 : (f32 && path != PATH_SIMT && head_dim <= 72 ? 768 : 512);
+  // the combine pass: a launch, and the partial rows written and read at memory speed (about 7 MB in the time of a tile;
+  // 2560 queries x 24 heads of 128, one split instead of two: 429 + 16 -> 426 us)
+  const double row_units = (double)nq * H * head_dim * (f32 ? 2.0 : 1.0) * 1.43e-7;
   const int ktile = simt ? 32 : 64;
   const int64_t blocks = (int64_t)((nq + qtile - 1) / qtile) * H;
   const int tiles = (kv_rows + ktile - 1) / ktile;
@@ -111,7 +116,7 @@ int choose_splits(int path, int dt, int nq, int H, int kv_rows, int head_dim) {
     const int64_t rounds = (wgs + resident - 1) / resident;
     const double fill = wgs >= resident ? 1.0 : (double)wgs / resident;
     double cost = (double)rounds * ((tiles + sp - 1) / sp + 4) * (1.0 + 0.5 * (1.0 - fill));
-    if (sp > 1) cost += 2.0 + 0.5 * sp;
+    if (sp > 1) cost += 2.0 + (4 * sp + 2) * row_units;
     if (cost < best_cost - 1e-9) { best_cost = cost; best = sp; }
   }
   return best;
@@ -408,8 +413,15 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
   // first row of the text / image rows in the workspace buffers and the distance between images, in rows
   const size_t t_row0 = 0, i_row0 = single ? (size_t)Tt : (size_t)B * Tt;
   const size_t t_pitch = single ? (size_t)R : (size_t)Tt, i_pitch = single ? (size_t)R : (size_t)n_img;
-  const bool gather = Tt && (single || (((uintptr_t)text | (uintptr_t)text_out | (uintptr_t)x_img | (uintptr_t)y_img) & 15));
-  if (gather) {
+  // The single-stream kind needs no gather either when the first norm and the first and last down projections, which touch
+  // the caller's rows, can treat text and image rows as two sets in one launch without an extra row of tiles (four copies of
+  // 7 - 45 us a call at Flux scale): with one image whose text rows end a 256-row tile.
+  const bool aligned = (((uintptr_t)text | (uintptr_t)text_out | (uintptr_t)x_img | (uintptr_t)y_img) & 15) == 0;
+  const bool two_sets = single && Tt && aligned && B == 1 && (Tt + 255) / 256 + (n_img + 255) / 256 == (R + 255) / 256;
+  const bool gather = Tt && !two_sets && (single || !aligned);
+  if (two_sets) {
+    xsrc = x_img;                                   // rows of the first layer; xres holds text and image rows in between
+  } else if (gather) {
     if (!single) tsrc = xres, xsrc = xbuf = xres + i_row0 * D;
     PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(xres + t_row0 * D, t_pitch * D, text, (size_t)Tt * D, (size_t)Tt * D, B, st); }));
     PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(xres + i_row0 * D, i_pitch * D, x_img, (size_t)n_img * D, (size_t)n_img * D, B, st); }));
@@ -480,7 +492,12 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
       const pf_layer_weights &lw = s->img[l];
       const float *m = s->mod(0, l);
       const int RT = B * R;
-      PF_TRY(run(s, PF_KC_LN_MODULATE, [&] { return launch_ln_modulate(dt, LnRows{xsrc, m, m + D, h, RT, B > 1 ? R : 0}, nullptr, D, c.ln_eps, D, D, 1, mstride, st); }));
+      PF_TRY(run(s, PF_KC_LN_MODULATE, [&] {
+        const LnRows all{xsrc, m, m + D, h, RT, B > 1 ? R : 0};
+        const LnRows parts[2] = {{text, m, m + D, h, Tt, 0}, {x_img, m, m + D, h + (size_t)Tt * D * e, n_img, 0}};
+        if (two_sets && l == 0) return launch_ln_modulate(dt, parts[0], &parts[1], D, c.ln_eps, D, D, 1, mstride, st);
+        return launch_ln_modulate(dt, all, nullptr, D, c.ln_eps, D, D, 1, mstride, st);
+      }));
       {
         const bool pre = pre_ok && qkv_route(s, h, lw, qkv, true) != ROUTE_SCATTER_PLAIN;
         const QkvPart part{h, &lw, qkv, R, Tt, 0, row0_img, img_off, true};
@@ -491,7 +508,19 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
       // MLP branch runs in parallel with attention: GELU(h W_up^T + b) lands right of the attention columns
       PF_TRY(gemm(s, PF_KC_GEMM_UP, gemm_args(s, h, D, lw.w_up, D, lw.b_up, a + (size_t)D * e, D + F, RT, F, D, 0, 0, nullptr, nullptr, 0, nullptr, 0)));
       PF_TRY(attention(s, PF_KC_ATTENTION, qkv, 3 * D, kb, vb, d.Lkv, d.Lp, a, D + F, R, q_pre));
-      PF_TRY(gemm(s, PF_KC_GEMM_DOWN, gemm_args(s, a, D + F, lw.w_down, D + F, lw.b_down, xbuf, D, RT, D, D + F, 1, 0, m + 2 * D, xsrc, D, nullptr, 0, nullptr, R)));
+      auto down = [&](size_t row, int rows, const float *from, float *to) {
+        return gemm_args(s, a + row * (D + F) * e, D + F, lw.w_down, D + F, lw.b_down, to, D, rows, D, D + F, 1, 0, m + 2 * D, from, D,
+                         nullptr, 0, nullptr, R);
+      };
+      const bool first = l == 0, last = l == c.n_layers - 1;
+      if (two_sets && (first || last)) {
+        const GemmArgs g[2] = {down(0, Tt, first ? text : xres, last && text_out ? text_out : xres),
+                               down(Tt, n_img, first ? x_img : xres + (size_t)Tt * D, last && y_img ? y_img : xres + (size_t)Tt * D)};
+        PF_TRY(gemm(s, PF_KC_GEMM_DOWN, g, 2));
+        xsrc = xres;
+        continue;
+      }
+      PF_TRY(gemm(s, PF_KC_GEMM_DOWN, down(0, RT, xsrc, xbuf)));
       xsrc = xbuf;
       continue;
     }
@@ -573,7 +602,7 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
       PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(y_img, (size_t)n_img * D, xres + i_row0 * D, i_pitch * D, (size_t)n_img * D, B, st); }));
     if (text_out)
       PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(text_out, (size_t)Tt * D, xres + t_row0 * D, t_pitch * D, (size_t)Tt * D, B, st); }));
-  } else if (Tt && text_out && tsrc != text_out) {
+  } else if (!single && Tt && text_out && tsrc != text_out) {
     // a stack of one final joint block passes its text rows through
     PF_TRY(run(s, PF_KC_COPY, [&] { return copy_blocks(text_out, (size_t)Tt * D, tsrc, (size_t)Tt * D, (size_t)Tt * D, B, st); }));
   }
