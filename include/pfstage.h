@@ -63,7 +63,7 @@ typedef enum {
 } pf_block_kind;
 
 typedef enum {
-  PF_PATH_AUTO = 0, /* MFMA kernels for bf16, plain SIMT kernels for fp32 */
+  PF_PATH_AUTO = 0, /* MFMA kernels (plain SIMT kernels for fp32 shapes those do not take) */
   PF_PATH_SIMT = 1, /* force the plain SIMT kernels (debugging aid; still GPU code) */
   /* pf_op_attention / pf_op_attention_static only: as PF_PATH_AUTO, but q already carries the factor
    * log2(e) / sqrt(head_dim), the form in which a stage's QKV projection hands the queries to its self-attention
@@ -295,8 +295,8 @@ pf_status pf_op_axpy(const float *x, const float *y, float alpha, float *out, in
  * coefficient on x_t (deterministic DDIM-type rules).  Same argument rules as pf_op_axpy. */
 pf_status pf_op_axpby(const float *x, const float *y, float a, float b, float *out, int64_t n, void *stream);
 
-/* Name of the kernel instance the library's tile heuristic runs for a GEMM of this shape (static string; matches the
- * template instance seen in a rocprofv3 kernel trace).  Used by the benchmark to group GEMM launches by kernel. */
+/* Kernel and tile configuration the library's tile heuristic runs for a GEMM of this shape with dense, aligned operands
+ * (static string; a rocprofv3 kernel trace shows the instance with its number of problems and epilogue in front).  Used by the benchmark to group GEMM launches by kernel. */
 const char *pf_gemm_kernel_name(int dtype, int path, int M, int N, int K);
 /* Likewise for an attention launch of nq query rows per image (q_prescaled: the stage's self-attention, whose queries
  * carry the softmax factor; 0: plain queries).  The string is per-thread storage, valid until the next call. */

@@ -487,7 +487,8 @@ static hipError_t launch_variant(int v, const GemmArgs &a, const GemmArgs *b, hi
   }
 }
 
-int gemm_mfma_dl_tile_count() { return V_COUNT; }
+// configurations a caller can pin: all but the last, which the rule alone takes
+int gemm_mfma_dl_tile_count() { return V_64x128_S3; }
 
 hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s, const GemmArgs *b) {
 #ifdef PF_TUNING
@@ -540,7 +541,7 @@ hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s, const GemmArgs 
     default: break;
   }
 #endif
-  if (a.tile >= 1 && a.tile <= V_COUNT) return launch_variant(a.tile - 1, a, b, s);
+  if (a.tile >= 1 && a.tile <= gemm_mfma_dl_tile_count()) return launch_variant(a.tile - 1, a, b, s);
   return launch_variant(pick_variant(a, b), a, b, s);
 }
 
@@ -552,7 +553,7 @@ const char *gemm_mfma_dl_variant_name(const GemmArgs &a) {
                                        "gemm_tile_kernel<64,64,2,2,2,64,false>", "gemm_tile_kernel<128,192,2,2,2,64,false>",
                                        "gemm_tile_kernel<256,192,2,4,2,64,false>", "gemm_tile_kernel<128,192,3,2,2,64,true>",
                                        "gemm_tile_kernel<64,128,3,2,2,64,false>"};
-  return names[(a.tile >= 1 && a.tile <= V_COUNT) ? a.tile - 1 : pick_variant(a)];
+  return names[(a.tile >= 1 && a.tile <= gemm_mfma_dl_tile_count()) ? a.tile - 1 : pick_variant(a)];
 }
 
 }  // namespace pf

@@ -87,15 +87,20 @@ struct GemmLaunch {
 // the ids x, x + 8, ...  Every XCD gets one rectangular block of the tile grid - the grid is cut gx times along M and
 // 8 / gx times along N - because what an XCD fetches from memory is the A rows of its block plus the W rows of its
 // block: a contiguous run of tiles (a block one tile-column wide and all of M high) makes every XCD fetch all of A
-// (Flux-scale MLP-down: 623 MB fetched per launch for 157 MB of operands).  Inside the block the N index runs
-// fastest (workgroups in flight together share A tiles; measured equal or better than M fastest on every GEMM of the
-// five workloads, up to 12 % on the QKV projections).  Returns false for the surplus ids of the padded grid.
-__host__ __device__ __forceinline__ bool tile_of_id(int id, int tiles_m, int tiles_n, int gx, int &tm, int &tn) {
-  const int gy = 8 / gx;
+// (Flux-scale MLP-down: 623 MB fetched per launch for 157 MB of operands).  Inside the block
+// the tiles are walked in bands of G tile rows (G = cut >> 8), column by column: the workgroups that an XCD runs at a time
+// should cover a near-square patch of the output, because per K step they fetch the A rows and the W rows of that patch, and
+// what all XCDs together fetch has to stay below the 7 TB/s at which the memory side fills the L2s (row by row, 32 tiles of
+// 256x256 ask for 33 operand panels per K step, in bands of four for 12).  Returns false for the surplus ids of the padded
+// grid.
+__host__ __device__ __forceinline__ bool tile_of_id(int id, int tiles_m, int tiles_n, int cut, int &tm, int &tn) {
+  const int gx = cut & 255, G = cut >> 8, gy = 8 / gx;
   const int bm = (tiles_m + gx - 1) / gx, bn = (tiles_n + gy - 1) / gy;
   const int x = id & 7, j = id >> 3;
   if (j >= bm * bn) return false;
-  const int lm = j / bn, ln = j - lm * bn;
+  const int band = j / (G * bn), jj = j - band * (G * bn);
+  const int rows = G < bm - band * G ? G : bm - band * G;   // (the last band may be lower)
+  const int ln = jj / rows, lm = band * G + (jj - ln * rows);
   tm = (x % gx) * bm + lm;
   tn = (x / gx) * bn + ln;
   return tm < tiles_m && tn < tiles_n;
@@ -297,7 +302,20 @@ inline int xcd_cut(const GemmArgs &a, int BM, int BN, unsigned *grid) {
   const int gy = 8 / best;
   const int bm = (tiles_m + best - 1) / best, bn = (tiles_n + gy - 1) / gy;
   *grid = (unsigned)(8 * bm * bn);
-  return best;
+  // band height: the patch of G x (resident / G) tiles with the fewest operand rows.  From four rounds of tiles on
+  // (16896x12288x3072: 256x256 1206 -> 1162 us, 128x192 1532 -> 1187, 128x128 1545 -> 1273); launches of fewer rounds keep N
+  // fastest (4096x3456x1152, 128x128: 41 us against 46 in bands).
+  const int resident = 32 * (BM * BN >= 256 * 128 ? 1 : 2);   // workgroups an XCD runs at a time
+  int G = 1;
+  if (bm * bn >= 4 * resident) {
+    int best_rows = 1 << 30;
+    for (int g = 1; g <= bm && g <= resident; g *= 2) {
+      const int cols = resident / g < bn ? resident / g : bn;
+      const int rows = resident / cols < bm ? resident / cols : bm;
+      if (rows * BM + cols * BN < best_rows) { best_rows = rows * BM + cols * BN; G = g; }
+    }
+  }
+  return best | G << 8;
 }
 
 inline bool vec_epilogue_ok(const GemmArgs &a) {
