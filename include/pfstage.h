@@ -233,6 +233,14 @@ pf_status pf_xattn_kv_view(const pf_stage *stage, int layer, pf_kv_view_t *out);
 pf_status pf_stage_attention_plan(const pf_stage *stage, int nq, int cross, int *splits, size_t *ws_needed,
                                   size_t *ws_reserved);
 
+/* Host-only query: how a patch call (with_text != 0: with its text rows, kinds 2 and 3) runs the QKV projections of one
+ * layer.  *launches GEMM launches (kind 2 with text: two when the streams cannot share one); *fused_text / *fused_img: 1
+ * when the stream's k and v go from the GEMM epilogue into the buffers, 0 when the scatter kernel moves them (K, or the
+ * alignment of that stream's biases or norm scales, which the caller may place anywhere).  *fused_text is 0 without text
+ * rows.  Errors: PF_ERR_NULL, PF_ERR_RANGE (layer), PF_ERR_CONFIG (text rows of a kind that has none). */
+pf_status pf_stage_qkv_plan(const pf_stage *stage, int layer, int with_text, int *launches, int *fused_text,
+                            int *fused_img);
+
 /* Change the stream later work is enqueued on (e.g. a capturing stream). */
 pf_status pf_stage_set_stream(pf_stage *stage, void *hip_stream);
 

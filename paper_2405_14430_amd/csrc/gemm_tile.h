@@ -140,10 +140,6 @@ __device__ __forceinline__ void load8(const float *p, float *o) { Vec16<float>::
 __device__ __forceinline__ void store8(bf16_t *p, const float *o) { Vec16<bf16_t>::store(p, o); }
 __device__ __forceinline__ void store8(float *p, const float *o) { Vec16<float>::store(p, o); Vec16<float>::store(p + 4, o + 4); }
 
-// Which epilogue a kernel is compiled for.  Compiled for all of them the kernels are four to five times the code they run,
-// and a launch of ten microseconds feels every instruction-cache line it has to fetch.
-enum { EM_STORE = 0, EM_RESIDUAL = 1, EM_KV_ROUTE = 2, EM_STORE_ERF = 3 };   // (store: plain columns or tanh GELU)
-
 // Epilogue over a finished fp32 tile held row-major in LDS (row stride TLD floats).  PRE: residual / gate operands
 // come from `ops` (fetched earlier) when ops->on.
 template <int EM, int BM, int BN, int TLD, int NT = 256, bool PRE = false, typename T>
@@ -343,13 +339,16 @@ inline unsigned make_launch(const GemmArgs &a, const GemmArgs *b, int BM, int BN
   return total;
 }
 
-// go(number of problems, epilogue), both as integral constants
+// go(number of problems, epilogue), both as integral constants; a pair's two GEMMs have the same epilogue (gemm_pair_one_launch)
 template <typename F>
 inline hipError_t for_launch_form(const GemmArgs &a, const GemmArgs *b, F &&go) {
   auto with = [&](auto em) { return b ? go(std::integral_constant<int, 2>{}, em) : go(std::integral_constant<int, 1>{}, em); };
-  if (a.kvr.kbuf) return with(std::integral_constant<int, EM_KV_ROUTE>{});
-  if (a.epilogue != 0) return with(std::integral_constant<int, EM_RESIDUAL>{});
-  return a.gelu_tanh || a.gelu_from >= a.N ? with(std::integral_constant<int, EM_STORE>{}) : with(std::integral_constant<int, EM_STORE_ERF>{});
+  switch (gemm_epilogue_form(a)) {
+    case EM_KV_ROUTE: return with(std::integral_constant<int, EM_KV_ROUTE>{});
+    case EM_RESIDUAL: return with(std::integral_constant<int, EM_RESIDUAL>{});
+    case EM_STORE_ERF: return with(std::integral_constant<int, EM_STORE_ERF>{});
+    default: return with(std::integral_constant<int, EM_STORE>{});
+  }
 }
 
 // tiles of a launch of one or two GEMMs

@@ -80,9 +80,19 @@ struct GemmArgs {
   GemmArgsKv kvr;      // kbuf == nullptr: plain GEMM
   int tile;            // 0: the tile heuristic picks; 1 .. gemm_mfma_dl_tile_count(): that tile configuration, this launch only
 };
+// Which epilogue a direct-to-LDS kernel is compiled for.  Compiled for all of them the kernels are four to five times the code
+// they run, and a launch of ten microseconds feels every instruction-cache line it has to fetch.
+enum { EM_STORE = 0, EM_RESIDUAL = 1, EM_KV_ROUTE = 2, EM_STORE_ERF = 3 };   // (store: plain columns or tanh GELU)
+inline int gemm_epilogue_form(const GemmArgs &a) {
+  if (a.kvr.kbuf) return EM_KV_ROUTE;
+  if (a.epilogue != 0) return EM_RESIDUAL;
+  return a.gelu_tanh || a.gelu_from >= a.N ? EM_STORE : EM_STORE_ERF;
+}
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
-// two GEMMs of one type and path that do not depend on each other; one launch where N, K and the kernel family agree
+// two GEMMs of one type and path that do not depend on each other; one launch where N, K, the kernel family and the epilogue
+// the kernel is compiled for agree
 hipError_t launch_gemm_pair(const GemmArgs &a, const GemmArgs &b, hipStream_t s);
+bool gemm_pair_one_launch(const GemmArgs &a, const GemmArgs &b);   // whether launch_gemm_pair makes one launch of them
 bool gemm_kv_route_supported(const GemmArgs &a);   // the fused QKV -> K/V^T write needs an MFMA kernel's vectorised epilogue
 
 // (cos, sin) of the RoPE angles for the rows of a call: rows [0, n_text) are text (no rotation), row n_text + i is image

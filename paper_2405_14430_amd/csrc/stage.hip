@@ -332,15 +332,18 @@ struct QkvPart {
   bool rope;
 };
 
-// QKV projection of one or two streams, in one launch where they share a route.
-// q_scale != 0: q is to leave this function multiplied by it (folded into whichever fp32 step writes q; the caller only
-// asks for it when every q row of the coming attention launch goes through such a step).
-pf_status qkv_project(pf_stage *s, const QkvPart *parts, int np, char *kb, char *vb, const void *rope_tab, float q_scale) {
+// The part of a stream whose rows start at row r0 of the workspace buffers and go to buffer rows from brow0 on.
+QkvPart qkv_part(const pf_stage *s, const pf_layer_weights *lw, size_t r0, int seg, int brow0, int tok0, bool rope) {
+  const size_t row = (size_t)s->cfg.hidden * s->d.esz;
+  return QkvPart{s->ws + s->w.h + r0 * row, lw, s->ws + s->w.qkv + r0 * 3 * row, seg, 0, 0, brow0, tok0, rope};
+}
+
+// The QKV GEMMs of one or two streams; fused[i]: stream i's k and v go to the buffers from the GEMM epilogue.
+void qkv_gemms(const pf_stage *s, const QkvPart *parts, int np, char *kb, char *vb, const void *rope_tab, float q_scale,
+               GemmArgs *g, bool *fused) {
   const pf_config &c = s->cfg;
   const Derived &d = s->d;
   const int D = c.hidden;
-  GemmArgs g[2];
-  bool fused[2];
   for (int i = 0; i < np; ++i) {
     const QkvPart &p = parts[i];
     GemmArgsKv kvr{kb, vb, d.Lp, c.head_dim, D, p.split, p.row0a, p.row0b, p.rope ? rope_tab : nullptr, d.B > 1 ? p.seg : 0,
@@ -350,6 +353,18 @@ pf_status qkv_project(pf_stage *s, const QkvPart *parts, int np, char *kb, char 
     g[i] = gemm_args(s, p.hs, D, p.lw->w_qkv, D, p.lw->b_qkv, p.qs, 3 * D, p.seg * d.B, 3 * D, D, 0, 3 * D, nullptr, nullptr, 0,
                      nullptr, 0, fused[i] ? &kvr : nullptr);
   }
+}
+
+// QKV projection of one or two streams, in one launch where they share a route (gemm_pair_one_launch).
+// q_scale != 0: q is to leave this function multiplied by it (folded into whichever fp32 step writes q; the caller only
+// asks for it when every q row of the coming attention launch goes through such a step).
+pf_status qkv_project(pf_stage *s, const QkvPart *parts, int np, char *kb, char *vb, const void *rope_tab, float q_scale) {
+  const pf_config &c = s->cfg;
+  const Derived &d = s->d;
+  const int D = c.hidden;
+  GemmArgs g[2];
+  bool fused[2];
+  qkv_gemms(s, parts, np, kb, vb, rope_tab, q_scale, g, fused);
   PF_TRY(gemm(s, PF_KC_GEMM_QKV, g, np));
   hipStream_t st = s->stream;
   for (int i = 0; i < np; ++i) {
@@ -550,7 +565,7 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
     for (int si = 0; si < ns; ++si) {
       const Stream &sm = streams[si];
       const bool rot = d.rope && sm.lw == &s->img[l];   // image stream of a rotating two-stream block
-      parts[si] = QkvPart{h + sm.r0 * D * e, sm.lw, qkv + sm.r0 * 3 * D * e, sm.seg, 0, 0, sm.brow0, rot ? img_off : -1, rot};
+      parts[si] = qkv_part(s, sm.lw, sm.r0, sm.seg, sm.brow0, rot ? img_off : -1, rot);
       q_pre = q_pre && qkv_route(s, parts[si].hs, *sm.lw, parts[si].qs, rot) != ROUTE_SCATTER_PLAIN;
     }
     PF_TRY(ln(streams, ns, false));
@@ -749,6 +764,26 @@ pf_status pf_stage_attention_plan(const pf_stage *s, int nq, int cross, int *spl
   *splits = plan_splits(s, nq, cross ? s->d.T : s->d.Lkv);
   *ws_needed = attention_ws_bytes(nq, s->cfg.n_heads * s->d.B, s->cfg.head_dim, *splits);
   *ws_reserved = s->w.attn_bytes;
+  return PF_OK;
+}
+
+pf_status pf_stage_qkv_plan(const pf_stage *s, int layer, int with_text, int *launches, int *fused_text, int *fused_img) {
+  if (!s || !launches || !fused_text || !fused_img) return PF_ERR_NULL;
+  if (layer < 0 || layer >= s->cfg.n_layers) return PF_ERR_RANGE;
+  if (with_text && !s->d.Tj) return PF_ERR_CONFIG;
+  const Derived &d = s->d;
+  const int Tt = with_text ? d.Tj : 0;
+  const bool two = Tt && s->cfg.kind == PF_BLOCK_MMDIT_JOINT, single = s->cfg.kind == PF_BLOCK_SINGLE_STREAM;
+  QkvPart parts[2];
+  int np = 0;
+  if (two) parts[np++] = qkv_part(s, &s->txt[layer], 0, Tt, 0, -1, false);
+  parts[np++] = qkv_part(s, &s->img[layer], two ? (size_t)d.B * Tt : 0, d.n + (single ? Tt : 0), d.Tj, 0, d.rope || single);
+  GemmArgs g[2];
+  bool fused[2];
+  qkv_gemms(s, parts, np, s->kptr(layer), s->vptr(layer), s->ws + s->w.rope, 0.f, g, fused);
+  *fused_img = fused[np - 1];
+  *fused_text = two ? fused[0] : (Tt ? fused[0] : 0);
+  *launches = np == 2 && !gemm_pair_one_launch(g[0], g[1]) ? 2 : 1;
   return PF_OK;
 }
 
@@ -1027,11 +1062,15 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s) {
   if (a.dt == DT_F32) return gemm_mfma_f32_supported(a) ? launch_gemm_mfma_f32(a, s) : launch_gemm_simt(a, s);
   return gemm_mfma_dl_supported(a) ? launch_gemm_mfma_dl(a, s) : launch_gemm_mfma(a, s);
 }
+// The kernels are compiled for one epilogue and the tile rule looks at the first GEMM's head size and norm, so both have to
+// agree on these.  They need not: a stream whose biases or norm scales are not 16-byte aligned takes no K/V route.
+bool gemm_pair_one_launch(const GemmArgs &a, const GemmArgs &b) {
+  if (a.path == PATH_SIMT || b.path == PATH_SIMT || a.N != b.N || a.K != b.K || a.dt != b.dt || a.tile != b.tile) return false;
+  if (gemm_epilogue_form(a) != gemm_epilogue_form(b) || !a.kvr.q_norm != !b.kvr.q_norm || a.kvr.dh != b.kvr.dh) return false;
+  return a.dt == DT_F32 ? gemm_mfma_f32_supported(a) && gemm_mfma_f32_supported(b) : gemm_mfma_dl_supported(a) && gemm_mfma_dl_supported(b);
+}
 hipError_t launch_gemm_pair(const GemmArgs &a, const GemmArgs &b, hipStream_t s) {
-  if (a.path != PATH_SIMT && a.N == b.N && a.K == b.K && a.dt == b.dt) {
-    if (a.dt == DT_F32 && gemm_mfma_f32_supported(a) && gemm_mfma_f32_supported(b)) return launch_gemm_mfma_f32(a, s, &b);
-    if (a.dt == DT_BF16 && gemm_mfma_dl_supported(a) && gemm_mfma_dl_supported(b)) return launch_gemm_mfma_dl(a, s, &b);
-  }
+  if (gemm_pair_one_launch(a, b)) return a.dt == DT_F32 ? launch_gemm_mfma_f32(a, s, &b) : launch_gemm_mfma_dl(a, s, &b);
   if (hipError_t e = launch_gemm(a, s); e != hipSuccess) return e;
   return launch_gemm(b, s);
 }
