@@ -420,7 +420,9 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
   // Residual rows.  The single-stream kind runs text and image rows through one weight set, so with text they are gathered
   // in the workspace.  Otherwise nothing is copied: the first layer reads the caller's rows, the first residual GEMM of a
   // stream writes into its output (or the workspace when the caller wants none) and everything after that runs in place.
-  // (With text, rows of a caller that are not 16-byte aligned are gathered too: the copy takes any address.)
+  // (With text, rows of a caller that are not 16-byte aligned are gathered too: the copy takes any address.  And so are rows
+  // whose outputs lie over the inputs in any other way than y over x and text_out over text: in place, one workgroup's output
+  // would overwrite what another has yet to read.)
   float *xbuf = xres;          // where updated image rows live
   const float *xsrc = xres;    // where the current image rows are read from (x_img until the first update)
   float *tbuf = xres;          // the same of the MMDiT kind's text rows
@@ -430,10 +432,15 @@ pf_status forward(pf_stage *s, const float *x_img, int n_img, int img_off, const
   const size_t t_pitch = single ? (size_t)R : (size_t)Tt, i_pitch = single ? (size_t)R : (size_t)n_img;
   // The single-stream kind needs no gather either when the first norm and the first and last down projections, which touch
   // the caller's rows, can treat text and image rows as two sets in one launch without an extra row of tiles (four copies of
-  // 7 - 45 us a call at Flux scale): with one image whose text rows end a 256-row tile.
+  // 7 - 45 us a call at Flux scale): with one image, where the two sets have no more 256-row tiles than all rows together.
   const bool aligned = (((uintptr_t)text | (uintptr_t)text_out | (uintptr_t)x_img | (uintptr_t)y_img) & 15) == 0;
-  const bool two_sets = single && Tt && aligned && B == 1 && (Tt + 255) / 256 + (n_img + 255) / 256 == (R + 255) / 256;
-  const bool gather = Tt && !two_sets && (single || !aligned);
+  auto apart = [&](const float *out, int out_rows, const float *in, int in_rows) {
+    return !out || !in || out + (size_t)B * out_rows * D <= in || in + (size_t)B * in_rows * D <= out;
+  };
+  const bool in_place = aligned && (y_img == x_img || apart(y_img, n_img, x_img, n_img)) && apart(y_img, n_img, text, Tt) &&
+                        (text_out == text || apart(text_out, Tt, text, Tt)) && apart(text_out, Tt, x_img, n_img);
+  const bool two_sets = single && Tt && in_place && B == 1 && (Tt + 255) / 256 + (n_img + 255) / 256 == (R + 255) / 256;
+  const bool gather = Tt && !two_sets && (single || !in_place);
   if (two_sets) {
     xsrc = x_img;                                   // rows of the first layer; xres holds text and image rows in between
   } else if (gather) {
