@@ -94,19 +94,22 @@ int use_path(const pf_config *c) { return c->kernel_path == PF_PATH_AUTO ? PATH_
 // so a split is worth its combine pass from two tiles on (64 queries x 6 heads over 256 keys: 4 splits of 2 tiles).
 int choose_splits(int path, int dt, int nq, int H, int kv_rows, int head_dim) {
   const bool f32 = dt == PF_F32, simt = path == PATH_SIMT || f32;
+  const bool mfma_f32 = f32 && path != PATH_SIMT && attn_mfma_f32_head_size(head_dim);
   const bool gen2 = !simt && pf::g_attn_variant == 0 && (head_dim == 64 || head_dim == 72 || head_dim == 128);
   const int qtile = simt ? 64 : (gen2 ? attn_mfma2_qtile(nq) : 128);
-  // workgroups the chip holds at a time (fp32, head sizes up to 72: three per CU; 512 queries x 16 heads x 4096 keys 134 ->
+  // workgroups the chip holds at a time (fp32 MFMA, head sizes up to 72: three per CU; 512 queries x 16 heads x 4096 keys 134 ->
   // 122 us with 6 splits instead of 4)
-  const int resident = qtile == 256 ? 256 : (f32 && path != PATH_SIMT && head_dim <= 72 ? 768 : 512);
+  const int resident = qtile == 256 ? 256 : (mfma_f32 && head_dim <= 72 ? 768 : 512);
   // the combine pass: a launch, and the partial rows written and read at memory speed (about 7 MB in the time of a tile;
-  // 2560 queries x 24 heads of 128, one split instead of two: 429 + 16 -> 426 us)
+  // 2560 queries x 24 heads of 128, one split instead of two: 429 + 16 -> 426 us).  The kernels of other head sizes and the
+  // plain ones keep the half tile per split they were measured with: their tiles take many times as long (fp32, 1024 queries x
+  // 24 heads of 48 on the plain kernel, two layers: 3901 us with 4 splits, 5321 with 2).
   const double row_units = (double)nq * H * head_dim * (f32 ? 2.0 : 1.0) * 1.43e-7;
   const int ktile = simt ? 32 : 64;
   const int64_t blocks = (int64_t)((nq + qtile - 1) / qtile) * H;
   const int tiles = (kv_rows + ktile - 1) / ktile;
   // at least four tiles per split (fp32 MFMA: two)
-  int cap = f32 && path != PATH_SIMT && attn_mfma_f32_head_size(head_dim) ? tiles / 2 : tiles / 4;
+  int cap = mfma_f32 ? tiles / 2 : tiles / 4;
   if (cap > 16) cap = 16;
   if (g_force_splits > 0) return g_force_splits < (cap < 1 ? 1 : cap) ? g_force_splits : (cap < 1 ? 1 : cap);
   int best = 1;
@@ -116,7 +119,7 @@ int choose_splits(int path, int dt, int nq, int H, int kv_rows, int head_dim) {
     const int64_t rounds = (wgs + resident - 1) / resident;
     const double fill = wgs >= resident ? 1.0 : (double)wgs / resident;
     double cost = (double)rounds * ((tiles + sp - 1) / sp + 4) * (1.0 + 0.5 * (1.0 - fill));
-    if (sp > 1) cost += 2.0 + (4 * sp + 2) * row_units;
+    if (sp > 1) cost += 2.0 + (gen2 || mfma_f32 ? (4 * sp + 2) * row_units : 0.5 * sp);
     if (cost < best_cost - 1e-9) { best_cost = cost; best = sp; }
   }
   return best;
