@@ -303,8 +303,11 @@ pf_status pf_op_axpy(const float *x, const float *y, float alpha, float *out, in
  * coefficient on x_t (deterministic DDIM-type rules).  Same argument rules as pf_op_axpy. */
 pf_status pf_op_axpby(const float *x, const float *y, float a, float b, float *out, int64_t n, void *stream);
 
-/* Kernel and tile configuration the library's tile heuristic runs for a GEMM of this shape with dense, aligned operands
- * (static string; a rocprofv3 kernel trace shows the instance with its number of problems and epilogue in front).  Used by the benchmark to group GEMM launches by kernel. */
+/* Kernel and tile configuration the library's tile heuristic runs for one GEMM of this shape with dense, aligned operands
+ * (static string; a rocprofv3 kernel trace shows the instance with its number of problems and epilogue in front).  A stage's
+ * launches can differ from it in two places: a two-stream launch is chosen by the tiles of both streams, and a QKV projection
+ * that normalises heads of 128 channels needs tiles of 128 or 256 columns.  Used by the benchmark to group GEMM launches by
+ * kernel. */
 const char *pf_gemm_kernel_name(int dtype, int path, int M, int N, int K);
 /* Likewise for an attention launch of nq query rows per image (q_prescaled: the stage's self-attention, whose queries
  * carry the softmax factor; 0: plain queries).  The string is per-thread storage, valid until the next call. */
@@ -368,7 +371,7 @@ pf_status pf_probe_mfma_loop(float *out, int workgroups, int iters, double *flop
 
 /* pf_op_gemm with the tile configuration of the bf16 MFMA kernel chosen by the caller for this one launch: tile = 0 lets
  * the library's heuristic pick (then it is pf_op_gemm), 1 .. pf_gemm_tile_count() pins one of the configurations the
- * heuristic chooses from (the unit tests run every one of them on ragged shapes).  Nothing outlives the call.  tile > 0
+ * heuristic chooses from or 64x64 with three stages (the unit tests run every one of them on ragged shapes).  Nothing outlives the call.  tile > 0
  * needs dtype PF_BF16, path PF_PATH_AUTO and K a multiple of 64 (PF_ERR_SHAPE otherwise); tile out of range: PF_ERR_RANGE. */
 int pf_gemm_tile_count(void);
 pf_status pf_op_gemm_tile(int tile, int dtype, int path, const void *A, int64_t lda, const void *W, int64_t ldw,

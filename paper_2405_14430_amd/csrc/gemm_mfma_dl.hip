@@ -16,8 +16,6 @@
 //    chain of K iterations by four; the four partial tiles are then summed through LDS.
 // Both finish through LDS: the fp32 tile is laid out row-major and every thread applies the epilogue to runs of 8
 // consecutive columns (16-byte bf16 stores, 32-byte fp32 stores).
-#include <mutex>
-
 #include "gemm_tile.h"
 
 namespace pf {
@@ -30,7 +28,7 @@ constexpr int ROW_BYTES = BK * 2;  // 128
 // ------------------------------------------------------------------------------------------------------------------
 // WGM x WGN wavefronts on one shared tile
 // ------------------------------------------------------------------------------------------------------------------
-template <int NP, int EM, int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, int KB = 64, bool SPREAD_LOADS = false>
+template <int NP, int EM, int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, bool SPREAD_LOADS = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf16_t, NP> L) {
   const bool second = NP == 2 && blockIdx.x >= L.grid0;
   const GemmProblem<bf16_t> &prob = L.p[second ? 1 : 0];
@@ -42,14 +40,12 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
   constexpr int NW = WGM * WGN;
   constexpr int WM = BM / WGM, WN = BN / WGN;
   constexpr int MI = WM / 32, NI = WN / 32;
-  // KB = K elements per stage: 64 (128-byte tile rows, 8 rows per load instruction, swizzle key (r>>1)&7) or
-  // 32 (64-byte rows, 16 rows per instruction, key (r>>2)&3: sixteen consecutive rows then cover all 64 banks)
-  constexpr int RBY = KB * 2, RPI = 1024 / RBY, CPR = KB / 8;
+  constexpr int RPI = 1024 / ROW_BYTES, CPR = BK / 8;    // rows per load instruction, 16-byte chunks per row
   constexpr int LA = BM / RPI / NW, LW = BN / RPI / NW;  // load instructions per wave per stage
   static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile rows must split evenly over the waves' load instructions");
   constexpr int LPS = LA + LW;
-  constexpr int STAGE_BYTES = (BM + BN) * RBY;
-  auto key = [](int r) { return KB == 64 ? ((r >> 1) & 7) : ((r >> 2) & 3); };
+  constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
+  auto key = [](int r) { return (r >> 1) & 7; };
   constexpr int TLD = BN + 4;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
@@ -76,11 +72,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
     int c = (lane % CPR) ^ key(r);
     pw[i] = (unsigned)(((size_t)min(r, N - 1 - n0) * ldw + c * 8) * 2);
   }
-  const int nk = K / KB;
+  const int nk = K / BK;
   auto issue = [&](int stage, int kt) {
     unsigned char *sa = smem + stage * STAGE_BYTES;
-    unsigned char *sw = sa + BM * RBY;
-    const unsigned koff = (unsigned)kt * (KB * 2);
+    unsigned char *sw = sa + BM * ROW_BYTES;
+    const unsigned koff = (unsigned)kt * (BK * 2);
 #pragma unroll
     for (int i = 0; i < LA; ++i) srcA.load16(pa[i], koff, sa + (i * NW + wave) * 1024);
 #pragma unroll
@@ -90,9 +86,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
   auto issue_one = [&](auto idx_c, int stage, int kt) __attribute__((always_inline)) {
     constexpr int idx = decltype(idx_c)::value;
     unsigned char *sa = smem + stage * STAGE_BYTES;
-    const unsigned koff = (unsigned)kt * (KB * 2);
+    const unsigned koff = (unsigned)kt * (BK * 2);
     if constexpr (idx < LA) srcA.load16(pa[idx], koff, sa + (idx * NW + wave) * 1024);
-    else srcW.load16(pw[idx - LA], koff, sa + BM * RBY + ((idx - LA) * NW + wave) * 1024);
+    else srcW.load16(pw[idx - LA], koff, sa + BM * ROW_BYTES + ((idx - LA) * NW + wave) * 1024);
   };
 
   // small tiles: the epilogue's residual / gate operands are requested first, ahead of every tile load
@@ -117,13 +113,13 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     int r = wm * WM + i * 32 + l32;
-    arow[i] = r * RBY;
+    arow[i] = r * ROW_BYTES;
     akey[i] = key(r);
   }
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
     int r = wn * WN + j * 32 + l32;
-    wrow[j] = BM * RBY + r * RBY;
+    wrow[j] = BM * ROW_BYTES + r * ROW_BYTES;
     wkey[j] = key(r);
   }
 
@@ -132,7 +128,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
   // then stalls at its own load instructions before it can start on its MFMAs).  Every iteration issues the same LPS
   // loads - past the last K tile it repeats the last tile into the stage that has just been freed - so the loop body has
   // no branch around a load and the wait in front of tile kt is the same for every kt.
-  constexpr int KS = KB / 16;
+  constexpr int KS = BK / 16;
   constexpr bool SPREAD = SPREAD_LOADS && MI * NI * KS >= 2 * LPS;
   const int prologue_tiles = min(NSTAGE - 1, nk);
   for (int kt = 0; kt < nk; ++kt) {
@@ -357,19 +353,24 @@ bool gemm_tile_map(int M, int N, int BM, int BN, unsigned id, unsigned *grid, in
 
 namespace {
 
-template <int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, int KB = 64, bool SPREAD = false>
+// PINNED: a configuration that only pf_op_gemm_tile asks for (one problem, no K/V route)
+template <int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, bool SPREAD = false, bool PINNED = false>
 hipError_t launch_tile(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   // the stage ring, or the fp32 tile (row stride BN + 4) that replaces it for the epilogue, whichever is larger
-  constexpr int ring = NSTAGE * (BM + BN) * KB * 2, tile = BM * (BN + 4) * 4;
+  constexpr int ring = NSTAGE * (BM + BN) * ROW_BYTES, tile = BM * (BN + 4) * 4;
   constexpr int smem = (tile > ring && tile <= 96 * 1024) ? tile : ring;   // larger tiles finish in row passes
   auto go = [&](auto np, auto em) -> hipError_t {
     constexpr int NP = decltype(np)::value, EM = decltype(em)::value;
-    constexpr auto kernel = &gemm_tile_kernel<NP, EM, BM, BN, NSTAGE, WGM, WGN, KB, SPREAD>;
-    if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
-    GemmLaunch<bf16_t, NP> L;
-    const unsigned grid = make_launch(a, b, BM, BN, &L);
-    kernel<<<grid, 64 * WGM * WGN, smem, s>>>(L);
-    return hipGetLastError();
+    if constexpr (PINNED && (NP == 2 || EM == EM_KV_ROUTE)) {
+      return hipErrorInvalidValue;
+    } else {
+      constexpr auto kernel = &gemm_tile_kernel<NP, EM, BM, BN, NSTAGE, WGM, WGN, SPREAD>;
+      if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
+      GemmLaunch<bf16_t, NP> L;
+      const unsigned grid = make_launch(a, b, BM, BN, &L);
+      kernel<<<grid, 64 * WGM * WGN, smem, s>>>(L);
+      return hipGetLastError();
+    }
   };
   return for_launch_form(a, b, go);
 }
@@ -437,8 +438,9 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 //    of 64x64 tiles or K is long enough to pay for it: 1024x3456x1152 16.9 -> 15.2 us, 512x6144x1536 22.8 -> 22.0,
 //    512x4608x1536 20.3 -> 18.7 against two-stage 64x64 tiles, which take what is left (512x4608x1152 inside a stage: 15.8
 //    us, with 64x128 17.3).
-enum { V_256x256 = 0, V_256x128_K32S3, V_256x128_S3, V_128x128, V_128x64, V_WAVEK, V_64x64_S4, V_64x64_S3, V_64x64_S2,
-       V_128x192_S2, V_256x192_S2, V_128x192_S3, V_64x128_S3, V_COUNT };
+// 64x64 with three stages is there for pf_op_gemm_tile only: the rule never takes it.
+enum { V_256x256 = 0, V_64x128_S3, V_256x128_S3, V_128x128, V_128x64, V_WAVEK, V_64x64_S4, V_64x64_S3, V_64x64_S2,
+       V_128x192_S2, V_256x192_S2, V_128x192_S3, V_COUNT };
 
 static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
   auto tiles = [&](int bm, int bn) { return launch_tiles(a, b, bm, bn); };
@@ -472,23 +474,22 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
 static hipError_t launch_variant(int v, const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   switch (v) {
     case V_256x256: return launch_tile<256, 256, 2, 4, 2>(a, b, s);
-    case V_256x128_K32S3: return launch_tile<256, 128, 3, 4, 2, 32>(a, b, s);
+    case V_64x128_S3: return launch_tile<64, 128, 3>(a, b, s);
     case V_256x128_S3: return launch_tile<256, 128, 3, 4, 2>(a, b, s);
     case V_128x128: return launch_tile<128, 128, 2>(a, b, s);
     case V_128x64: return launch_tile<128, 64, 2>(a, b, s);
     case V_WAVEK: return launch_wavek<64, 64>(a, b, s);
     case V_64x64_S4: return launch_tile<64, 64, 4>(a, b, s);
-    case V_64x64_S3: return launch_tile<64, 64, 3>(a, b, s);
+    case V_64x64_S3: return launch_tile<64, 64, 3, 2, 2, false, true>(a, b, s);
     case V_128x192_S2: return launch_tile<128, 192, 2>(a, b, s);
     case V_256x192_S2: return launch_tile<256, 192, 2, 4, 2>(a, b, s);
-    case V_64x128_S3: return launch_tile<64, 128, 3>(a, b, s);
-    case V_128x192_S3: return launch_tile<128, 192, 3, 2, 2, 64, true>(a, b, s);
+    case V_128x192_S3: return launch_tile<128, 192, 3, 2, 2, true>(a, b, s);
     default: return launch_tile<64, 64, 2>(a, b, s);
   }
 }
 
-// configurations a caller can pin: all but the last, which the rule alone takes
-int gemm_mfma_dl_tile_count() { return V_64x128_S3; }
+// configurations a caller can pin
+int gemm_mfma_dl_tile_count() { return V_COUNT; }
 
 hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s, const GemmArgs *b) {
 #ifdef PF_TUNING
@@ -507,37 +508,23 @@ hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s, const GemmArgs 
     case 15: return launch_tile<256, 256, 2, 4, 2>(a, b, s);
     case 16: return launch_tile<128, 256, 3, 2, 4>(a, b, s);
     case 17: return launch_tile<256, 128, 2, 4, 2>(a, b, s);
-    case 22: return launch_tile<256, 128, 3, 4, 2, 32>(a, b, s);
-    case 26: return launch_tile<64, 64, 3>(a, b, s);
     case 27: return launch_tile<128, 64, 3>(a, b, s);
     case 28: return launch_tile<128, 192, 2>(a, b, s);
     case 29: return launch_tile<256, 192, 2, 4, 2>(a, b, s);
     case 30: return launch_tile<128, 192, 3>(a, b, s);
-    case 40: return launch_tile<128, 192, 2, 2, 2, 64, true>(a, b, s);
-    case 41: return launch_tile<256, 192, 2, 4, 2, 64, true>(a, b, s);
-    case 42: return launch_tile<128, 192, 3, 2, 2, 64, true>(a, b, s);
-    case 43: return launch_tile<256, 256, 2, 4, 2, 64, true>(a, b, s);
-    case 44: return launch_tile<256, 128, 3, 4, 2, 64, true>(a, b, s);
-    case 45: return launch_tile<128, 128, 2, 2, 2, 64, true>(a, b, s);
-    case 46: return launch_tile<128, 192, 4, 2, 2, 64, true>(a, b, s);
-    case 47: return launch_tile<128, 128, 3, 2, 2, 64, true>(a, b, s);
-    case 48: return launch_tile<128, 128, 4, 2, 2, 64, true>(a, b, s);
-    case 49: return launch_tile<128, 64, 4, 2, 2, 64, true>(a, b, s);
-    case 50: return launch_tile<64, 64, 4, 2, 2, 64, true>(a, b, s);
-    case 51: return launch_tile<128, 256, 3, 2, 2, 64, true>(a, b, s);
-    case 70: return launch_tile<128, 64, 6, 4, 1>(a, b, s);
-    case 71: return launch_tile<128, 96, 5, 4, 1>(a, b, s);
-    case 72: return launch_tile<128, 128, 4, 2, 2>(a, b, s);
-    case 73: return launch_tile<128, 128, 4, 4, 2>(a, b, s);
-    case 74: return launch_tile<64, 64, 8, 2, 2>(a, b, s);
-    case 75: return launch_tile<64, 64, 5, 2, 2>(a, b, s);
-    case 76: return launch_tile<64, 128, 6, 2, 2>(a, b, s);
-    case 77: return launch_tile<128, 64, 6, 2, 2>(a, b, s);
-    case 78: return launch_tile<128, 64, 6, 4, 2>(a, b, s);
-    case 79: return launch_tile<64, 128, 3, 2, 2>(a, b, s);
-    case 80: return launch_tile<64, 64, 9, 2, 2>(a, b, s);
-    case 81: return launch_tile<96, 128, 5, 1, 4>(a, b, s);
-    case 52: return launch_tile<128, 192, 3, 2, 2, 64, false>(a, b, s);
+    case 40: return launch_tile<128, 192, 2, 2, 2, true>(a, b, s);
+    case 41: return launch_tile<256, 192, 2, 4, 2, true>(a, b, s);
+    case 42: return launch_tile<128, 192, 3, 2, 2, true>(a, b, s);
+    case 43: return launch_tile<256, 256, 2, 4, 2, true>(a, b, s);
+    case 44: return launch_tile<256, 128, 3, 4, 2, true>(a, b, s);
+    case 45: return launch_tile<128, 128, 2, 2, 2, true>(a, b, s);
+    case 46: return launch_tile<128, 192, 4, 2, 2, true>(a, b, s);
+    case 47: return launch_tile<128, 128, 3, 2, 2, true>(a, b, s);
+    case 48: return launch_tile<128, 128, 4, 2, 2, true>(a, b, s);
+    case 49: return launch_tile<128, 64, 4, 2, 2, true>(a, b, s);
+    case 50: return launch_tile<64, 64, 4, 2, 2, true>(a, b, s);
+    case 51: return launch_tile<128, 256, 3, 2, 2, true>(a, b, s);
+    case 52: return launch_tile<128, 192, 3, 2, 2, false>(a, b, s);
     default: break;
   }
 #endif
@@ -546,13 +533,12 @@ hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s, const GemmArgs 
 }
 
 const char *gemm_mfma_dl_variant_name(const GemmArgs &a) {
-  static const char *names[V_COUNT] = {"gemm_tile_kernel<256,256,2,4,2,64,false>", "gemm_tile_kernel<256,128,3,4,2,32,false>",
-                                       "gemm_tile_kernel<256,128,3,4,2,64,false>", "gemm_tile_kernel<128,128,2,2,2,64,false>",
-                                       "gemm_tile_kernel<128,64,2,2,2,64,false>", "gemm_wavek_kernel<64,64>",
-                                       "gemm_tile_kernel<64,64,4,2,2,64,false>", "gemm_tile_kernel<64,64,3,2,2,64,false>",
-                                       "gemm_tile_kernel<64,64,2,2,2,64,false>", "gemm_tile_kernel<128,192,2,2,2,64,false>",
-                                       "gemm_tile_kernel<256,192,2,4,2,64,false>", "gemm_tile_kernel<128,192,3,2,2,64,true>",
-                                       "gemm_tile_kernel<64,128,3,2,2,64,false>"};
+  static const char *names[V_COUNT] = {"gemm_tile_kernel<256,256,2,4,2,false>", "gemm_tile_kernel<64,128,3,2,2,false>",
+                                       "gemm_tile_kernel<256,128,3,4,2,false>", "gemm_tile_kernel<128,128,2,2,2,false>",
+                                       "gemm_tile_kernel<128,64,2,2,2,false>", "gemm_wavek_kernel<64,64>",
+                                       "gemm_tile_kernel<64,64,4,2,2,false>", "gemm_tile_kernel<64,64,3,2,2,false>",
+                                       "gemm_tile_kernel<64,64,2,2,2,false>", "gemm_tile_kernel<128,192,2,2,2,false>",
+                                       "gemm_tile_kernel<256,192,2,4,2,false>", "gemm_tile_kernel<128,192,3,2,2,true>"};
   return names[(a.tile >= 1 && a.tile <= gemm_mfma_dl_tile_count()) ? a.tile - 1 : pick_variant(a)];
 }
 
