@@ -303,11 +303,11 @@ pf_status pf_op_axpy(const float *x, const float *y, float alpha, float *out, in
  * coefficient on x_t (deterministic DDIM-type rules).  Same argument rules as pf_op_axpy. */
 pf_status pf_op_axpby(const float *x, const float *y, float a, float b, float *out, int64_t n, void *stream);
 
-/* Kernel and tile configuration the library's tile heuristic runs for one GEMM of this shape with dense, aligned operands
- * (static string; a rocprofv3 kernel trace shows the instance with its number of problems and epilogue in front).  A stage's
- * launches can differ from it in two places: a two-stream launch is chosen by the tiles of both streams, and a QKV projection
- * that normalises heads of 128 channels needs tiles of 128 or 256 columns.  Used by the benchmark to group GEMM launches by
- * kernel. */
+/* Kernel and tile configuration the library's tile heuristic runs for one GEMM of this shape with dense, aligned operands and
+ * a plain store (static string; a rocprofv3 kernel trace shows the instance with its number of problems and epilogue in
+ * front).  A stage's launch can take another tile: its epilogue (GELU, residual, K/V route) weighs differently on small and
+ * large tiles, a two-stream launch is chosen by the tiles of both streams, and a QKV projection that normalises heads of 128
+ * channels needs tiles of 128 or 256 columns.  Used by the benchmark to group GEMM launches by kernel. */
 const char *pf_gemm_kernel_name(int dtype, int path, int M, int N, int K);
 /* Likewise for an attention launch of nq query rows per image (q_prescaled: the stage's self-attention, whose queries
  * carry the softmax factor; 0: plain queries).  The string is per-thread storage, valid until the next call. */

@@ -411,23 +411,31 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 // Tile choice.
 //
 // Launches with enough tiles to fill the chip (512 of 128x64, or long K and 128 of 256x128): the candidate with the least
-//   rounds x tile area / rate x (K tiles + fill) / K tiles
-// rounds = ceil(tiles / 256 CUs); rate = what a CU does on the tile in steady state, relative to 128x192 (1.0 PFLOP/s on
-// the chip); fill = K tiles' worth of time that the start and the epilogue of a workgroup cost, 2 when a second workgroup of
-// the CU covers them, 9 for tiles that
-// fill a CU by themselves, 14 for those of the two-workgroup kernels that find no second one.  Measured (us, isolated GEMMs with cold weights; 256x256 | 256x192 | 256x128 |
-// 128x192 | 128x128, * = chosen; the rule before took three-stage 256x128 tiles with 32-wide K tiles from 512 of them on):
-//    2560 x  9216 x  3072   164 | 152* | 155 | 145 | 158    (198 before)
-//    2560 x 12288 x  3072   184* | 233 | 218 | 203 | 221    (272 before)
-//    2560 x  3072 x 15360   374 | 339 | 235* | 301 | 257
-//   16896 x  9216 x  3072   852* | 903 | 972 | 1032 | 1088
-//   16896 x  3072 x 15360  1562* | 1728 | 1662 | 1646 | 1696 (2140 before)
-//    4096 x  4608 x  1152    86 | 68 | 74 | 61* | 71, 128x64 63
-//    4096 x  1152 x  4608   116 | 106 | 70 | 61* | 72, 128x64 70
-//    4096 x  3456 x  1152    38 | 52 | 41 | 46 | 41*, 128x64 48
-// 128x192 takes three stages and issues its prefetch loads one at a time between the MFMAs (instead of in a burst behind the
-// barrier) for long K with at most one tile per CU: 2048x3072x15360 204 -> 183 us, 4096x1152x4608 65 -> 55 us; every other
-// tile loses by it or keeps nothing of the gain inside a stage.
+//   rounds x (us x (K tiles + fill) + epilogue)
+// rounds = padded grid / 256 CUs.  The grid counts, not the tiles: an XCD's block of the tile grid is padded to whole rows and
+// columns, and 52 x 9 tiles of 64x128 cut into blocks of 13 x 5 take one more round than fits on every XCD (3306x1152x4608: 85 us
+// against 65).  us, fill (the start-up, in K tiles) and the epilogues' us are fitted to isolated GEMMs with cold weights, the K/V
+// route's to QKV launches inside stages: 290 shapes of 64 .. 16384 rows at widths of 384 .. 3072, each with every tile.  us1 and
+// fill1 hold where one workgroup has a CU to itself; an epilogue weighs most where no second one runs beside it.  Over these
+// shapes the choice is 0.9 % (K/V route: 1.4 %) off the fastest tile on average, 18 % at most.  Measured (us; * = chosen):
+//                                  256x256  256x192  256x128  128x192 3-stage  128x128   128x64   64x128
+//    2048 x  9216 x  3072 store         152      129      139     118*      120      132      153      167
+//    2048 x 12288 x  3072 GELU          167     150*      160      154      175      154      196      207
+//    2048 x  3072 x 15360 residual      347      317      215      238     191*      220      249      296
+//    2560 x  9216 x  3072 store         156     140*      150      145      159      146      193      204
+//    2560 x 12288 x  3072 GELU         179*      204      205      192      218      197      247      258
+//    2560 x  3072 x 15360 residual      352      318     238*      279      320      241      364      340
+//   16896 x  9216 x  3072 store        850*      916      967      881      989      944     1178     1215
+//   16896 x 12288 x  3072 GELU        1168*     1264     1346     1212     1413     1298     1572     1663
+//   16896 x  3072 x 15360 residual     1599     1750     1692    1573*     1681     1720     2074     2216
+//    4096 x  3456 x  1152 store       38.5*     52.3     43.3     46.3     54.1     41.1     48.5     51.9
+//    4096 x  4608 x  1152 GELU         78.7     66.8     71.1    61.4*     71.9     65.9     65.4     74.9
+//    4096 x  1152 x  4608 residual      114      104     68.3     79.2    61.2*     69.7     69.8     87.0
+//    4096 x  1152 x  1152 residual     42.5     33.3     26.4     26.8     24.6     24.5    23.4*     28.8
+//    2882 x  2048 x 10240 residual      224      181     142*      187      202      145      161      196
+// The three-stage 128x192 tile issues its prefetch loads one at a time between the MFMAs (instead of in a burst behind the
+// barrier): 2048x3072x15360 204 -> 183 us, 4096x1152x4608 65 -> 55 us; every other tile loses by it or keeps nothing of the
+// gain inside a stage.
 //
 // Fewer tiles (patches of a few hundred rows), by counts of 64x64 tiles:
 //  * the wave-split-K kernel, one workgroup per CU (128 KB of LDS): up to one tile per CU, from K = 1024 on.  512x1152x1152
@@ -444,31 +452,39 @@ enum { V_256x256 = 0, V_64x128_S3, V_256x128_S3, V_128x128, V_128x64, V_WAVEK, V
 
 static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
   auto tiles = [&](int bm, int bn) { return launch_tiles(a, b, bm, bn); };
+  auto grid = [&](int bm, int bn) -> int64_t {
+    unsigned ga = 0, gb = 0;
+    xcd_cut(a, bm, bn, &ga);
+    if (b) xcd_cut(*b, bm, bn, &gb);
+    return (int64_t)ga + gb;
+  };
   // per-head norm in the epilogue: heads of 128 channels need tiles of 128 or 256 columns
   const bool wide_heads = a.kvr.q_norm && a.kvr.dh > 64;
   if (tiles(128, 64) >= 512 || (a.K >= 4096 && tiles(256, 128) >= 128)) {
-    struct Candidate { int v, bm, bn, per_cu; double rate; };
-    static constexpr Candidate cand[] = {{V_256x256, 256, 256, 1, 1.25}, {V_256x192_S2, 256, 192, 1, 1.15}, {V_256x128_S3, 256, 128, 1, 1.03},
-                                         {V_128x192_S2, 128, 192, 2, 1.0}, {V_128x128, 128, 128, 2, 0.95}, {V_128x64, 128, 64, 3, 0.78}};
-    const double nk = a.K / BK;
+    struct Candidate { int v, bm, bn; double us1, fill1, us, fill, gelu, residual, route; };   // us1, fill1: one round
+    static constexpr Candidate cand[] = {
+        {V_256x256, 256, 256, 1.31, 8, 1.51, 5, 5.0, 12.0, 14.0},   {V_256x192_S2, 256, 192, 1.14, 6, 1.28, 4, 5.5, 10.5, 14.5},
+        {V_256x128_S3, 256, 128, 0.77, 9, 0.88, 5, 2.5, 7.0, 14.5}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 3.0, 5.0, 8.5},
+        {V_128x192_S3, 128, 192, 0.64, 11, 0.65, 9, 5.0, 7.5, 11.5}, {V_128x128, 128, 128, 0.80, 6, 0.45, 6, 1.5, 3.5, 5.5},
+        {V_128x64, 128, 64, 0.76, 0, 0.31, 4, 0.4, 1.7, 2.0},       {V_64x128_S3, 64, 128, 0.46, 9, 0.33, 4, 0.7, 2.0, 2.0}};
+    const int form = gemm_epilogue_form(a);
     int best = V_128x128;
     double best_cost = 1e300;
     for (const Candidate &c : cand) {
       if (wide_heads && c.bn % 128) continue;
-      const int64_t t = tiles(c.bm, c.bn);
-      const double fill = c.per_cu == 1 ? 9.0 : (t > 256 ? 2.0 : 14.0);
-      const double cost = (double)((t + 255) / 256) * c.bm * c.bn / c.rate * (nk + fill) / nk;
+      const int64_t rounds = (grid(c.bm, c.bn) + 255) / 256;
+      const double epilogue = form == EM_KV_ROUTE ? c.route : form == EM_RESIDUAL ? c.residual : a.gelu_from < a.N ? c.gelu : 0.0;
+      const double cost = rounds * ((rounds == 1 ? c.us1 * (a.K / BK + c.fill1) : c.us * (a.K / BK + c.fill)) + epilogue);
       if (cost < best_cost) { best_cost = cost; best = c.v; }
     }
-    return best == V_128x192_S2 && a.K >= 4096 && tiles(128, 192) <= 256 ? V_128x192_S3 : best;
+    return best;
   }
   if (wide_heads) return V_64x128_S3;
   const int64_t t64 = tiles(64, 64);
   if (t64 <= g_wavek_max_tiles && a.K >= g_wavek_min_k) return V_WAVEK;
   if (t64 <= 512) return V_64x64_S4;
-  const int64_t t128 = tiles(64, 128);
-  const bool even = (t128 + 255) / 256 * 2 <= (t64 + 255) / 256;
-  return t128 <= 512 && (even || a.K >= 1536) ? V_64x128_S3 : V_64x64_S2;
+  const bool even = (tiles(64, 128) + 255) / 256 * 2 <= (t64 + 255) / 256;
+  return grid(64, 128) <= 512 && (even || a.K >= 1536) ? V_64x128_S3 : V_64x64_S2;
 }
 
 static hipError_t launch_variant(int v, const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
@@ -512,6 +528,7 @@ hipError_t launch_gemm_mfma_dl(const GemmArgs &a, hipStream_t s, const GemmArgs 
     case 28: return launch_tile<128, 192, 2>(a, b, s);
     case 29: return launch_tile<256, 192, 2, 4, 2>(a, b, s);
     case 30: return launch_tile<128, 192, 3>(a, b, s);
+    case 31: return launch_tile<64, 128, 3>(a, b, s);
     case 40: return launch_tile<128, 192, 2, 2, 2, true>(a, b, s);
     case 41: return launch_tile<256, 192, 2, 4, 2, true>(a, b, s);
     case 42: return launch_tile<128, 192, 3, 2, 2, true>(a, b, s);
