@@ -98,12 +98,12 @@ int choose_splits(int path, int dt, int nq, int H, int kv_rows, int head_dim) {
   const bool gen2 = !simt && pf::g_attn_variant == 0 && (head_dim == 64 || head_dim == 72 || head_dim == 128);
   const int qtile = simt ? 64 : (gen2 ? attn_mfma2_qtile(nq) : 128);
   // workgroups the chip holds at a time (fp32 MFMA, head sizes up to 72: three per CU; 512 queries x 16 heads x 4096 keys 134 ->
-  // 122 us with 6 splits instead of 4)
-  const int resident = qtile == 256 ? 256 : (mfma_f32 && head_dim <= 72 ? 768 : 512);
+  // 122 us with 6 splits instead of 4).  The plain kernel's are single waves, two a SIMD by their registers up to 72 channels
+  // and one beyond: 1024 queries x 24 heads of 48 over 4096 keys 1182 us with 4 splits, 976 with 5, 1421 with 6 (2304 waves).
+  const int resident = qtile == 256 ? 256 : simt && !mfma_f32 ? (head_dim <= 72 ? 2048 : 1024) : mfma_f32 && head_dim <= 72 ? 768 : 512;
   // the combine pass: a launch, and the partial rows written and read at memory speed (about 7 MB in the time of a tile;
   // 2560 queries x 24 heads of 128, one split instead of two: 429 + 16 -> 426 us).  The kernels of other head sizes and the
-  // plain ones keep the half tile per split they were measured with: their tiles take many times as long (fp32, 1024 queries x
-  // 24 heads of 48 on the plain kernel, two layers: 3901 us with 4 splits, 5321 with 2).
+  // plain ones keep half a tile per split: their tiles take up to 25 us, and where the rounds come out even it does not matter.
   const double row_units = (double)nq * H * head_dim * (f32 ? 2.0 : 1.0) * 1.43e-7;
   const int ktile = simt ? 32 : 64;
   const int64_t blocks = (int64_t)((nq + qtile - 1) / qtile) * H;
