@@ -445,7 +445,7 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 //  * beyond, 64x128 with three stages under the same condition, where its rounds (of 256 tiles) are no more work than those
 //    of 64x64 tiles or K is long enough to pay for it: 1024x3456x1152 16.9 -> 15.2 us, 512x6144x1536 22.8 -> 22.0,
 //    512x4608x1536 20.3 -> 18.7 against two-stage 64x64 tiles, which take what is left (512x4608x1152 inside a stage: 15.8
-//    us, with 64x128 17.3).
+//    us, with 64x128 17.3; 512x4608x1536 with a residual and an unaligned bias 33 us, with 64x128 39).
 // 64x64 with three stages is there for pf_op_gemm_tile only: the rule never takes it.
 enum { V_256x256 = 0, V_64x128_S3, V_256x128_S3, V_128x128, V_128x64, V_WAVEK, V_64x64_S4, V_64x64_S3, V_64x64_S2,
        V_128x192_S2, V_256x192_S2, V_128x192_S3, V_COUNT };
@@ -460,20 +460,23 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
   };
   // per-head norm in the epilogue: heads of 128 channels need tiles of 128 or 256 columns
   const bool wide_heads = a.kvr.q_norm && a.kvr.dh > 64;
+  // operands that are not aligned for vectors have an element-wise epilogue (`odd` us per round, with a residual 2.6 times that)
+  const bool odd = !vec_epilogue_ok(a) || (b && !vec_epilogue_ok(*b));
   if (tiles(128, 64) >= 512 || (a.K >= 4096 && tiles(256, 128) >= 128)) {
-    struct Candidate { int v, bm, bn; double us1, fill1, us, fill, gelu, residual, route; };   // us1, fill1: one round
+    struct Candidate { int v, bm, bn; double us1, fill1, us, fill, gelu, residual, route, odd; };   // us1, fill1: one round
     static constexpr Candidate cand[] = {
-        {V_256x256, 256, 256, 1.31, 8, 1.51, 5, 5.0, 12.0, 14.0},   {V_256x192_S2, 256, 192, 1.14, 6, 1.28, 4, 5.5, 10.5, 14.5},
-        {V_256x128_S3, 256, 128, 0.77, 9, 0.88, 5, 2.5, 7.0, 14.5}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 3.0, 5.0, 8.5},
-        {V_128x192_S3, 128, 192, 0.64, 11, 0.65, 9, 5.0, 7.5, 11.5}, {V_128x128, 128, 128, 0.80, 6, 0.45, 6, 1.5, 3.5, 5.5},
-        {V_128x64, 128, 64, 0.76, 0, 0.31, 4, 0.4, 1.7, 2.0},       {V_64x128_S3, 64, 128, 0.46, 9, 0.33, 4, 0.7, 2.0, 2.0}};
+        {V_256x256, 256, 256, 1.31, 8, 1.51, 5, 5.0, 12.0, 14.0, 31.0},   {V_256x192_S2, 256, 192, 1.14, 6, 1.28, 4, 5.5, 10.5, 14.5, 27.0},
+        {V_256x128_S3, 256, 128, 0.77, 9, 0.88, 5, 2.5, 7.0, 14.5, 16.0}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 3.0, 5.0, 8.5, 16.0},
+        {V_128x192_S3, 128, 192, 0.64, 11, 0.65, 9, 5.0, 7.5, 11.5, 22.0}, {V_128x128, 128, 128, 0.80, 6, 0.45, 6, 1.5, 3.5, 5.5, 10.0},
+        {V_128x64, 128, 64, 0.76, 0, 0.31, 4, 0.4, 1.7, 2.0, 2.7},       {V_64x128_S3, 64, 128, 0.46, 9, 0.33, 4, 0.7, 2.0, 2.0, 4.6}};
     const int form = gemm_epilogue_form(a);
     int best = V_128x128;
     double best_cost = 1e300;
     for (const Candidate &c : cand) {
       if (wide_heads && c.bn % 128) continue;
       const int64_t rounds = (grid(c.bm, c.bn) + 255) / 256;
-      const double epilogue = form == EM_KV_ROUTE ? c.route : form == EM_RESIDUAL ? c.residual : a.gelu_from < a.N ? c.gelu : 0.0;
+      const double epilogue = odd ? c.odd * (form == EM_RESIDUAL ? 2.6 : 1.0)
+                                  : form == EM_KV_ROUTE ? c.route : form == EM_RESIDUAL ? c.residual : a.gelu_from < a.N ? c.gelu : 0.0;
       const double cost = rounds * ((rounds == 1 ? c.us1 * (a.K / BK + c.fill1) : c.us * (a.K / BK + c.fill)) + epilogue);
       if (cost < best_cost) { best_cost = cost; best = c.v; }
     }
@@ -484,7 +487,7 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
   if (t64 <= g_wavek_max_tiles && a.K >= g_wavek_min_k) return V_WAVEK;
   if (t64 <= 512) return V_64x64_S4;
   const bool even = (tiles(64, 128) + 255) / 256 * 2 <= (t64 + 255) / 256;
-  return grid(64, 128) <= 512 && (even || a.K >= 1536) ? V_64x128_S3 : V_64x64_S2;
+  return grid(64, 128) <= 512 && (even || a.K >= 1536) && !odd ? V_64x128_S3 : V_64x64_S2;
 }
 
 static hipError_t launch_variant(int v, const GemmArgs &a, const GemmArgs *b, hipStream_t s) {

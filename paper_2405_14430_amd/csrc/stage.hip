@@ -944,7 +944,8 @@ const char *pf_gemm_kernel_name(int dtype, int path, int M, int N, int K) {
   GemmArgs g{};
   g.dt = dtype; g.path = path == PF_PATH_AUTO ? PATH_AUTO : PATH_SIMT; g.M = M; g.N = N; g.K = K;
   g.lda = g.ldw = K;   // dense operands at aligned addresses
-  g.gelu_from = N;     // plain store
+  g.gelu_from = N;     // plain store of aligned rows
+  g.ldc = (N + 7) / 8 * 8;
   if (dtype == PF_F32) return gemm_mfma_f32_supported(g) ? gemm_mfma_f32_variant_name(g) : "gemm_simt_kernel";
   if (g.path == PATH_SIMT) return "gemm_simt_kernel";
   return gemm_mfma_dl_supported(g) ? gemm_mfma_dl_variant_name(g) : "gemm_mfma_kernel";

@@ -87,3 +87,33 @@ def test_tile_64x128(M, N, K):
     ref = R.double() + gate.double() * lin
     assert bool(((x.double() - ref).abs() <= 4e-3 * ref.square().mean().sqrt()).all())          # |gate| up to 4
     assert torch.equal(copy, x.to(BF))
+
+
+@pytest.mark.parametrize("dtype", [BF, F32])
+@pytest.mark.parametrize("M,N,K", [(70, 130, 128), (300, 1156, 512), (33, 9, 64), (2100, 1203, 320), (500, 4611, 1536)])
+def test_columns_behind_the_last_group_of_eight(dtype, M, N, K):
+    """N no multiple of eight in rows that are: whole groups by vectors, the rest by elements, the columns behind untouched."""
+    import ctypes as C
+    from paper_2405_14430_amd import binding as B
+    print("tail", dtype, M, N, K, flush=True)
+    lib, ld = B.load_library(), (N + 7) // 8 * 8
+    A, W, b = _operands(M, N, K, dtype)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    bias, gate = torch.zeros(ld, dtype=dtype, device="cuda"), torch.randn(ld, generator=g, device="cuda")
+    bias[:N] = b
+    R = torch.randn(M, ld, generator=g, device="cuda")
+    out, X, X2 = (torch.full((M, ld), 7.0, dtype=t, device="cuda") for t in (dtype, F32, dtype))
+    p = lambda t: C.c_void_p(t.data_ptr())
+    stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    dt = int(dtype == BF)
+    assert lib.pf_op_gemm(dt, 0, p(A), K, p(W), K, p(bias), p(out), ld, M, N, K, 0, N // 2, 1, None, None, 0, None, 0, stream) == 0
+    assert lib.pf_op_gemm(dt, 0, p(A), K, p(W), K, p(bias), p(X), ld, M, N, K, 1, N, 1, p(gate), p(R), ld, p(X2), ld, stream) == 0
+    lin = A.double() @ W.double().T + b.double()
+    ref = lin.clone()
+    ref[:, N // 2:] = torch.nn.functional.gelu(lin[:, N // 2:], approximate="tanh")
+    assert _ok(out[:, :N], ref, K)
+    ref = R[:, :N].double() + gate[:N].double() * lin
+    assert bool(((X[:, :N].double() - ref).abs() <= (4e-3 if dt else 4 * (12 * math.sqrt(K) + 32) * 2.0 ** -24) * ref.square().mean().sqrt()).all())
+    assert torch.equal(X2[:, :N], X[:, :N].to(dtype))
+    for t in (out, X, X2):
+        assert bool((t[:, N:] == 7.0).all())
