@@ -315,7 +315,7 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
   }
 }
 
-// Cut of the tile grid over the 8 XCDs (see tile_of_block): the gx in {1, 2, 4, 8} for which an XCD's block needs the
+// Cut of the tile grid over the 8 XCDs (see tile_of_id): the gx in {1, 2, 4, 8} for which an XCD's block needs the
 // fewest operand rows; a cut that pads the grid by more than an eighth is priced four times.  *grid receives the
 // workgroup count.
 inline int xcd_cut(const GemmArgs &a, int BM, int BN, unsigned *grid) {

@@ -1,6 +1,10 @@
-"""The bf16 GEMM's tile rule against measured launches (CPU, host-only query): for shapes at the edges of its rounds - few rows
+"""The GEMMs' tile rules and the banded tile walk (CPU, host-only queries).
+
+The bf16 rule against measured launches: for shapes at the edges of its rounds - few rows
 at wide outputs, one round and a little more, grids that an XCD's block of whole rows and columns pads - the tile it picks is
 within an eighth of the fastest.  us per launch, plain store, isolated GEMMs with cold weights on an MI355X."""
+import ctypes as C
+
 import pytest
 
 from paper_2405_14430_amd import binding as B
@@ -30,3 +34,41 @@ def test_rule_picks_a_tile_near_the_fastest(shape):
     us = MEASURED[shape]
     name = B.load_library().pf_gemm_kernel_name(1, 0, *shape).decode()
     assert us[name.replace("gemm_tile_kernel", "")] <= 1.125 * min(us.values()), (name, min(us, key=us.get))
+
+
+# fp32 shapes of the GPU tests, one of every kernel and of the rule's edges (384 tiles of 64x64, 256 of 32x32, K = 6144)
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (1025, 1608, 160, "gemm_f32_tile_kernel<64,64,3,2,2>"), (1024, 1536, 1152, "gemm_f32_tile_kernel<64,64,3,2,2>"),
+    (1024, 1472, 1152, "gemm_f32_wavek_kernel<32,32,4>"), (500, 1160, 1152, "gemm_f32_wavek_kernel<32,32,4>"), (77, 4608, 1536, "gemm_f32_wavek_kernel<32,32,4>"),
+    (512, 512, 1152, "gemm_f32_wavek_kernel<32,32,8>"), (33, 1000, 96, "gemm_f32_wavek_kernel<32,32,8>"), (300, 1544, 6144, "gemm_f32_wavek_kernel<32,32,8>"),
+    (300, 1544, 6112, "gemm_f32_wavek_kernel<32,32,4>"), (70, 72, 40, "gemm_simt_kernel")])
+def test_fp32_rule(M, N, K, kernel):
+    assert B.load_library().pf_gemm_kernel_name(0, 0, M, N, K).decode() == kernel
+
+
+# tile grids of at least four rounds per XCD, whose blocks are walked in bands: a lower last band (17 tile rows in bands of four),
+# bands of both kinds of tiles, more rows than columns and the reverse
+@pytest.mark.parametrize("M,N,bm,bn", [(16896, 12288, 256, 256), (16896, 9216, 256, 256), (65536, 3456, 128, 192), (16896, 3072, 128, 192), (17000, 9300, 128, 128), (3000, 60000, 128, 64), (30000, 20000, 64, 128)])
+def test_banded_walk_covers_every_tile_once(M, N, bm, bn):
+    lib = B.load_library()
+    tiles_m, tiles_n = -(-M // bm), -(-N // bn)
+    grid, tm, tn = C.c_uint(0), C.c_int(0), C.c_int(0)
+    lib.pf_gemm_tile_map(M, N, bm, bn, 0, C.byref(grid), C.byref(tm), C.byref(tn))
+    assert grid.value % 8 == 0
+    seen, banded = set(), False
+    for x in range(8):
+        walk = []                                    # tiles of one XCD in the order of its workgroups
+        for wg in range(x, grid.value, 8):
+            if lib.pf_gemm_tile_map(M, N, bm, bn, wg, C.byref(grid), C.byref(tm), C.byref(tn)):
+                walk.append((tm.value, tn.value))
+        assert not seen.intersection(walk) and len(set(walk)) == len(walk)
+        seen.update(walk)
+        r0, c0 = min(t[0] for t in walk), min(t[1] for t in walk)
+        rows, cols = max(t[0] for t in walk) - r0 + 1, max(t[1] for t in walk) - c0 + 1
+        assert len(walk) == rows * cols              # a full rectangle
+        # band height: rows before the second column; then whole bands, column by column, the last one maybe lower
+        G = next((i for i, t in enumerate(walk) if t[1] != c0), len(walk))
+        order = [(r0 + i, c0 + j) for b in range(0, rows, G) for j in range(cols) for i in range(b, min(b + G, rows))]
+        assert walk == order
+        banded = banded or G > 1
+    assert banded and seen == {(i, j) for i in range(tiles_m) for j in range(tiles_n)}

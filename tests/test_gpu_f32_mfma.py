@@ -21,8 +21,9 @@ def _err(got, ref):
     return float((got.double() - ref).abs().max() / ref.square().mean().sqrt())
 
 
-# one K tile; ragged rows and columns of every variant; at most one tile per CU; many tiles; long K; K the kernels refuse
-@pytest.mark.parametrize("M,N,K", [(1, 8, 32), (31, 40, 64), (33, 1000, 96), (65, 1544, 384), (300, 520, 6144), (1025, 1608, 160), (70, 72, 40)])
+# one K tile; ragged rows and columns of every variant (64x64: 1025 rows; K over four waves: 500 and 77 rows; over eight: the others);
+# at most one tile per CU; many tiles; long K; K the kernels refuse
+@pytest.mark.parametrize("M,N,K", [(1, 8, 32), (31, 40, 64), (33, 1000, 96), (65, 1544, 384), (300, 520, 6144), (1025, 1608, 160), (70, 72, 40), (500, 1160, 1152), (77, 4616, 1536)])
 def test_gemm_f32(M, N, K):
     B = _pkg()
     print("gemm_f32", M, N, K, flush=True)
