@@ -440,8 +440,10 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 // Fewer tiles (patches of a few hundred rows), by counts of 64x64 tiles:
 //  * the wave-split-K kernel, one workgroup per CU (128 KB of LDS): up to one tile per CU, from K = 1024 on.  512x1152x1152
 //    8.2 us (four-stage 64x64: 8.9), 512x1152x4608 19.8 (23.6), 512x1536x6144 25.5 (31.5); with more tiles than CUs it loses:
-//    1024x1152x4608 34.3 (29.4).
-//  * 64x64 with four stages while every workgroup is resident at once (two per CU), 375x4608x1536 14.0 us (two stages 19.6);
+//    1024x1152x4608 34.3 (29.4) - until the second round of its workgroups is nearly full too and K is long: 633x3072x15360
+//    106.8 (120.1; 432 tiles: 103.0 against 93.7), 1275x1536x6144 46.0 (50.5), 633x3072x3072 28.2 (29.0), 1275x1536x1536 17.5 (14.9).
+//  * 64x64 with four stages while every workgroup of the padded grid is resident at once (two per CU), 375x4608x1536 14.0 us
+//    (two stages 19.6); 1339x1536x6144, 21 x 24 tiles in a grid of 528, 65 us (64x128 54);
 //  * beyond, 64x128 with three stages under the same condition, where its rounds (of 256 tiles) are no more work than those
 //    of 64x64 tiles or K is long enough to pay for it: 1024x3456x1152 16.9 -> 15.2 us, 512x6144x1536 22.8 -> 22.0,
 //    512x4608x1536 20.3 -> 18.7 against two-stage 64x64 tiles, which take what is left (512x4608x1152 inside a stage: 15.8
@@ -485,7 +487,7 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
   if (wide_heads) return V_64x128_S3;
   const int64_t t64 = tiles(64, 64);
   if (t64 <= g_wavek_max_tiles && a.K >= g_wavek_min_k) return V_WAVEK;
-  if (t64 <= 512) return V_64x64_S4;
+  if (grid(64, 64) <= 512) return t64 >= 472 && a.K >= 2560 ? V_WAVEK : V_64x64_S4;
   const bool even = (tiles(64, 128) + 255) / 256 * 2 <= (t64 + 255) / 256;
   return grid(64, 128) <= 512 && (even || a.K >= 1536) && !odd ? V_64x128_S3 : V_64x64_S2;
 }

@@ -26,6 +26,18 @@ MEASURED = {
     (4096, 3456, 1152): {"<256,256,2,4,2,false>": 37.4, "<256,192,2,4,2,false>": 51.7, "<256,128,3,4,2,false>": 41.5, "<128,192,2,2,2,false>": 45.4, "<128,192,3,2,2,true>": 54.4, "<128,128,2,2,2,false>": 41.1, "<128,64,2,2,2,false>": 48.3, "<64,128,3,2,2,false>": 49.6},
     (3677, 8192, 2048): {"<256,256,2,4,2,false>": 116.7, "<256,192,2,4,2,false>": 130.7, "<256,128,3,4,2,false>": 138.0, "<128,192,2,2,2,false>": 131.0, "<128,192,3,2,2,true>": 150.2, "<128,128,2,2,2,false>": 128.1, "<128,64,2,2,2,false>": 159.4, "<64,128,3,2,2,false>": 165.9},
     (1024, 4608, 1536): {"<256,256,2,4,2,false>": 43.2, "<256,192,2,4,2,false>": 39.0, "<256,128,3,4,2,false>": 26.2, "<128,192,2,2,2,false>": 30.3, "<128,192,3,2,2,true>": 24.4, "<128,128,2,2,2,false>": 26.5, "<128,64,2,2,2,false>": 27.0, "<64,128,3,2,2,false>": 31.7},
+    # fewer tiles, where the rule does not look at the epilogue: 430 to 528 tiles of 64x64, with a residual
+    (633, 3072, 15360): {"gemm_wavek_kernel<64,64>": 106.8, "<64,64,4,2,2,false>": 120.1, "<64,128,3,2,2,false>": 119.1, "<64,64,2,2,2,false>": 162.9, "<128,64,2,2,2,false>": 177.2},
+    (633, 3072, 12288): {"gemm_wavek_kernel<64,64>": 79.9, "<64,64,4,2,2,false>": 96.7, "<64,128,3,2,2,false>": 93.8, "<64,64,2,2,2,false>": 126.9, "<128,64,2,2,2,false>": 139.2},
+    (569, 3072, 15360): {"gemm_wavek_kernel<64,64>": 103.0, "<64,64,4,2,2,false>": 93.7, "<64,128,3,2,2,false>": 115.2, "<64,64,2,2,2,false>": 161.6, "<128,64,2,2,2,false>": 175.8},
+    (1275, 1536, 6144): {"gemm_wavek_kernel<64,64>": 46.0, "<64,64,4,2,2,false>": 50.5, "<64,128,3,2,2,false>": 51.7, "<64,64,2,2,2,false>": 67.1, "<128,64,2,2,2,false>": 74.2},
+    (1339, 1536, 6144): {"gemm_wavek_kernel<64,64>": 64.0, "<64,64,4,2,2,false>": 65.3, "<64,128,3,2,2,false>": 53.6, "<64,64,2,2,2,false>": 66.9, "<128,64,2,2,2,false>": 74.4},
+    (1211, 1536, 6144): {"gemm_wavek_kernel<64,64>": 45.7, "<64,64,4,2,2,false>": 43.1, "<64,128,3,2,2,false>": 51.1, "<64,64,2,2,2,false>": 67.0, "<128,64,2,2,2,false>": 74.3},
+    (765, 2560, 10240): {"gemm_wavek_kernel<64,64>": 74.5, "<64,64,4,2,2,false>": 84.7, "<64,128,3,2,2,false>": 83.6, "<64,64,2,2,2,false>": 108.6, "<128,64,2,2,2,false>": 119.4},
+    (1021, 2048, 8192): {"gemm_wavek_kernel<64,64>": 57.5, "<64,64,4,2,2,false>": 63.8, "<64,128,3,2,2,false>": 67.4, "<64,64,2,2,2,false>": 85.6, "<128,64,2,2,2,false>": 93.5},
+    (1527, 1152, 4608): {"gemm_wavek_kernel<64,64>": 34.7, "<64,64,4,2,2,false>": 30.9, "<64,128,3,2,2,false>": 39.1, "<64,64,2,2,2,false>": 50.8, "<128,64,2,2,2,false>": 56.6},
+    (1783, 1152, 4608): {"gemm_wavek_kernel<64,64>": 36.8, "<64,64,4,2,2,false>": 39.4, "<64,128,3,2,2,false>": 41.7, "<64,64,2,2,2,false>": 51.4, "<128,64,2,2,2,false>": 58.0},
+    (1275, 1536, 1536): {"gemm_wavek_kernel<64,64>": 17.5, "<64,64,4,2,2,false>": 14.9, "<64,128,3,2,2,false>": 17.8, "<64,64,2,2,2,false>": 16.6, "<128,64,2,2,2,false>": 19.2},
 }
 
 
