@@ -1,7 +1,7 @@
 // Plain SIMT attention of patch queries over a full-sequence K/V buffer (PipeFusion Sec. 3.3: the buffer
 // mixes fresh and stale rows; the kernel does not care which is which).  One query row per thread, one
 // wavefront per workgroup, K/V streamed through LDS in tiles of 32 rows, online softmax per thread.
-// Used for the fp32 dtype and as the forced-SIMT path for bf16.
+// The forced-SIMT path of both dtypes, and what the fp32 MFMA kernel does not take (head sizes other than 64, 72 and 128).
 #include "common.h"
 #include "ops.h"
 

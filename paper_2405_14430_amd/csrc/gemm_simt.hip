@@ -1,5 +1,5 @@
-// Plain LDS-tiled SIMT GEMM, C = epilogue(A W^T + bias), fp32 accumulation.  Used for the fp32 dtype and as
-// the forced-SIMT path for bf16.  64x64 output tile per 256-thread workgroup, 4x4 outputs per thread.
+// Plain LDS-tiled SIMT GEMM, C = epilogue(A W^T + bias), fp32 accumulation.  The forced-SIMT
+// path of both dtypes, and what the fp32 MFMA kernels do not take (K no multiple of 32, unaligned operand rows).  64x64 output tile per 256-thread workgroup, 4x4 outputs per thread.
 #include "common.h"
 #include "epilogue.h"
 #include "ops.h"

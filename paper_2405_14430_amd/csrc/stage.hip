@@ -306,7 +306,7 @@ hipError_t attention(pf_stage *s, int cls, const void *q, int64_t ldq, const voi
 
 // QKV projection of `rows` rows plus the write of their K/V into the layer's buffers.  Rows are image-major, `seg` per
 // image (rows = B * seg); inside an image, row r goes to buffer row (r < split ? row0a + r : row0b + r - split).  When
-// the bf16 GEMM's vectorised epilogue can do it, k and v go straight from the accumulators into K / V^T (q, and RoPE
+// the GEMM's vectorised epilogue can do it, k and v go straight from the accumulators into K / V^T (q, and RoPE
 // through `rope_tab`, likewise); otherwise the projection lands in the qkv workspace and the scatter kernel moves (and
 // rotates) it, one launch per image and row range.
 // How the QKV projection of a stream reaches the buffers: through the GEMM epilogue, or through the scatter kernel,
