@@ -16,6 +16,7 @@
 //    chain of K iterations by four; the four partial tiles are then summed through LDS.
 // Both finish through LDS: the fp32 tile is laid out row-major and every thread applies the epilogue to runs of 8
 // consecutive columns (16-byte bf16 stores, 32-byte fp32 stores).
+#include "gemm_pp.h"
 #include "gemm_tile.h"
 
 namespace pf {
@@ -30,6 +31,11 @@ constexpr int ROW_BYTES = BK * 2;  // 128
 // ------------------------------------------------------------------------------------------------------------------
 template <int NP, int EM, int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, bool SPREAD_LOADS = false>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf16_t, NP> L) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  if constexpr (BM == 256 && BN == 256) {
+    gemm_pp256_body<NP, EM>(L, smem);
+    return;
+  } else {
   const bool second = NP == 2 && blockIdx.x >= L.grid0;
   const GemmProblem<bf16_t> &prob = L.p[second ? 1 : 0];
   const bf16_t *__restrict__ A = prob.A, *__restrict__ W = prob.W;
@@ -47,7 +53,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
   constexpr int STAGE_BYTES = (BM + BN) * ROW_BYTES;
   auto key = [](int r) { return (r >> 1) & 7; };
   constexpr int TLD = BN + 4;
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -201,6 +206,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
     __syncthreads();
     if constexpr (EPRE && RB == BM) tile_epilogue<EM, BM, BN, TLD, 64 * NW, true>(tile, m0, n0, M, N, epi, vec_ok != 0, &eops);
     else tile_epilogue<EM, RB, BN, TLD, 64 * NW>(tile, m0 + pass * RB, n0, M, N, epi, vec_ok != 0);
+  }
   }
 }
 
@@ -358,7 +364,7 @@ template <int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, bool SPREAD = fa
 hipError_t launch_tile(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   // the stage ring, or the fp32 tile (row stride BN + 4) that replaces it for the epilogue, whichever is larger
   constexpr int ring = NSTAGE * (BM + BN) * ROW_BYTES, tile = BM * (BN + 4) * 4;
-  constexpr int smem = (tile > ring && tile <= 96 * 1024) ? tile : ring;   // larger tiles finish in row passes
+  constexpr int smem = BM == 256 && BN == 256 ? PingPong256::SMEM : (tile > ring && tile <= 96 * 1024) ? tile : ring;   // larger tiles finish in row passes
   auto go = [&](auto np, auto em) -> hipError_t {
     constexpr int NP = decltype(np)::value, EM = decltype(em)::value;
     if constexpr (PINNED && (NP == 2 || EM == EM_KV_ROUTE)) {
