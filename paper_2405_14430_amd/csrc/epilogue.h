@@ -39,8 +39,9 @@ struct Epilogue {
     return gate_seg > 0 ? gate + (int64_t)(row / gate_seg) * gate_stride : gate;
   }
 
-  __device__ __forceinline__ void apply(int row, int col, float acc) const {
-    float v = acc + (bias ? to_f32(bias[col]) : 0.f);
+  __device__ __forceinline__ void apply(int row, int col, float acc) const { put(row, col, acc + (bias ? to_f32(bias[col]) : 0.f)); }
+
+  __device__ __forceinline__ void put(int row, int col, float v) const {   // v: with its bias
     if (mode == 0) {
       if (col >= gelu_from) v = gelu_f(v, gelu_tanh);
       Elem<T>::store(reinterpret_cast<T *>(C) + (size_t)row * ldc + col, v);

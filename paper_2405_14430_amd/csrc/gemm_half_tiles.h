@@ -1,22 +1,27 @@
-// bf16 MFMA GEMM of 256x256 tiles for launches with many of them (gfx950): C = epilogue(A W^T + bias), K a multiple of 64.
+// bf16 MFMA GEMM body of the 256x256 tile: C = epilogue(A W^T + bias), K a multiple of 64.
 //
-// Eight wavefronts, 2 along M x 4 along N, one workgroup per CU; waves 0-3 sit one to a SIMD, and so do 4-7.  A K tile is
-// 64 wide and lives in LDS as four half tiles (A0 A1 B0 B1: 128 rows x 128 bytes each), two K tiles deep (128 KB).  A wave owns
-// 64 rows of either A half and 32 rows of either W half, so a K tile is four phases of eight MFMAs:
+// Eight wavefronts, 2 along M x 4 along N, one workgroup per CU.  A K tile is 64 wide and lives in LDS as four half tiles
+// (A0 A1 W0 W1: 128 rows x 128 bytes each), two K tiles deep (128 KB).  A wave owns 64 rows of either A half (two blocks of 32)
+// and 32 rows of either W half, so a K tile is four phases of eight MFMAs, one block of A rows with both W halves each:
 //
-//   phase   reads from LDS        loads                  multiplies
-//     0     A0(t)   8 reads       B0(t+2)                A0 B0
-//     1     B1(t)   4             A0(t+2)                A0 B1
-//     2     A1(t)   8             B1(t+2)                A1 B1
-//     3     B0(t+1) 4             A1(t+2)                A1 B0
+//   phase   multiplies    reads from LDS (for the next phase, for the next K tile)    loads
+//     0     block 0       block 1 (A0),  W0(t+1)                                      A1(t+1)
+//     1     block 1       block 2 (A1)                                                W1(t+2)
+//     2     block 2       block 3 (A1),  W1(t+1)                                      A0(t+2)
+//     3     block 3       block 0 of t+1 (A0)                                         W0(t+3)
 //
-// Every phase is a memory part (reads, two load instructions per wave, waits), a barrier, the MFMAs, a barrier; waves 4-7 run
-// one barrier behind waves 0-3, so on every SIMD one wave feeds the matrix unit while the other fetches its operands.
-// The half tiles are numbered in the order B0 A0 B1 A1 of each K tile: number j is read in phase j - 1, so its place is free
-// for number j + 8 from phase j on, where that is loaded.  A load has seven phases to arrive (six half tiles, 96 KB per CU, are in
-// flight at any time), and the waits never drain the queue: in phase k a wave waits for its part of number k + 2, twelve of
-// its load instructions behind it.  Both waves of a SIMD pass that wait before the first of them reads number k + 2.
+// A half tile is loaded again as soon as its last rows have been read, one and a half to two K tiles before they are needed, and
+// every fragment is read a phase before its MFMAs: nothing in a phase waits for what was asked for in it.  Reads and loads are
+// issued between the MFMAs.  Two barriers a K tile, behind phases 1 and 3: what the next two phases read has landed
+// (three half tiles, six of the wave's load instructions, may still be in flight), and what they overwrite has been read (the four
+// reads behind the barrier's phase may still be on their way; they are of the half that is loaded a barrier later).
 // LDS rows are swizzled as in gemm_mfma_dl.hip.
+//
+// What bounds it is power: 85 % of the cycles have the matrix unit busy (8192x8192x8192), at the clock the card then allows.
+// One K tile at a time behind one barrier (43 - 49 % busy) -> this: 8192x8192x8192 1063 -> 767 - 800 us (1.37 - 1.43 PFLOP/s, the
+// vendor library 690), 16896x9216x3072 850 -> 754, 16896x12288x3072 with GELU 1168 -> 1033, 16896x3072x15360 with a
+// residual 1599 -> 1402.  Waves 4-7 half a phase behind waves 0-3, one multiplying while the other reads (eight barriers a K tile):
+// 1 % slower; reads in the phase that uses them: 4 % slower.
 #pragma once
 #include "gemm_tile.h"
 
@@ -24,7 +29,7 @@ namespace pf {
 
 namespace {
 
-struct PingPong256 {
+struct HalfTiles256 {
   static constexpr int BM = 256, BN = 256, NT = 512;
   static constexpr int HALF_BYTES = 128 * 128;            // 16 KB
   static constexpr int W_BASE = 4 * HALF_BYTES;           // A: [stage][half] at 0, W: the same behind it
@@ -38,16 +43,11 @@ __device__ __forceinline__ void phase_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int N>
-__device__ __forceinline__ void wait_lgkmcnt() {
-  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
-}
-
 template <int NP, int EM>
-__device__ __forceinline__ void gemm_pp256_body(const GemmLaunch<bf16_t, NP> &L, unsigned char *smem) {
+__device__ __forceinline__ void gemm_half_tiles_body(const GemmLaunch<bf16_t, NP> &L, unsigned char *smem) {
   constexpr int BK = 64, ROW_BYTES = BK * 2;
-  constexpr int BM = PingPong256::BM, BN = PingPong256::BN, NT = PingPong256::NT, TLD = PingPong256::TLD, RB = PingPong256::RB;
-  constexpr int HALF_BYTES = PingPong256::HALF_BYTES, W_BASE = PingPong256::W_BASE;
+  constexpr int BM = HalfTiles256::BM, BN = HalfTiles256::BN, NT = HalfTiles256::NT, TLD = HalfTiles256::TLD, RB = HalfTiles256::RB;
+  constexpr int HALF_BYTES = HalfTiles256::HALF_BYTES, W_BASE = HalfTiles256::W_BASE;
   const bool second = NP == 2 && blockIdx.x >= L.grid0;
   const GemmProblem<bf16_t> &prob = L.p[second ? 1 : 0];
   const int64_t lda = prob.lda, ldw = prob.ldw;
@@ -98,6 +98,9 @@ __device__ __forceinline__ void gemm_pp256_body(const GemmLaunch<bf16_t, NP> &L,
   auto read_b1 = [&](int stage, int h, int ks) __attribute__((always_inline)) {
     fragB[stage][h][ks] = *reinterpret_cast<const bf16x8 *>(fw + (stage * 2 + h) * HALF_BYTES + slot[ks]);
   };
+
+  ColumnBias<2, 128, bf16_t> column_bias;
+  column_bias.fetch(prob.epi, n0 + wn * 32 + l32, N);
 
   f32x16 acc[4][2];   // [32-row block][W half]
 #pragma unroll
@@ -170,6 +173,8 @@ __device__ __forceinline__ void gemm_pp256_body(const GemmLaunch<bf16_t, NP> &L,
   step(c0, c1, t);
   if (!(nk & 1)) step(c1, c0, t + 1);
 
+  float bias[2];
+  column_bias.widen(bias);
   // accumulators -> row-major fp32 rows in LDS (lane -> column l32, register r -> row 8 * (r / 4) + 4 * hi + r % 4), one A half
   // at a time: every wave holds 64 rows of either
   float *tile = reinterpret_cast<float *>(smem);
@@ -182,7 +187,7 @@ __device__ __forceinline__ void gemm_pp256_body(const GemmLaunch<bf16_t, NP> &L,
       for (int g = 0; g < 2; ++g)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          tile[(wm * 64 + i * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)) * TLD + g * 128 + wn * 32 + l32] = acc[h * 2 + i][g][r];
+          tile[(wm * 64 + i * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)) * TLD + g * 128 + wn * 32 + l32] = acc[h * 2 + i][g][r] + bias[g];
     __syncthreads();
     tile_epilogue<EM, RB, BN, TLD, NT>(tile, m0 + h * RB, n0, M, N, prob.epi, prob.vec_ok != 0);
   }

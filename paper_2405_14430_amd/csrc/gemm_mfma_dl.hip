@@ -16,7 +16,8 @@
 //    chain of K iterations by four; the four partial tiles are then summed through LDS.
 // Both finish through LDS: the fp32 tile is laid out row-major and every thread applies the epilogue to runs of 8
 // consecutive columns (16-byte bf16 stores, 32-byte fp32 stores).
-#include "gemm_pp.h"
+#include "gemm_half_tiles.h"
+#include "gemm_ring.h"
 #include "gemm_tile.h"
 
 namespace pf {
@@ -29,12 +30,28 @@ constexpr int ROW_BYTES = BK * 2;  // 128
 // ------------------------------------------------------------------------------------------------------------------
 // WGM x WGN wavefronts on one shared tile
 // ------------------------------------------------------------------------------------------------------------------
+
+// K loops of gemm_tile_kernel.  256x256: half tiles refilled one by one (gemm_half_tiles.h).  The other tiles of at least 128x192 and
+// 256x128: a ring for either operand, NSTAGE K tiles of A and loop_depth_w of W deep, as LDS allows (gemm_ring.h).  Below, and for
+// the one-round 128x192 tile (SPREAD): one ring of whole K tiles (this file).  us with this file's loop -> with the other:
+//    2048x9216x3072   128x192 two stages 109 -> 108, 256x192 135 -> 115     2048x12288x3072 GELU   256x192 154 -> 140
+//    2560x3072x15360 residual   256x128 240 -> 212                          16896x9216x3072   256x256 850 -> 765
+// and where the ring is not used: 2048x3072x15360 residual, 128x192 three stages 185, ring of four 188; 4096x1152x4608 residual,
+// 128x128 59, ring 64; 1024x4608x1152 GELU, 128x64 21.4, ring 24.4; 512x4608x1536 GELU, 64x128 18.2, ring 18.6.
+constexpr bool loop_half_tiles(int BM, int BN) { return BM == 256 && BN == 256; }
+constexpr int loop_depth_w(int BM, int BN, int NSTAGE, bool SPREAD) {
+  if (SPREAD || loop_half_tiles(BM, BN) || BM * BN < 128 * 192) return 0;
+  return BM == 256 ? 4 : NSTAGE;
+}
+
 template <int NP, int EM, int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, bool SPREAD_LOADS = false>
-__global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf16_t, NP> L) {
+__global__ __launch_bounds__(64 * WGM * WGN, NSTAGE * (BM + BN) * ROW_BYTES <= 80 * 1024 ? WGM * WGN / 2 : WGM * WGN / 4) void gemm_tile_kernel(GemmLaunch<bf16_t, NP> L) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  if constexpr (BM == 256 && BN == 256) {
-    gemm_pp256_body<NP, EM>(L, smem);
-    return;
+  constexpr int DW = loop_depth_w(BM, BN, NSTAGE, SPREAD_LOADS);
+  if constexpr (loop_half_tiles(BM, BN)) {
+    gemm_half_tiles_body<NP, EM>(L, smem);
+  } else if constexpr (DW > 0) {
+    gemm_ring_body<NP, EM, BM, BN, WGM, WGN, NSTAGE, DW>(L, smem);
   } else {
   const bool second = NP == 2 && blockIdx.x >= L.grid0;
   const GemmProblem<bf16_t> &prob = L.p[second ? 1 : 0];
@@ -96,11 +113,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
     else srcW.load16(pw[idx - LA], koff, sa + BM * ROW_BYTES + ((idx - LA) * NW + wave) * 1024);
   };
 
-  // small tiles: the epilogue's residual / gate operands are requested first, ahead of every tile load
-  constexpr bool EPRE = EM == EM_RESIDUAL && BM * BN / 8 / (64 * NW) <= 2;
-  EpiOperands<BM, BN, 64 * NW> eops;
-  if constexpr (EPRE) eops.fetch(m0, n0, M, N, epi, vec_ok != 0);
-
   f32x16 acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -112,6 +124,14 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
 #pragma unroll
   for (int s = 0; s < NSTAGE - 1; ++s)
     if (s < nk) issue(s, s);
+
+  // the epilogue's operands (residual and gate of small tiles) behind the first tiles, whose latency covers the address arithmetic
+  constexpr bool EPRE = EM == EM_RESIDUAL && BM * BN / 8 / (64 * NW) <= 2;
+  EpiOperands<BM, BN, 64 * NW> eops;
+  if constexpr (EPRE) eops.fetch(m0, n0, M, N, epi, vec_ok != 0);
+
+  ColumnBias<NI, 32, bf16_t> column_bias;
+  column_bias.fetch(epi, n0 + wn * WN + (lane & 31), N);
 
   const int l32 = lane & 31, hi = lane >> 5;
   int arow[MI], akey[MI], wrow[NI], wkey[NI];
@@ -183,6 +203,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
     });
   }
 
+  float bias[NI];
+  column_bias.widen(bias);
   // accumulators -> row-major fp32 tile in LDS (lane -> column l32, register r -> row 8*(r/4) + 4*hi + r%4), in
   // passes of RB rows when the whole tile does not fit in the stage memory
   constexpr int RING = NSTAGE * STAGE_BYTES;
@@ -201,7 +223,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(GemmLaunch<bf
       for (int j = 0; j < NI; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          tile[(rbase - pass * RB + 8 * (r >> 2) + 4 * hi + (r & 3)) * TLD + wn * WN + j * 32 + l32] = acc[i][j][r];
+          tile[(rbase - pass * RB + 8 * (r >> 2) + 4 * hi + (r & 3)) * TLD + wn * WN + j * 32 + l32] = acc[i][j][r] + bias[j];
     }
     __syncthreads();
     if constexpr (EPRE && RB == BM) tile_epilogue<EM, BM, BN, TLD, 64 * NW, true>(tile, m0, n0, M, N, epi, vec_ok != 0, &eops);
@@ -279,10 +301,13 @@ __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> 
 
   constexpr bool EPRE = EM == EM_RESIDUAL && BM * BN / 8 / 256 <= 2 && BM * BN / 8 >= 256;
   EpiOperands<BM, BN, 256> eops;
-  if constexpr (EPRE) eops.fetch(m0, n0, M, N, epi, vec_ok != 0);
+  ColumnBias<4, 1, bf16_t> column_bias;   // of the columns this thread sums
 
   if (my_nk > 0) issue(0, 0);
   if (my_nk > 1) issue(1, 1);
+  // the epilogue's operands behind the first tiles, whose latency covers the address arithmetic (row / gate_seg)
+  if constexpr (EPRE) eops.fetch(m0, n0, M, N, epi, vec_ok != 0);
+  column_bias.fetch(epi, n0 + (tid % (BN / 4)) * 4, N, vec_ok != 0);
 
   const int l32 = lane & 31, hi = lane >> 5;
   for (int t = 0; t < my_nk; ++t) {
@@ -318,6 +343,8 @@ __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> 
     if (t + 2 < my_nk) issue(t & 1, t + 2);
   }
 
+  float bias[4];
+  column_bias.widen(bias);
   // partial tiles -> LDS (each wave into its own ring), then sum of the four and epilogue
   float *part = reinterpret_cast<float *>(ring);
 #pragma unroll
@@ -330,6 +357,7 @@ __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> 
   __syncthreads();
   float *p0 = reinterpret_cast<float *>(smem);
   constexpr int WSTRIDE = WAVE_BYTES / 4;
+  static_assert(256 % (BN / 4) == 0, "a thread sums the same columns of every row");
   for (int e = tid; e < BM * BN / 4; e += 256) {
     int r = e / (BN / 4), c = (e % (BN / 4)) * 4;
     float4 s0 = *reinterpret_cast<const float4 *>(p0 + r * TLD + c);
@@ -338,6 +366,7 @@ __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> 
       float4 s1 = *reinterpret_cast<const float4 *>(p0 + w * WSTRIDE + r * TLD + c);
       s0.x += s1.x; s0.y += s1.y; s0.z += s1.z; s0.w += s1.w;
     }
+    s0.x += bias[0]; s0.y += bias[1]; s0.z += bias[2]; s0.w += bias[3];
     *reinterpret_cast<float4 *>(p0 + r * TLD + c) = s0;
   }
   __syncthreads();
@@ -359,12 +388,18 @@ bool gemm_tile_map(int M, int N, int BM, int BN, unsigned id, unsigned *grid, in
 
 namespace {
 
+// the rings, or the fp32 tile (row stride BN + 4) that replaces them for the epilogue, whichever is larger
+constexpr int tile_lds_bytes(int BM, int BN, int NSTAGE, bool SPREAD) {
+  const int ring = NSTAGE * (BM + BN) * ROW_BYTES, tile = BM * (BN + 4) * 4, dw = loop_depth_w(BM, BN, NSTAGE, SPREAD);
+  if (loop_half_tiles(BM, BN)) return HalfTiles256::SMEM;
+  if (dw) return (NSTAGE * BM + dw * BN) * ROW_BYTES;
+  return (tile > ring && tile <= 96 * 1024) ? tile : ring;   // larger tiles finish in row passes
+}
+
 // PINNED: a configuration that only pf_op_gemm_tile asks for (one problem, no K/V route)
 template <int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, bool SPREAD = false, bool PINNED = false>
 hipError_t launch_tile(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
-  // the stage ring, or the fp32 tile (row stride BN + 4) that replaces it for the epilogue, whichever is larger
-  constexpr int ring = NSTAGE * (BM + BN) * ROW_BYTES, tile = BM * (BN + 4) * 4;
-  constexpr int smem = BM == 256 && BN == 256 ? PingPong256::SMEM : (tile > ring && tile <= 96 * 1024) ? tile : ring;   // larger tiles finish in row passes
+  constexpr int smem = tile_lds_bytes(BM, BN, NSTAGE, SPREAD);
   auto go = [&](auto np, auto em) -> hipError_t {
     constexpr int NP = decltype(np)::value, EM = decltype(em)::value;
     if constexpr (PINNED && (NP == 2 || EM == EM_KV_ROUTE)) {
@@ -473,8 +508,8 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
   if (tiles(128, 64) >= 512 || (a.K >= 4096 && tiles(256, 128) >= 128)) {
     struct Candidate { int v, bm, bn; double us1, fill1, us, fill, gelu, residual, route, odd; };   // us1, fill1: one round
     static constexpr Candidate cand[] = {
-        {V_256x256, 256, 256, 1.31, 8, 1.51, 5, 5.0, 12.0, 14.0, 31.0},   {V_256x192_S2, 256, 192, 1.14, 6, 1.28, 4, 5.5, 10.5, 14.5, 27.0},
-        {V_256x128_S3, 256, 128, 0.77, 9, 0.88, 5, 2.5, 7.0, 14.5, 16.0}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 3.0, 5.0, 8.5, 16.0},
+        {V_256x256, 256, 256, 1.12, 8, 1.44, 4, 4.0, 10.0, 12.0, 31.0},   {V_256x192_S2, 256, 192, 0.95, 6, 1.17, 5, 4.5, 9.0, 12.0, 27.0},
+        {V_256x128_S3, 256, 128, 0.77, 9, 0.85, 5, 2.5, 6.0, 12.0, 16.0}, {V_128x192_S2, 128, 192, 0.95, 8, 0.64, 5, 2.5, 5.0, 7.5, 16.0},
         {V_128x192_S3, 128, 192, 0.64, 11, 0.65, 9, 5.0, 7.5, 11.5, 22.0}, {V_128x128, 128, 128, 0.80, 6, 0.45, 6, 1.5, 3.5, 5.5, 10.0},
         {V_128x64, 128, 64, 0.76, 0, 0.31, 4, 0.4, 1.7, 2.0, 2.7},       {V_64x128_S3, 64, 128, 0.46, 9, 0.33, 4, 0.7, 2.0, 2.0, 4.6}};
     const int form = gemm_epilogue_form(a);

@@ -82,6 +82,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_tile_kernel(GemmLaunc
 #pragma unroll
   for (int s = 0; s < NSTAGE - 1; ++s)
     if (s < nk) issue(s, s);
+  ColumnBias<NI, 32, float> column_bias;
+  column_bias.fetch(epi, n0 + wn * WN + (lane & 31), N);
 
   const int l32 = lane & 31, hi = lane >> 5;
   for (int kt = 0; kt < nk; ++kt) {
@@ -113,6 +115,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_tile_kernel(GemmLaunc
     }
   }
 
+  float bias[NI];
+  column_bias.widen(bias);
   // accumulators -> row-major tile in LDS (lane -> column l32, register r -> row 8*(r/4) + 4*hi + r%4)
   float *tile = reinterpret_cast<float *>(smem);
   __syncthreads();
@@ -122,7 +126,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_f32_tile_kernel(GemmLaunc
     for (int j = 0; j < NI; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        tile[(wm * WM + i * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)) * TLD + wn * WN + j * 32 + l32] = acc[j][i][r];
+        tile[(wm * WM + i * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)) * TLD + wn * WN + j * 32 + l32] = acc[j][i][r] + bias[j];
   __syncthreads();
   tile_epilogue<EM, BM, BN, TLD, 64 * NW>(tile, m0, n0, M, N, epi, vec_ok != 0);
 }
@@ -206,6 +210,15 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_wavek_kernel(GemmLaunch<floa
       for (int j = 0; j < NI; ++j) mma8<MI>(af[ks], wf[ks][j], acc[j]);
   }
 
+  // the epilogue's operands: their latency runs under the exchange through LDS.  Residual and gate only with eight waves, that is
+  // with tiles for few of the CUs (tiny stage 43.9 -> 43.6 us a call); four waves have a neighbour on their CU to hide it
+  // (PixArt-scale fp32 call 396 -> 403 us with them, 412 with them in front of the K loop).
+  constexpr bool EPRE = EM == EM_RESIDUAL && NW == 8;
+  EpiOperands<BM, BN, NT> eops;
+  if constexpr (EPRE) eops.fetch(m0, n0, M, N, epi, vec_ok != 0);
+  ColumnBias<4, 1, float> column_bias;   // of the columns this thread sums
+  column_bias.fetch(epi, n0 + (tid % (BN / 4)) * 4, N, vec_ok != 0);
+
   // partial tiles -> LDS (each wave into its own ring), sum in wave order, epilogue
   float *part = reinterpret_cast<float *>(ring);
 #pragma unroll
@@ -216,8 +229,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_wavek_kernel(GemmLaunch<floa
       for (int r = 0; r < 16; ++r)
         part[(i * 32 + 8 * (r >> 2) + 4 * hi + (r & 3)) * TLD + j * 32 + l32] = acc[j][i][r];
   __syncthreads();
+  float bias[4];
+  column_bias.widen(bias);
   float *p0 = reinterpret_cast<float *>(smem);
   constexpr int WSTRIDE = WAVE_BYTES / 4;
+  static_assert(NT % (BN / 4) == 0, "a thread sums the same columns of every row");
   for (int e = tid; e < BM * BN / 4; e += NT) {
     const int r = e / (BN / 4), c = (e % (BN / 4)) * 4;
     float4 s0 = *reinterpret_cast<const float4 *>(p0 + r * TLD + c);
@@ -226,10 +242,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_wavek_kernel(GemmLaunch<floa
       const float4 s1 = *reinterpret_cast<const float4 *>(p0 + w * WSTRIDE + r * TLD + c);
       s0.x += s1.x; s0.y += s1.y; s0.z += s1.z; s0.w += s1.w;
     }
+    s0.x += bias[0]; s0.y += bias[1]; s0.z += bias[2]; s0.w += bias[3];
     *reinterpret_cast<float4 *>(p0 + r * TLD + c) = s0;
   }
   __syncthreads();
-  tile_epilogue<EM, BM, BN, TLD, NT>(p0, m0, n0, M, N, epi, vec_ok != 0);
+  if constexpr (EPRE) tile_epilogue<EM, BM, BN, TLD, NT, true>(p0, m0, n0, M, N, epi, vec_ok != 0, &eops);
+  else tile_epilogue<EM, BM, BN, TLD, NT>(p0, m0, n0, M, N, epi, vec_ok != 0);
 }
 
 template <int BM, int BN, int NSTAGE, int WGM, int WGN>

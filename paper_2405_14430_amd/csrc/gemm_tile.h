@@ -16,6 +16,11 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+template <int N>
+__device__ __forceinline__ void wait_lgkmcnt() {
+  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // s_waitcnt vmcnt(behind * LPS) for a wave-uniform run-time `behind` in [0, MAXB] (the count is an immediate)
 template <int LPS, int MAXB>
 __device__ __forceinline__ void wait_tiles_behind(int behind) {
@@ -112,7 +117,7 @@ __host__ __device__ __forceinline__ bool tile_of_id(int id, int tiles_m, int til
 // read and written by its own workgroup only, so reading R early is safe when the GEMM updates it in place.
 template <int BM, int BN, int NT>
 struct EpiOperands {
-  static constexpr int IT = BM * BN / 8 / NT;
+  static constexpr int GROUPS = BM * BN / 8, IT = (GROUPS + NT - 1) / NT;
   float4 r[IT][2], g[IT][2];
   bool on;
   template <typename T>
@@ -123,7 +128,7 @@ struct EpiOperands {
     for (int it = 0; it < IT; ++it) {
       const int grp = threadIdx.x + it * NT;
       const int row = m0 + grp / (BN / 8), col = n0 + (grp % (BN / 8)) * 8;
-      if (row >= M || col + 8 > N) continue;
+      if ((GROUPS % NT != 0 && grp >= GROUPS) || row >= M || col + 8 > N) continue;
       const float *rp = epi.R + (size_t)row * epi.ldr + col;
       r[it][0] = *reinterpret_cast<const float4 *>(rp); r[it][1] = *reinterpret_cast<const float4 *>(rp + 4);
       if (epi.gate) {
@@ -140,12 +145,56 @@ __device__ __forceinline__ void load8(const float *p, float *o) { Vec16<float>::
 __device__ __forceinline__ void store8(bf16_t *p, const float *o) { Vec16<bf16_t>::store(p, o); }
 __device__ __forceinline__ void store8(float *p, const float *o) { Vec16<float>::store(p, o); Vec16<float>::store(p + 4, o + 4); }
 
-// Epilogue over a finished fp32 tile held row-major in LDS (row stride TLD floats).  PRE: residual / gate operands
-// come from `ops` (fetched earlier) when ops->on.
+// Bias of columns col, col + STEP, ..., for the kernels' accumulator layouts: fetched before the K loop, because an epilogue
+// that asked for it group by group waited for a load from L2 in every one, and kept as stored until it is used: a conversion
+// that the compiler moved up to the load would wait for it in front of the loop (0.3 us of a 10 us launch).  Columns past
+// the matrix repeat its last one.
+template <int N, int STEP, typename T>
+struct ColumnBias {
+  unsigned raw[N];
+  bool pairs = false;   // raw[0] and raw[2] hold two columns each
+  // vec: four consecutive columns from a multiple of four, of an operand that is aligned for vectors
+  __device__ __forceinline__ void fetch(const Epilogue<T> &epi, int col, int cols, bool vec = false) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) raw[j] = 0;
+    if (!epi.bias) return;
+    if constexpr (N == 4 && STEP == 1) {
+      if (vec && cols % 4 == 0) {
+        const T *p = epi.bias + min(col, cols - 4);
+        if constexpr (sizeof(T) == 2) {
+          const uint2 u = *reinterpret_cast<const uint2 *>(p);
+          raw[0] = u.x, raw[2] = u.y, pairs = true;
+        } else {
+          const uint4 u = *reinterpret_cast<const uint4 *>(p);
+          raw[0] = u.x, raw[1] = u.y, raw[2] = u.z, raw[3] = u.w;
+        }
+        return;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const T *p = epi.bias + min(col + j * STEP, cols - 1);
+      if constexpr (sizeof(T) == 2) raw[j] = *reinterpret_cast<const unsigned short *>(p);
+      else raw[j] = *reinterpret_cast<const unsigned *>(p);
+    }
+  }
+  // what the epilogue adds; once, behind the loop
+  __device__ __forceinline__ void widen(float (&b)[N]) {
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      asm volatile("" : "+v"(raw[j]));
+      if (N == 4 && STEP == 1 && sizeof(T) == 2 && pairs) b[j] = __builtin_bit_cast(float, j & 1 ? raw[j & ~1] & 0xffff0000u : raw[j] << 16);
+      else b[j] = __builtin_bit_cast(float, sizeof(T) == 2 ? raw[j] << 16 : raw[j]);
+    }
+  }
+};
+
+// Epilogue over a finished fp32 tile held row-major in LDS (row stride TLD floats), its bias added.  PRE: residual / gate
+// operands come from `ops` (fetched earlier) when ops->on.
 template <int EM, int BM, int BN, int TLD, int NT = 256, bool PRE = false, typename T>
 __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0, int M, int N, const Epilogue<T> &epi, bool vec_ok, const EpiOperands<BM, BN, NT> *ops = nullptr) {
   constexpr int GROUPS = BM * BN / 8;
-  constexpr int IT = (GROUPS + NT - 1) / NT, UNR = PRE ? IT : 1;
+  constexpr int IT = (GROUPS + NT - 1) / NT;
   if constexpr (EM != EM_KV_ROUTE) {
     // Operands that are not aligned for vectors, and the columns behind the last whole group of eight: one element per thread,
     // consecutive threads along a row (eight elements of a row per thread, as in the vector passes: 512x1152x1152, unaligned
@@ -156,7 +205,7 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
       int r = threadIdx.x / width, c = c_from + threadIdx.x % width;
 #pragma unroll 1
       while (r < BM) {
-        if (m0 + r < M && c < BN && n0 + c < N) epi.apply(m0 + r, n0 + c, tile[r * TLD + c]);
+        if (m0 + r < M && c < BN && n0 + c < N) epi.put(m0 + r, n0 + c, tile[r * TLD + c]);
         r += dr;
         c += dc;
         if (c >= c_from + width) c -= width, ++r;
@@ -164,96 +213,113 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
     }
     if (!vec_ok) return;
   }
-#pragma unroll UNR
-  for (int it = 0; it < IT; ++it) {
-    const int g = threadIdx.x + it * NT;
-    if (GROUPS % NT != 0 && g >= GROUPS) break;
-    const int r = g / (BN / 8), c0 = (g % (BN / 8)) * 8;
-    const int row = m0 + r, col = n0 + c0;
-    if (row >= M || col >= N) continue;
-    const float *src = tile + r * TLD + c0;
-    float4 lo = *reinterpret_cast<const float4 *>(src), hi4 = *reinterpret_cast<const float4 *>(src + 4);
-    float v[8] = {lo.x, lo.y, lo.z, lo.w, hi4.x, hi4.y, hi4.z, hi4.w};
-    if (col + 8 > N) continue;   // (columns behind the last whole group: below)
-    if (epi.bias) {
-      float b[8];
-      load8(epi.bias + col, b);
+  // Groups of eight columns, UB of a thread at a time: what they need from memory is asked for together, since the compiler may
+  // not move a load over the store of the group before it.
+  constexpr int UB = PRE ? IT : IT < 4 ? IT : 4;
+  constexpr bool LOADS = EM == EM_RESIDUAL || EM == EM_KV_ROUTE;
+#pragma unroll 1
+  for (int it0 = 0; it0 < IT; it0 += UB) {
+    float4 q0[LOADS ? UB : 1], q1[LOADS ? UB : 1], g0[LOADS ? UB : 1], g1[LOADS ? UB : 1];   // residual and gate, or (q0, q1) RoPE table
+    auto place = [&](int u, int &r, int &c0) {   // group `it0 + u` of the thread; false: nothing to do
+      const int g = threadIdx.x + (it0 + u) * NT;
+      r = g / (BN / 8), c0 = (g % (BN / 8)) * 8;
+      return (GROUPS % (NT * UB) == 0 || g < GROUPS) && m0 + r < M && n0 + c0 + 8 <= N;   // (columns behind the last whole group: above)
+    };
+    if constexpr (LOADS) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] += b[e];
+      for (int u = 0; u < UB; ++u) {
+        int r, c0;
+        if (!place(u, r, c0)) continue;
+        const int row = m0 + r, col = n0 + c0;
+        if constexpr (EM == EM_RESIDUAL) {
+          if constexpr (PRE) {
+            if (ops->on) { q0[u] = ops->r[u][0]; q1[u] = ops->r[u][1]; g0[u] = ops->g[u][0]; g1[u] = ops->g[u][1]; continue; }
+          }
+          const float *rp = epi.R + (size_t)row * epi.ldr + col;
+          q0[u] = *reinterpret_cast<const float4 *>(rp); q1[u] = *reinterpret_cast<const float4 *>(rp + 4);
+          if (epi.gate) {
+            const float *gp = epi.gate_of(row) + col;
+            g0[u] = *reinterpret_cast<const float4 *>(gp); g1[u] = *reinterpret_cast<const float4 *>(gp + 4);
+          }
+        } else {
+          const KvRoute &kv = epi.kv;
+          if (kv.rope && col < 2 * kv.d) {
+            const int lrow = row - (kv.seg > 0 ? row / kv.seg * kv.seg : 0);
+            const float2 *tab = kv.rope + (size_t)lrow * (kv.dh >> 1) + (col % kv.dh >> 1);   // (d is a whole number of heads)
+            const float2 t0 = tab[0], t1 = tab[1], t2 = tab[2], t3 = tab[3];
+            q0[u] = make_float4(t0.x, t0.y, t1.x, t1.y); q1[u] = make_float4(t2.x, t2.y, t3.x, t3.y);
+          }
+        }
+      }
     }
-    if constexpr (EM == EM_KV_ROUTE) {
-      // QKV projection routed into the K / V^T buffers (an 8-column group never straddles q|k|v or two heads)
-      const KvRoute &kv = epi.kv;
-      const int part = col / kv.d, cc = col - part * kv.d;
-      const int hh = cc / kv.dh, ch = cc - hh * kv.dh;
-      const int img = kv.seg > 0 ? row / kv.seg : 0;
-      const int lrow = row - img * kv.seg;           // row inside its image
-      if (kv.q_norm && part < 2) {
-        // a head's dh / 8 groups of the row are consecutive, aligned lanes (the tile is a whole number of heads wide)
-        float ss = 0.f, wn[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ss = fmaf(v[e], v[e], ss);
-        for (int m = 1; m < kv.dh >> 3; m <<= 1) ss += __shfl_xor(ss, m, kWave);
-        const float rinv = rsqrtf(ss / (float)kv.dh + kv.norm_eps);
-        load8(reinterpret_cast<const T *>(part == 0 ? kv.q_norm : kv.k_norm) + ch, wn);
+    for (int u = 0; u < UB; ++u) {
+      int r, c0;
+      if (!place(u, r, c0)) continue;
+      const int row = m0 + r, col = n0 + c0;
+      const float *src = tile + r * TLD + c0;
+      float4 lo = *reinterpret_cast<const float4 *>(src), hi4 = *reinterpret_cast<const float4 *>(src + 4);
+      float v[8] = {lo.x, lo.y, lo.z, lo.w, hi4.x, hi4.y, hi4.z, hi4.w};
+      if constexpr (EM == EM_KV_ROUTE) {
+        // QKV projection routed into the K / V^T buffers (an 8-column group never straddles q|k|v or two heads)
+        const KvRoute &kv = epi.kv;
+        const int part = col / kv.d, cc = col - part * kv.d;
+        const int hh = cc / kv.dh, ch = cc - hh * kv.dh;
+        const int img = kv.seg > 0 ? row / kv.seg : 0;
+        const int lrow = row - img * kv.seg;           // row inside its image
+        if (kv.q_norm && part < 2) {
+          // a head's dh / 8 groups of the row are consecutive, aligned lanes (the tile is a whole number of heads wide)
+          float ss = 0.f, wn[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = v[e] * rinv * wn[e];
-      }
-      if (kv.rope && part < 2) {
-        const float2 *tab = kv.rope + (size_t)lrow * (kv.dh >> 1) + (ch >> 1);
+          for (int e = 0; e < 8; ++e) ss = fmaf(v[e], v[e], ss);
+          for (int m = 1; m < kv.dh >> 3; m <<= 1) ss += __shfl_xor(ss, m, kWave);
+          const float rinv = rsqrtf(ss / (float)kv.dh + kv.norm_eps);
+          load8(reinterpret_cast<const T *>(part == 0 ? kv.q_norm : kv.k_norm) + ch, wn);
 #pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          float2 cs = tab[e >> 1];
-          float a0 = v[e], b0 = v[e + 1];
-          v[e] = a0 * cs.x - b0 * cs.y;
-          v[e + 1] = a0 * cs.y + b0 * cs.x;
+          for (int e = 0; e < 8; ++e) v[e] = v[e] * rinv * wn[e];
         }
-      }
-      if (part == 0 && kv.q_scale != 0.f) {
+        if (kv.rope && part < 2) {
+          const float2 cs[4] = {{q0[u].x, q0[u].y}, {q0[u].z, q0[u].w}, {q1[u].x, q1[u].y}, {q1[u].z, q1[u].w}};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] *= kv.q_scale;
-      }
-      if (part == 0) {
+          for (int e = 0; e < 8; e += 2) {
+            float a0 = v[e], b0 = v[e + 1];
+            v[e] = a0 * cs[e >> 1].x - b0 * cs[e >> 1].y;
+            v[e + 1] = a0 * cs[e >> 1].y + b0 * cs[e >> 1].x;
+          }
+        }
+        if (part == 0 && kv.q_scale != 0.f) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] *= kv.q_scale;
+        }
+        if (part == 0) {
+          store8(reinterpret_cast<T *>(epi.C) + (size_t)row * epi.ldc + col, v);
+        } else if (part == 1) {
+          const int brow = lrow < kv.split ? kv.row0a + lrow : kv.row0b + (lrow - kv.split);
+          store8(reinterpret_cast<T *>(kv.kbuf) + (size_t)img * kv.img_stride + ((size_t)hh * kv.Lp + brow) * kv.dh + ch, v);
+        }
+        // part 2 (v) is written by the transposed pass below
+      } else if constexpr (EM == EM_STORE || EM == EM_STORE_ERF) {
+        if (col + 8 > epi.gelu_from) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (col + e >= epi.gelu_from) v[e] = gelu_f(v[e], EM != EM_STORE_ERF);
+        }
         store8(reinterpret_cast<T *>(epi.C) + (size_t)row * epi.ldc + col, v);
-      } else if (part == 1) {
-        const int brow = lrow < kv.split ? kv.row0a + lrow : kv.row0b + (lrow - kv.split);
-        store8(reinterpret_cast<T *>(kv.kbuf) + (size_t)img * kv.img_stride + ((size_t)hh * kv.Lp + brow) * kv.dh + ch, v);
-      }
-      // part 2 (v) is written by the transposed pass below
-    } else if constexpr (EM == EM_STORE || EM == EM_STORE_ERF) {
-      if (col + 8 > epi.gelu_from) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-          if (col + e >= epi.gelu_from) v[e] = gelu_f(v[e], EM != EM_STORE_ERF);
-      }
-      store8(reinterpret_cast<T *>(epi.C) + (size_t)row * epi.ldc + col, v);
-    } else {
-      float4 r0, r1, g0, g1;
-      bool have = false;
-      if constexpr (PRE) {
-        if (ops->on) { r0 = ops->r[it][0]; r1 = ops->r[it][1]; g0 = ops->g[it][0]; g1 = ops->g[it][1]; have = true; }
-      }
-      if (!have) {
-        const float *rp = epi.R + (size_t)row * epi.ldr + col;
-        r0 = *reinterpret_cast<const float4 *>(rp); r1 = *reinterpret_cast<const float4 *>(rp + 4);
-        if (epi.gate) {
-          const float *gp = epi.gate_of(row) + col;
-          g0 = *reinterpret_cast<const float4 *>(gp); g1 = *reinterpret_cast<const float4 *>(gp + 4);
-        }
-      }
-      float x[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
-      if (epi.gate) {
-        float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] += gg[e] * v[e];
       } else {
+        float x[8] = {q0[u].x, q0[u].y, q0[u].z, q0[u].w, q1[u].x, q1[u].y, q1[u].z, q1[u].w};
+        if (epi.gate) {
+          float gg[8] = {g0[u].x, g0[u].y, g0[u].z, g0[u].w, g1[u].x, g1[u].y, g1[u].z, g1[u].w};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] += v[e];
+          for (int e = 0; e < 8; ++e) x[e] += gg[e] * v[e];
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) x[e] += v[e];
+        }
+        float *xp = reinterpret_cast<float *>(epi.C) + (size_t)row * epi.ldc + col;
+        *reinterpret_cast<float4 *>(xp) = make_float4(x[0], x[1], x[2], x[3]);
+        *reinterpret_cast<float4 *>(xp + 4) = make_float4(x[4], x[5], x[6], x[7]);
+        if (epi.C2) store8(epi.C2 + (size_t)row * epi.ldc2 + col, x);
       }
-      float *xp = reinterpret_cast<float *>(epi.C) + (size_t)row * epi.ldc + col;
-      *reinterpret_cast<float4 *>(xp) = make_float4(x[0], x[1], x[2], x[3]);
-      *reinterpret_cast<float4 *>(xp + 4) = make_float4(x[4], x[5], x[6], x[7]);
-      if (epi.C2) store8(epi.C2 + (size_t)row * epi.ldc2 + col, x);
     }
   }
   // v columns of a routed QKV projection: V^T[h][c][buffer row].  The tile is walked column-wise, eight consecutive
@@ -267,10 +333,10 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
     const KvRoute &kv = epi.kv;
     constexpr int RG = BM / 8;
     auto buffer_row = [&](int lrow) { return lrow < kv.split ? kv.row0a + lrow : kv.row0b + (lrow - kv.split); };
-    auto put = [&](int r, int cl, float b) {   // one element: tile row r, column cl
+    auto put = [&](int r, int cl) {   // one element: tile row r, column cl
       const int row = m0 + r, img = kv.seg > 0 ? row / kv.seg : 0;
       reinterpret_cast<T *>(kv.vtbuf)[(size_t)img * kv.img_stride + (size_t)(n0 + cl - 2 * kv.d) * kv.Lp + buffer_row(row - img * kv.seg)] =
-          (T)(tile[r * TLD + cl] + b);
+          (T)tile[r * TLD + cl];
     };
     const int lrow0 = m0 - (kv.seg > 0 ? m0 / kv.seg * kv.seg : 0);
     const int first = -buffer_row(lrow0) & 7;   // tile row of the first group
@@ -280,10 +346,9 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
       for (int u = threadIdx.x; u < RG * BN; u += NT) {
         const int r = u % RG * 8, cl = u / RG, col = n0 + cl;
         if (col >= N || col < 2 * kv.d) continue;
-        const float b = epi.bias ? (float)epi.bias[col] : 0.f;
         float o[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = tile[(r + e) * TLD + cl] + b;
+        for (int e = 0; e < 8; ++e) o[e] = tile[(r + e) * TLD + cl];
         store8(vt + (size_t)(col - 2 * kv.d) * kv.Lp + r, o);
       }
       return;
@@ -292,25 +357,24 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
       const int r = u % RG * 8 + first, cl = u / RG;
       const int col = n0 + cl, row = m0 + r;
       if (col >= N || col < 2 * kv.d || row >= M || r + 8 > BM) continue;
-      const float b = epi.bias ? (float)epi.bias[col] : 0.f;
       const int img = kv.seg > 0 ? row / kv.seg : 0;
       const int lrow = row - img * kv.seg, brow = buffer_row(lrow);
       const bool whole = row + 8 <= M && (kv.seg <= 0 || lrow + 8 <= kv.seg) && (lrow >= kv.split || lrow + 8 <= kv.split);
       if (whole && (brow & 7) == 0) {
         float o[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = tile[(r + e) * TLD + cl] + b;
+        for (int e = 0; e < 8; ++e) o[e] = tile[(r + e) * TLD + cl];
         store8(reinterpret_cast<T *>(kv.vtbuf) + (size_t)img * kv.img_stride + (size_t)(col - 2 * kv.d) * kv.Lp + brow, o);   // (col - 2d = h*dh + c)
       } else {
 #pragma unroll 1
-        for (int e = 0; e < 8 && row + e < M; ++e) put(r + e, cl, b);
+        for (int e = 0; e < 8 && row + e < M; ++e) put(r + e, cl);
       }
     }
     if (first != 0)
       for (int u = threadIdx.x; u < 8 * BN; u += NT) {
         const int e = u & 7, cl = u >> 3, col = n0 + cl;
         const int r = e < first ? e : BM - 8 + e;
-        if (col < N && col >= 2 * kv.d && m0 + r < M) put(r, cl, epi.bias ? (float)epi.bias[col] : 0.f);
+        if (col < N && col >= 2 * kv.d && m0 + r < M) put(r, cl);
       }
   }
 }
