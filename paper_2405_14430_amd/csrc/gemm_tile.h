@@ -85,7 +85,7 @@ template <typename T, int NP>
 struct GemmLaunch {
   GemmProblem<T> p[NP];
   int N, K;
-  unsigned grid0;
+  unsigned grid0, grid;   // workgroups of the first problem, of all
 };
 
 // Workgroup id -> output tile.  Workgroup ids are dealt round-robin to the 8 XCDs, each with its own L2, so XCD x runs
@@ -435,7 +435,7 @@ inline unsigned make_launch(const GemmArgs &a, const GemmArgs *b, int BM, int BN
     if (i == 0) L->grid0 = grid;
     total += grid;
   }
-  L->N = a.N; L->K = a.K;
+  L->N = a.N; L->K = a.K; L->grid = total;
   return total;
 }
 
