@@ -8,8 +8,8 @@
 // beyond M (or N) are clamped to the last valid row: they only feed accumulators that the epilogue never stores.
 //
 // Two kernels share that machinery:
-//  * gemm_tile_kernel<BM,BN,NSTAGE>: 2x2 wavefronts share one BM x BN tile; NSTAGE LDS stages, one s_barrier per K
-//    tile.  For GEMMs with enough tiles to fill the chip.
+//  * gemm_tile_kernel<BM,BN,NSTAGE>: WGM x WGN wavefronts share one BM x BN tile.  For GEMMs with enough tiles to fill the
+//    chip.  K loops: rings of whole K tiles here, operand rings in gemm_ring.h, half tiles in gemm_half_tiles.h.
 //  * gemm_wavek_kernel<BM,BN>: for skinny GEMMs (n = 512 patch rows: a few hundred tiles at most).  The four
 //    wavefronts of a workgroup split K between them: each streams its own K tiles through a private two-stage LDS
 //    ring with no workgroup barrier in the loop, which quadruples the loads in flight per CU and divides the serial
@@ -493,29 +493,29 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 // against 65).  us, fill (the start-up, in K tiles) and the epilogues' us are fitted to isolated GEMMs with cold weights, the K/V
 // route's to QKV launches inside stages: 290 shapes of 64 .. 16384 rows at widths of 384 .. 3072, each with every tile.  us1 and
 // fill1 hold where one workgroup has a CU to itself; an epilogue weighs most where no second one runs beside it.  Over these
-// shapes the choice is 0.9 % (K/V route: 1.4 %) off the fastest tile on average, 18 % at most.  Measured (us; * = chosen):
-//                                  256x256  256x192  256x128  128x192 3-stage  128x128   128x64   64x128
-//    2048 x  9216 x  3072 store         152      129      139     118*      120      132      153      167
-//    2048 x 12288 x  3072 GELU          167     150*      160      154      175      154      196      207
-//    2048 x  3072 x 15360 residual      347      317      215      238     191*      220      249      296
-//    2560 x  9216 x  3072 store         156     140*      150      145      159      146      193      204
-//    2560 x 12288 x  3072 GELU         179*      204      205      192      218      197      247      258
-//    2560 x  3072 x 15360 residual      352      318     238*      279      320      241      364      340
-//   16896 x  9216 x  3072 store        850*      916      967      881      989      944     1178     1215
-//   16896 x 12288 x  3072 GELU        1168*     1264     1346     1212     1413     1298     1572     1663
-//   16896 x  3072 x 15360 residual     1599     1750     1692    1573*     1681     1720     2074     2216
-//    4096 x  3456 x  1152 store       38.5*     52.3     43.3     46.3     54.1     41.1     48.5     51.9
-//    4096 x  4608 x  1152 GELU         78.7     66.8     71.1    61.4*     71.9     65.9     65.4     74.9
-//    4096 x  1152 x  4608 residual      114      104     68.3     79.2    61.2*     69.7     69.8     87.0
-//    4096 x  1152 x  1152 residual     42.5     33.3     26.4     26.8     24.6     24.5    23.4*     28.8
-//    2882 x  2048 x 10240 residual      224      181     142*      187      202      145      161      196
+// shapes the choice was 0.9 % (K/V route: 1.4 %) off the fastest tile on average, 18 % at most; the constants of 256x256, 256x192,
+// 256x128 and 128x192 were then lowered to what their loops of gemm_half_tiles.h and gemm_ring.h take.  Measured (us; * = chosen):
+//                                   256x256  256x192  256x128  128x192  3-stage  128x128   128x64   64x128
+//    2048 x  9216 x  3072 store         134      115      124     108*      116      132      153      167
+//    2048 x 12288 x  3072 GELU          152     140*      147      146      171      175      196      207
+//    2048 x  3072 x 15360 residual      273      240      190      240     185*      220      249      296
+//    2560 x  9216 x  3072 store         135     126*      134      133      150      159      193      204
+//    2560 x 12288 x  3072 GELU         165*                                          218      247      258
+//    2560 x  3072 x 15360 residual                       212*               279      320      364      340
+//   16896 x  9216 x  3072 store        765*      826      873      830      948      944     1178     1215
+//   16896 x 12288 x  3072 GELU        1067*     1155     1227     1141     1387     1413     1572     1663
+//   16896 x  3072 x 15360 residual    1423*     1547     1524     1528     1661     1681     2074     2216
+//    4096 x  3456 x  1152 store       34.7*     48.9     41.9     46.1     51.2     54.1     48.5     51.9
+//    4096 x  4608 x  1152 GELU         69.3     62.1     65.2    57.7*     69.0     66.0     65.4     74.9
+//    4096 x  1152 x  4608 residual                                        50.3*     59.2     66.6     80.6
+//    4096 x  1152 x  1152 residual                                        25.3*     23.5     25.5     29.6
 // The three-stage 128x192 tile issues its prefetch loads one at a time between the MFMAs (instead of in a burst behind the
 // barrier): 2048x3072x15360 204 -> 183 us, 4096x1152x4608 65 -> 55 us; every other tile loses by it or keeps nothing of the
 // gain inside a stage.
 //
 // Fewer tiles (patches of a few hundred rows), by counts of 64x64 tiles:
 //  * the wave-split-K kernel, one workgroup per CU (128 KB of LDS): up to one tile per CU, from K = 1024 on.  512x1152x1152
-//    8.2 us (four-stage 64x64: 8.9), 512x1152x4608 19.8 (23.6), 512x1536x6144 25.5 (31.5); with more tiles than CUs it loses:
+//    8.2 us (four-stage 64x64: 8.9), 512x1152x4608 19.8 (23.6; both before idle CUs read ahead), 512x1536x6144 25.5 (31.5); with more tiles than CUs it loses:
 //    1024x1152x4608 34.3 (29.4) - until the second round of its workgroups is nearly full too and K is long: 633x3072x15360
 //    106.8 (120.1; 432 tiles: 103.0 against 93.7), 1275x1536x6144 46.0 (50.5), 633x3072x3072 28.2 (29.0), 1275x1536x1536 17.5 (14.9).
 //  * 64x64 with four stages while every workgroup of the padded grid is resident at once (two per CU), 375x4608x1536 14.0 us
