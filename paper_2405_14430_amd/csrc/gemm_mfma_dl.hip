@@ -31,16 +31,17 @@ constexpr int ROW_BYTES = BK * 2;  // 128
 // WGM x WGN wavefronts on one shared tile
 // ------------------------------------------------------------------------------------------------------------------
 
-// K loops of gemm_tile_kernel.  256x256: half tiles refilled one by one (gemm_half_tiles.h).  The other tiles of at least 128x192 and
+// K loops of gemm_tile_kernel.  256x256: half tiles refilled one by one (gemm_half_tiles.h).  The other tiles of at least
 // 256x128: a ring for either operand, NSTAGE K tiles of A and loop_depth_w of W deep, as LDS allows (gemm_ring.h).  Below, and for
 // the one-round 128x192 tile (SPREAD): one ring of whole K tiles (this file).  us with this file's loop -> with the other:
-//    2048x9216x3072   128x192 two stages 109 -> 108, 256x192 135 -> 115     2048x12288x3072 GELU   256x192 154 -> 140
+//    2048x9216x3072   256x192 135 -> 115     2048x12288x3072 GELU   256x192 154 -> 140
 //    2560x3072x15360 residual   256x128 240 -> 212                          16896x9216x3072   256x256 850 -> 765
-// and where the ring is not used: 2048x3072x15360 residual, 128x192 three stages 185, ring of four 188; 4096x1152x4608 residual,
+// and where the ring is not used: 2048x9216x3072, 128x192 two stages 109, ring of two 108, but 125 and 134 inside the Flux-scale stage,
+// whose weights are cold (two K tiles deep, the ring asks for W a quarter of a K tile later); 2048x3072x15360 residual, 128x192 three stages 185, ring of four 188; 4096x1152x4608 residual,
 // 128x128 59, ring 64; 1024x4608x1152 GELU, 128x64 21.4, ring 24.4; 512x4608x1536 GELU, 64x128 18.2, ring 18.6.
 constexpr bool loop_half_tiles(int BM, int BN) { return BM == 256 && BN == 256; }
 constexpr int loop_depth_w(int BM, int BN, int NSTAGE, bool SPREAD) {
-  if (SPREAD || loop_half_tiles(BM, BN) || BM * BN < 128 * 192) return 0;
+  if (SPREAD || loop_half_tiles(BM, BN) || BM * BN < 256 * 128) return 0;
   return BM == 256 ? 4 : NSTAGE;
 }
 
@@ -493,20 +494,20 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 // against 65).  us, fill (the start-up, in K tiles) and the epilogues' us are fitted to isolated GEMMs with cold weights, the K/V
 // route's to QKV launches inside stages: 290 shapes of 64 .. 16384 rows at widths of 384 .. 3072, each with every tile.  us1 and
 // fill1 hold where one workgroup has a CU to itself; an epilogue weighs most where no second one runs beside it.  Over these
-// shapes the choice was 0.9 % (K/V route: 1.4 %) off the fastest tile on average, 18 % at most; the constants of 256x256, 256x192,
-// 256x128 and 128x192 were then lowered to what their loops of gemm_half_tiles.h and gemm_ring.h take.  Measured (us; * = chosen):
+// shapes the choice was 0.9 % (K/V route: 1.4 %) off the fastest tile on average, 18 % at most; the constants of 256x256, 256x192
+// and 256x128 were then set to what their loops of gemm_half_tiles.h and gemm_ring.h take.  Measured (us; * = chosen):
 //                                   256x256  256x192  256x128  128x192  3-stage  128x128   128x64   64x128
-//    2048 x  9216 x  3072 store         134      115      124     108*      116      132      153      167
-//    2048 x 12288 x  3072 GELU          152     140*      147      146      171      175      196      207
-//    2048 x  3072 x 15360 residual      273      240      190      240     185*      220      249      296
-//    2560 x  9216 x  3072 store         135     126*      134      133      150      159      193      204
+//    2048 x  9216 x  3072 store         134      115      124     109*      116      132      153      167
+//    2048 x 12288 x  3072 GELU          152     140*      147      151      171      175      196      207
+//    2048 x  3072 x 15360 residual      273      240      190      237     185*      220      249      296
+//    2560 x  9216 x  3072 store         135     126*      134      137      150      159      193      204
 //    2560 x 12288 x  3072 GELU         165*                                          218      247      258
 //    2560 x  3072 x 15360 residual                       212*               279      320      364      340
-//   16896 x  9216 x  3072 store        765*      826      873      830      948      944     1178     1215
-//   16896 x 12288 x  3072 GELU        1067*     1155     1227     1141     1387     1413     1572     1663
-//   16896 x  3072 x 15360 residual    1423*     1547     1524     1528     1661     1681     2074     2216
-//    4096 x  3456 x  1152 store       34.7*     48.9     41.9     46.1     51.2     54.1     48.5     51.9
-//    4096 x  4608 x  1152 GELU         69.3     62.1     65.2    57.7*     69.0     66.0     65.4     74.9
+//   16896 x  9216 x  3072 store        765*      826      873      859      948      944     1178     1215
+//   16896 x 12288 x  3072 GELU        1067*     1155     1227     1200     1387     1413     1572     1663
+//   16896 x  3072 x 15360 residual    1423*     1547     1524     1551     1661     1681     2074     2216
+//    4096 x  3456 x  1152 store       34.7*     48.9     41.9     44.0     51.2     54.1     48.5     51.9
+//    4096 x  4608 x  1152 GELU         69.3     62.1     65.2    55.3*     69.0     66.0     65.4     74.9
 //    4096 x  1152 x  4608 residual                                        50.3*     59.2     66.6     80.6
 //    4096 x  1152 x  1152 residual                                        25.3*     23.5     25.5     29.6
 // The three-stage 128x192 tile issues its prefetch loads one at a time between the MFMAs (instead of in a burst behind the
@@ -544,7 +545,7 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
     struct Candidate { int v, bm, bn; double us1, fill1, us, fill, gelu, residual, route, odd; };   // us1, fill1: one round
     static constexpr Candidate cand[] = {
         {V_256x256, 256, 256, 1.12, 8, 1.44, 4, 4.0, 10.0, 12.0, 31.0},   {V_256x192_S2, 256, 192, 0.95, 6, 1.17, 5, 4.5, 9.0, 12.0, 27.0},
-        {V_256x128_S3, 256, 128, 0.77, 9, 0.85, 5, 2.5, 6.0, 12.0, 16.0}, {V_128x192_S2, 128, 192, 0.95, 8, 0.64, 5, 2.5, 5.0, 7.5, 16.0},
+        {V_256x128_S3, 256, 128, 0.77, 9, 0.85, 5, 2.5, 6.0, 16.0, 16.0}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 2.5, 5.0, 8.5, 16.0},
         {V_128x192_S3, 128, 192, 0.64, 11, 0.65, 9, 5.0, 7.5, 11.5, 22.0}, {V_128x128, 128, 128, 0.80, 6, 0.45, 6, 1.5, 3.5, 5.5, 10.0},
         {V_128x64, 128, 64, 0.76, 0, 0.31, 4, 0.4, 1.7, 2.0, 2.7},       {V_64x128_S3, 64, 128, 0.46, 9, 0.33, 4, 0.7, 2.0, 2.0, 4.6}};
     const int form = gemm_epilogue_form(a);

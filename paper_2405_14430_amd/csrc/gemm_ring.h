@@ -1,4 +1,4 @@
-// bf16 MFMA GEMM body of the 256x192, 256x128 and (two workgroups per CU) 128x192 tiles: C = epilogue(A W^T + bias), K a multiple of 64.
+// bf16 MFMA GEMM body of the 256x192 and 256x128 tiles: C = epilogue(A W^T + bias), K a multiple of 64.
 //
 // WGM x WGN wavefronts on one tile; a ring of DA K tiles (64 wide) of A and one of DW of W in LDS, the deeper one for W because
 // its rows come from farther away (nothing has read a layer's weights since the last call).  A K tile is four slices of 16:
@@ -7,7 +7,7 @@
 // there on, and the next tile has landed for every wave, whose first slice is read next.
 //
 // What bounds it: power and, for the smaller tiles, the path from the L2s into the CUs (gemm_mfma_dl.hip has the figures of the
-// loop it replaces).  2048x12288x3072 GELU, 256x192: 154 -> 140 us; 2048x9216x3072, 256x192 135 -> 115, 128x192 109 -> 108;
+// loop it replaces).  2048x12288x3072 GELU, 256x192: 154 -> 140 us; 2048x9216x3072, 256x192 135 -> 115;
 // 2560x3072x15360 residual, 256x128: 240 -> 212 us.  Four waves with a quarter of a 256x256 tile each (128 KB of fragment
 // reads a K tile instead of 192) multiply 2 - 5 % faster but finish a tile 10 us later: one wave per SIMD has nothing beside
 // its epilogue's latencies (16896x12288x3072 GELU 1132 us against 1033).

@@ -219,7 +219,7 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
   constexpr bool LOADS = EM == EM_RESIDUAL || EM == EM_KV_ROUTE;
 #pragma unroll 1
   for (int it0 = 0; it0 < IT; it0 += UB) {
-    float4 q0[LOADS ? UB : 1], q1[LOADS ? UB : 1], g0[LOADS ? UB : 1], g1[LOADS ? UB : 1];   // residual and gate, or (q0, q1) RoPE table
+    float4 q0[LOADS ? UB : 1], q1[LOADS ? UB : 1], g0[LOADS ? UB : 1], g1[LOADS ? UB : 1];   // residual and gate, or RoPE table (q0, q1) and norm scales (g0)
     auto place = [&](int u, int &r, int &c0) {   // group `it0 + u` of the thread; false: nothing to do
       const int g = threadIdx.x + (it0 + u) * NT;
       r = g / (BN / 8), c0 = (g % (BN / 8)) * 8;
@@ -249,6 +249,10 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
             const float2 t0 = tab[0], t1 = tab[1], t2 = tab[2], t3 = tab[3];
             q0[u] = make_float4(t0.x, t0.y, t1.x, t1.y); q1[u] = make_float4(t2.x, t2.y, t3.x, t3.y);
           }
+          if constexpr (sizeof(T) == 2) {   // scales of the per-head norm, as stored
+            if (kv.q_norm && col < 2 * kv.d)
+              g0[u] = *reinterpret_cast<const float4 *>(reinterpret_cast<const T *>(col < kv.d ? kv.q_norm : kv.k_norm) + col % kv.dh);
+          }
         }
       }
     }
@@ -274,7 +278,13 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
           for (int e = 0; e < 8; ++e) ss = fmaf(v[e], v[e], ss);
           for (int m = 1; m < kv.dh >> 3; m <<= 1) ss += __shfl_xor(ss, m, kWave);
           const float rinv = rsqrtf(ss / (float)kv.dh + kv.norm_eps);
-          load8(reinterpret_cast<const T *>(part == 0 ? kv.q_norm : kv.k_norm) + ch, wn);
+          if constexpr (sizeof(T) == 2) {
+            const bf16x8 w = __builtin_bit_cast(bf16x8, g0[u]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) wn[e] = (float)w[e];
+          } else {
+            load8(reinterpret_cast<const T *>(part == 0 ? kv.q_norm : kv.k_norm) + ch, wn);
+          }
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] = v[e] * rinv * wn[e];
         }
