@@ -16,6 +16,8 @@
 //    chain of K iterations by four; the four partial tiles are then summed through LDS.
 // Both finish through LDS: the fp32 tile is laid out row-major and every thread applies the epilogue to runs of 8
 // consecutive columns (16-byte bf16 stores, 32-byte fp32 stores).
+#include <algorithm>
+
 #include "gemm_half_tiles.h"
 #include "gemm_ring.h"
 #include "gemm_tile.h"
@@ -240,27 +242,40 @@ __global__ __launch_bounds__(64 * WGM * WGN, NSTAGE * (BM + BN) * ROW_BYTES <= 8
 // Workgroups behind the tiles of a launch that leaves CUs idle: they read the rows of their XCD's block of the tile grid (see
 // tile_of_id) ahead of the workgroups that multiply, K tile by K tile, two words of every 128-byte row piece, so that the tile loads
 // find them in the XCD's L2.  The weights of a stage's GEMMs come from the memory-side cache or HBM, and a CU that waits for
-// them takes in 60 bytes a ns, half of what it gets from its L2.  PixArt-scale call (144 tiles) 473 -> 456 us, with reads ahead for
-// K = 4608 only 469 -> 458; SD3-scale (192 tiles) 363 -> 358.  Launches of two problems lose by it (SD3-scale with 77 text rows
-// 245 -> 267 us: every XCD has blocks of two matrices to read) and do without.
-template <int BM, int BN, int NP>
-__device__ void read_ahead(const GemmLaunch<bf16_t, NP> &L) {
+// them takes in 60 bytes a ns, half of what it gets from its L2.  A reader asks for READ_AHEAD_LOADS words a thread at a time and
+// takes 1 - 1.2 us for a K tile of 576 rows (one word at a time: 2 us).  us of a launch without readers, with:
+//   512x1152x4608 residual (12 per XCD)   20.8, 16.1      512x1152x1152 (12)   9.2, 8.2      375x1536x6144 (14)   26.7, 21.3
+//   512x1536x6144 (8)   27.5, 22.7      64x3072x15360 (16)   74.5, 50.5
+// PixArt-scale call (144 tiles) 471 -> 441, SD3-scale (192 tiles) 364 -> 346.
+// The launch lasts until the readers are through, so how many there are is bounded (gemm_read_ahead_workgroups).  Launches of two
+// problems lose by them (SD3-scale with 77 text rows 245 -> 267 us: every XCD has blocks of two matrices to read) and do without.
+// Readers hold a CU each, which a launch on another stream does not get meanwhile: a call each of two PixArt-scale stages on two
+// streams takes 652 us with them and 673 without, of two SD3-scale stages 714 and 748, sixteen PixArt-scale calls beside a Flux-scale
+// one 12395 and 12400.
+constexpr int READ_AHEAD_LOADS = 6;
+
+template <int BM, int BN>
+__device__ void read_ahead(const GemmLaunch<bf16_t, 1> &L) {
+  const GemmProblem<bf16_t> &p = L.p[0];
   const int x = blockIdx.x & 7, first = (int)((blockIdx.x - L.grid) >> 3), step = (int)((gridDim.x - L.grid) >> 3);
-  const int nk = L.K / BK;
+  const int gx = p.xcd_gx & 255, tiles_m = (p.M + BM - 1) / BM, tiles_n = (L.N + BN - 1) / BN;
+  const int bm = (tiles_m + gx - 1) / gx, bn = (tiles_n + 8 / gx - 1) / (8 / gx);
+  const int w0 = min(L.N, (x / gx) * bn * BN), w_rows = min(L.N, (x / gx + 1) * bn * BN) - w0;
+  const int a0 = min(p.M, (x % gx) * bm * BM), a_rows = min(p.M, (x % gx + 1) * bm * BM) - a0;
+  const int words = 2 * (w_rows + a_rows);
   unsigned keep = 0;
-  for (int kt = first; kt < nk; kt += step) {
+  for (int kt = first; kt < L.K / BK; kt += step) {
+#pragma unroll 1
+    for (int from = threadIdx.x; from < words; from += READ_AHEAD_LOADS * 256) {
+      unsigned v[READ_AHEAD_LOADS];
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      const GemmProblem<bf16_t> &p = L.p[i];
-      const int gx = p.xcd_gx & 255, tiles_m = (p.M + BM - 1) / BM, tiles_n = (L.N + BN - 1) / BN;
-      const int bm = (tiles_m + gx - 1) / gx, bn = (tiles_n + 8 / gx - 1) / (8 / gx);
-      auto rows = [&](const bf16_t *base, int64_t ld, int from, int to) {
-#pragma unroll 4
-        for (int u = from * 2 + (int)threadIdx.x; u < to * 2; u += 256)
-          keep ^= *reinterpret_cast<const unsigned *>(base + (size_t)(u >> 1) * ld + kt * BK + (u & 1) * (BK / 2));
-      };
-      rows(p.W, p.ldw, min(L.N, (x / gx) * bn * BN), min(L.N, (x / gx + 1) * bn * BN));
-      rows(p.A, p.lda, min(p.M, (x % gx) * bm * BM), min(p.M, (x % gx + 1) * bm * BM));
+      for (int i = 0; i < READ_AHEAD_LOADS; ++i) {   // (past the last word: that one again)
+        const int u = min(from + i * 256, words - 1), r = u >> 1;
+        const bf16_t *row = r < w_rows ? p.W + (size_t)(w0 + r) * p.ldw : p.A + (size_t)(a0 + r - w_rows) * p.lda;
+        v[i] = *reinterpret_cast<const unsigned *>(row + kt * BK + (u & 1) * (BK / 2));
+      }
+#pragma unroll
+      for (int i = 0; i < READ_AHEAD_LOADS; ++i) keep ^= v[i];
     }
   }
   asm volatile("" ::"v"(keep));
@@ -268,9 +283,11 @@ __device__ void read_ahead(const GemmLaunch<bf16_t, NP> &L) {
 
 template <int NP, int EM, int BM, int BN>
 __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> L) {
-  if (blockIdx.x >= L.grid) {
-    read_ahead<BM, BN>(L);
-    return;
+  if constexpr (NP == 1) {
+    if (blockIdx.x >= L.grid) {
+      read_ahead<BM, BN>(L);
+      return;
+    }
   }
   const bool second = NP == 2 && blockIdx.x >= L.grid0;
   const GemmProblem<bf16_t> &prob = L.p[second ? 1 : 0];
@@ -421,6 +438,25 @@ bool gemm_tile_map(int M, int N, int BM, int BN, unsigned id, unsigned *grid, in
   return tile_of_id((int)id, (M + BM - 1) / BM, (N + BN - 1) / BN, gx, *tm, *tn);
 }
 
+// Readers behind the 64x64 tiles of a wave-split-K launch of one problem (see read_ahead), as many per XCD as it has idle CUs, up to
+// 16.  Every one reads 1 / readers of the K tiles, whatever K is, so too few of them, or too many rows for each, end long after the
+// multiplication would.  us without and with readers:
+//   at least five per XCD   5: 704x1152x4608 residual 20.8, 20.0   4: 256x3584x14336 60.7, 59.6, 448x2048x8192 32.2, 32.3   2: 320x3072x15360 63, 131
+//   at most sixteen         16: 64x3072x15360 74.2, 48.3 (as many as are idle, 26: 55.3; 12: 44.9), 192x3072x15360 66.1, 50.4
+//   a K tile of the block in two rounds of loads (24 tiles wide and high)   1x20 tiles: 64x10240x2560 19.8, 18.3   1x24: 64x12288x3072 22.4, 23.9
+unsigned gemm_read_ahead_workgroups(int M, int N) {
+  constexpr int CUS = 256, TILE = 64;
+  GemmArgs a{};
+  a.M = M; a.N = N;
+  unsigned grid = 0;
+  const int gx = xcd_cut(a, TILE, TILE, &grid) & 255, gy = 8 / gx;
+  if (grid >= CUS) return 0;
+  const int bm = ((M + TILE - 1) / TILE + gx - 1) / gx, bn = ((N + TILE - 1) / TILE + gy - 1) / gy;
+  const int readers = std::min((CUS - (int)grid) / 8, 16);
+  const bool two_rounds = 2 * (bm + bn) * TILE <= 2 * READ_AHEAD_LOADS * 256;
+  return readers >= 5 && two_rounds ? 8 * readers : 0;
+}
+
 namespace {
 
 // the rings, or the fp32 tile (row stride BN + 4) that replaces them for the epilogue, whichever is larger
@@ -460,8 +496,9 @@ hipError_t launch_wavek(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
     if (hipError_t e = allow_dynamic_lds<kernel, smem>(); e != hipSuccess) return e;
     GemmLaunch<bf16_t, NP> L;
     const unsigned grid = make_launch(a, b, BM, BN, &L);
-    const bool ahead = !b && grid < 256;
-    kernel<<<ahead ? 256 : grid, 256, smem, s>>>(L);   // (one workgroup per CU: those behind the tiles read ahead)
+    static_assert(BM == 64 && BN == 64, "gemm_read_ahead_workgroups");
+    const unsigned ahead = NP == 1 ? gemm_read_ahead_workgroups(a.M, a.N) : 0;
+    kernel<<<grid + ahead, 256, smem, s>>>(L);
     return hipGetLastError();
   };
   return for_launch_form(a, b, go);

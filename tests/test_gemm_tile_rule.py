@@ -84,3 +84,40 @@ def test_banded_walk_covers_every_tile_once(M, N, bm, bn):
         assert walk == order
         banded = banded or G > 1
     assert banded and seen == {(i, j) for i in range(tiles_m) for j in range(tiles_n)}
+
+
+# us of wave-split-K launches (residual; 64 rows: plain store) without workgroups that read ahead and with as many as CUs were idle, up to 16 per XCD
+READ_AHEAD = {
+    (512, 1152, 4608): (20.5, 16.1), (256, 1152, 4608): (21.5, 15.1), (64, 3072, 15360): (74.2, 48.3), (375, 1536, 6144): (26.5, 19.6),
+    (512, 1536, 6144): (26.5, 23.7), (576, 1152, 4608): (20.5, 19.0), (704, 1152, 4608): (20.8, 20.0), (64, 10240, 2560): (19.8, 18.3),
+    (768, 1152, 4608): (20.7, 39.4), (768, 1152, 1152): (9.3, 10.3), (576, 1536, 6144): (26.7, 54.5), (640, 1536, 1536): (10.7, 11.5),
+    (320, 3072, 15360): (63.3, 130.7), (320, 3072, 3072): (17.4, 20.1), (1100, 768, 3072): (15.0, 22.4), (64, 12288, 3072): (22.4, 23.9),
+}
+
+
+def _wavek_grid(lib, M, N):
+    """(workgroups of the 64x64 tiles, tile rows and columns of an XCD's block)"""
+    grid, tm, tn = C.c_uint(0), C.c_int(0), C.c_int(0)
+    lib.pf_gemm_tile_map(M, N, 64, 64, 0, C.byref(grid), C.byref(tm), C.byref(tn))
+    mine = [(tm.value, tn.value) for wg in range(0, grid.value, 8) if lib.pf_gemm_tile_map(M, N, 64, 64, wg, C.byref(grid), C.byref(tm), C.byref(tn))]
+    return grid.value, len({t[0] for t in mine}), len({t[1] for t in mine})
+
+
+@pytest.mark.parametrize("shape", list(READ_AHEAD))
+def test_reads_ahead_where_it_was_faster(shape):
+    without, with_readers = READ_AHEAD[shape]
+    assert (B.load_library().pf_gemm_read_ahead(*shape[:2]) > 0) == (with_readers < without)
+
+
+def test_read_ahead_is_bounded():
+    """Over the grids of up to a tile per CU: never more workgroups than CUs, at least five readers per XCD, and a K tile of the
+    XCD's block in two rounds of loads (each reads 1 / readers of the K tiles, and the launch lasts until it has)."""
+    lib, on = B.load_library(), 0
+    for tiles_m in range(1, 40):
+        for tiles_n in range(1, 256 // tiles_m + 1):
+            M, N = 64 * tiles_m - tiles_m % 3, 64 * tiles_n - tiles_n % 5
+            grid, rows, cols = _wavek_grid(lib, M, N)
+            ahead = lib.pf_gemm_read_ahead(M, N)
+            assert ahead % 8 == 0 and (ahead == 0 or (grid + ahead <= 256 and 5 <= ahead // 8 <= 16 and rows + cols <= 24))
+            on += ahead > 0
+    assert on > 500 and lib.pf_gemm_read_ahead(0, 64) == -6

@@ -52,3 +52,9 @@ def test_edges(tile, M, N, pad, shift):
 @pytest.mark.parametrize("M,N,K", [(64, 64, 64), (65, 1152, 1152), (512, 1152, 4608), (70, 1000, 192), (500, 1156, 1152), (1024, 1024, 1024)])
 def test_read_ahead(M, N, K):
     _check("wavek", M, N, K)
+
+
+# the most readers of an XCD and the fewest, two rounds of loads (the second one not full), XCDs without weight rows, too few readers (none), padded rows
+@pytest.mark.parametrize("M,N,K,pad", [(64, 3072, 2048, 0), (700, 1150, 1152, 0), (60, 10200, 320, 0), (200, 3456, 1152, 0), (1, 136, 512, 8), (768, 1152, 256, 0), (130, 1536, 1536, 64)])
+def test_read_ahead_readers(M, N, K, pad):
+    _check("wavek", M, N, K, pad)
