@@ -243,15 +243,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, NSTAGE * (BM + BN) * ROW_BYTES <= 8
 // tile_of_id) ahead of the workgroups that multiply, K tile by K tile, two words of every 128-byte row piece, so that the tile loads
 // find them in the XCD's L2.  The weights of a stage's GEMMs come from the memory-side cache or HBM, and a CU that waits for
 // them takes in 60 bytes a ns, half of what it gets from its L2.  A reader asks for READ_AHEAD_LOADS words a thread at a time and
-// takes 1 - 1.2 us for a K tile of 576 rows (one word at a time: 2 us).  us of a launch without readers, with:
-//   512x1152x4608 residual (12 per XCD)   20.8, 16.1      512x1152x1152 (12)   9.2, 8.2      375x1536x6144 (14)   26.7, 21.3
-//   512x1536x6144 (8)   27.5, 22.7      64x3072x15360 (16)   74.5, 50.5
-// PixArt-scale call (144 tiles) 471 -> 441, SD3-scale (192 tiles) 364 -> 346.
+// takes 1 - 1.2 us for a K tile of 576 rows (one word at a time: 2 us).  us of a launch without readers, with, weights from HBM:
+//   512x1152x4608 residual (11 per XCD)   20.5, 16.1      512x1152x1152 (11)   9.1, 8.2      375x1536x6144 (11)   26.6, 19.8
+//   512x1536x6144 (8)   26.6, 23.7      64x3072x15360 (11)   66.7, 43.7
+// PixArt-scale call (144 tiles) 410 -> 400, SD3-scale (192 tiles) 326 -> 320.
 // The launch lasts until the readers are through, so how many there are is bounded (gemm_read_ahead_workgroups).  Launches of two
 // problems lose by them (SD3-scale with 77 text rows 245 -> 267 us: every XCD has blocks of two matrices to read) and do without.
 // Readers hold a CU each, which a launch on another stream does not get meanwhile: a call each of two PixArt-scale stages on two
-// streams takes 652 us with them and 673 without, of two SD3-scale stages 714 and 748, sixteen PixArt-scale calls beside a Flux-scale
-// one 12395 and 12400.
+// streams takes 636 us with them and 656 without, of two SD3-scale stages 703 and 740, sixteen PixArt-scale calls beside a Flux-scale
+// one 12220 and 12260.
 constexpr int READ_AHEAD_LOADS = 6;
 
 template <int BM, int BN>
@@ -439,11 +439,12 @@ bool gemm_tile_map(int M, int N, int BM, int BN, unsigned id, unsigned *grid, in
 }
 
 // Readers behind the 64x64 tiles of a wave-split-K launch of one problem (see read_ahead), as many per XCD as it has idle CUs, up to
-// 16.  Every one reads 1 / readers of the K tiles, whatever K is, so too few of them, or too many rows for each, end long after the
-// multiplication would.  us without and with readers:
+// 11.  Every one reads 1 / readers of the K tiles, whatever K is, so too few of them, or too many rows for each, end long after the
+// multiplication would; too many run so far ahead that the L2 drops what they read.  us without and with readers:
 //   at least five per XCD   5: 704x1152x4608 residual 20.8, 20.0   4: 256x3584x14336 60.7, 59.6, 448x2048x8192 32.2, 32.3   2: 320x3072x15360 63, 131
-//   at most sixteen         16: 64x3072x15360 74.2, 48.3 (as many as are idle, 26: 55.3; 12: 44.9), 192x3072x15360 66.1, 50.4
-//   a K tile of the block in two rounds of loads (24 tiles wide and high)   1x20 tiles: 64x10240x2560 19.8, 18.3   1x24: 64x12288x3072 22.4, 23.9
+//   at most eleven          64x3072x15360, weights from HBM 66.7, 43.7 (8: 49.9, 26: 57.9), from the memory-side cache 45.1, 44.9 (8: 38.7, 26: 52.5);
+//                           256x1152x4608, HBM 21.7, 15.5 (8: 17.5, 22: 15.4), 320x1536x6144, memory-side cache 21.7, 18.9 (8: 20.0, 17: 21.4)
+//   a K tile of the block in two rounds of loads (24 tiles wide and high)   1x20 tiles: 64x10240x2560 19.8, 18.5   1x24: 64x12288x3072 22.4, 23.9
 unsigned gemm_read_ahead_workgroups(int M, int N) {
   constexpr int CUS = 256, TILE = 64;
   GemmArgs a{};
@@ -452,7 +453,7 @@ unsigned gemm_read_ahead_workgroups(int M, int N) {
   const int gx = xcd_cut(a, TILE, TILE, &grid) & 255, gy = 8 / gx;
   if (grid >= CUS) return 0;
   const int bm = ((M + TILE - 1) / TILE + gx - 1) / gx, bn = ((N + TILE - 1) / TILE + gy - 1) / gy;
-  const int readers = std::min((CUS - (int)grid) / 8, 16);
+  const int readers = std::min((CUS - (int)grid) / 8, 11);
   const bool two_rounds = 2 * (bm + bn) * TILE <= 2 * READ_AHEAD_LOADS * 256;
   return readers >= 5 && two_rounds ? 8 * readers : 0;
 }

@@ -86,10 +86,11 @@ def test_banded_walk_covers_every_tile_once(M, N, bm, bn):
     assert banded and seen == {(i, j) for i in range(tiles_m) for j in range(tiles_n)}
 
 
-# us of wave-split-K launches (residual; 64 rows: plain store) without workgroups that read ahead and with as many as CUs were idle, up to 16 per XCD
+# us of wave-split-K launches (residual; wide outputs of 64 rows: plain store), weights from HBM, without workgroups that read ahead and
+# with as many as CUs were idle, up to 11 per XCD
 READ_AHEAD = {
-    (512, 1152, 4608): (20.5, 16.1), (256, 1152, 4608): (21.5, 15.1), (64, 3072, 15360): (74.2, 48.3), (375, 1536, 6144): (26.5, 19.6),
-    (512, 1536, 6144): (26.5, 23.7), (576, 1152, 4608): (20.5, 19.0), (704, 1152, 4608): (20.8, 20.0), (64, 10240, 2560): (19.8, 18.3),
+    (512, 1152, 4608): (20.5, 16.1), (256, 1152, 4608): (21.7, 15.5), (64, 3072, 15360): (66.7, 43.7), (375, 1536, 6144): (26.6, 19.8),
+    (512, 1536, 6144): (26.6, 23.7), (576, 1152, 4608): (20.5, 19.0), (704, 1152, 4608): (20.8, 20.0), (64, 10240, 2560): (19.8, 18.5),
     (768, 1152, 4608): (20.7, 39.4), (768, 1152, 1152): (9.3, 10.3), (576, 1536, 6144): (26.7, 54.5), (640, 1536, 1536): (10.7, 11.5),
     (320, 3072, 15360): (63.3, 130.7), (320, 3072, 3072): (17.4, 20.1), (1100, 768, 3072): (15.0, 22.4), (64, 12288, 3072): (22.4, 23.9),
 }
@@ -110,7 +111,7 @@ def test_reads_ahead_where_it_was_faster(shape):
 
 
 def test_read_ahead_is_bounded():
-    """Over the grids of up to a tile per CU: never more workgroups than CUs, at least five readers per XCD, and a K tile of the
+    """Over the grids of up to a tile per CU: never more workgroups than CUs, five to eleven readers per XCD, and a K tile of the
     XCD's block in two rounds of loads (each reads 1 / readers of the K tiles, and the launch lasts until it has)."""
     lib, on = B.load_library(), 0
     for tiles_m in range(1, 40):
@@ -118,6 +119,6 @@ def test_read_ahead_is_bounded():
             M, N = 64 * tiles_m - tiles_m % 3, 64 * tiles_n - tiles_n % 5
             grid, rows, cols = _wavek_grid(lib, M, N)
             ahead = lib.pf_gemm_read_ahead(M, N)
-            assert ahead % 8 == 0 and (ahead == 0 or (grid + ahead <= 256 and 5 <= ahead // 8 <= 16 and rows + cols <= 24))
+            assert ahead % 8 == 0 and (ahead == 0 or (grid + ahead <= 256 and 5 <= ahead // 8 <= 11 and rows + cols <= 24))
             on += ahead > 0
     assert on > 500 and lib.pf_gemm_read_ahead(0, 64) == -6
