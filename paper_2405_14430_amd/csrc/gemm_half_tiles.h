@@ -18,9 +18,9 @@
 // LDS rows are swizzled as in gemm_mfma_dl.hip.
 //
 // What bounds it is power: 85 % of the cycles have the matrix unit busy (8192x8192x8192), at the clock the card then allows.
-// One K tile at a time behind one barrier (43 - 49 % busy) -> this: 8192x8192x8192 1063 -> 767 - 800 us (1.37 - 1.43 PFLOP/s, the
-// vendor library 690), 16896x9216x3072 850 -> 754, 16896x12288x3072 with GELU 1168 -> 1033, 16896x3072x15360 with a
-// residual 1599 -> 1402.  Waves 4-7 half a phase behind waves 0-3, one multiplying while the other reads (eight barriers a K tile):
+// One K tile at a time behind one barrier (43 - 49 % busy) -> this: 8192x8192x8192 866 -> 758 us (1.45 PFLOP/s, the vendor
+// library 683), 16896x9216x3072 847 -> 737 (724), 16896x12288x3072 with GELU 1157 -> 1031, 16896x3072x15360 with a
+// residual 1574 -> 1369.  Waves 4-7 half a phase behind waves 0-3, one multiplying while the other reads (eight barriers a K tile):
 // 1 % slower; reads in the phase that uses them: 4 % slower.
 #pragma once
 #include "gemm_tile.h"

@@ -36,11 +36,12 @@ constexpr int ROW_BYTES = BK * 2;  // 128
 // K loops of gemm_tile_kernel.  256x256: half tiles refilled one by one (gemm_half_tiles.h).  The other tiles of at least
 // 256x128: a ring for either operand, NSTAGE K tiles of A and loop_depth_w of W deep, as LDS allows (gemm_ring.h).  Below, and for
 // the one-round 128x192 tile (SPREAD): one ring of whole K tiles (this file).  us with this file's loop -> with the other:
-//    2048x9216x3072   256x192 135 -> 115     2048x12288x3072 GELU   256x192 154 -> 140
-//    2560x3072x15360 residual   256x128 240 -> 212                          16896x9216x3072   256x256 850 -> 765
-// and where the ring is not used: 2048x9216x3072, 128x192 two stages 109, ring of two 108, but 125 and 134 inside the Flux-scale stage,
-// whose weights are cold (two K tiles deep, the ring asks for W a quarter of a K tile later); 2048x3072x15360 residual, 128x192 three stages 185, ring of four 188; 4096x1152x4608 residual,
-// 128x128 59, ring 64; 1024x4608x1152 GELU, 128x64 21.4, ring 24.4; 512x4608x1536 GELU, 64x128 18.2, ring 18.6.
+//    2048x9216x3072   256x192 132 -> 113     2048x12288x3072 GELU   256x192 154 -> 136
+//    2560x3072x15360 residual   256x128 241 -> 204                          16896x9216x3072   256x256 847 -> 737
+// and where the ring is not used (two builds in one run): 2048x9216x3072, 128x192 two stages 109, ring of two 108, but 125 and 134
+// inside the Flux-scale stage, whose weights are cold (two K tiles deep, the ring asks for W a quarter of a K tile later);
+// 2048x3072x15360 residual, 128x192 three stages 185, ring of four 188; 4096x1152x4608 residual, 128x128 59, ring 64; 1024x4608x1152
+// GELU, 128x64 21.4, ring 24.4; 512x4608x1536 GELU, 64x128 18.2, ring 18.6.
 constexpr bool loop_half_tiles(int BM, int BN) { return BM == 256 && BN == 256; }
 constexpr int loop_depth_w(int BM, int BN, int NSTAGE, bool SPREAD) {
   if (SPREAD || loop_half_tiles(BM, BN) || BM * BN < 256 * 128) return 0;
@@ -529,40 +530,46 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 //   rounds x (us x (K tiles + fill) + epilogue)
 // rounds = padded grid / 256 CUs.  The grid counts, not the tiles: an XCD's block of the tile grid is padded to whole rows and
 // columns, and 52 x 9 tiles of 64x128 cut into blocks of 13 x 5 take one more round than fits on every XCD (3306x1152x4608: 85 us
-// against 65).  us, fill (the start-up, in K tiles) and the epilogues' us are fitted to isolated GEMMs with cold weights, the K/V
-// route's to QKV launches inside stages: 290 shapes of 64 .. 16384 rows at widths of 384 .. 3072, each with every tile.  us1 and
-// fill1 hold where one workgroup has a CU to itself; an epilogue weighs most where no second one runs beside it.  Over these
-// shapes the choice was 0.9 % (K/V route: 1.4 %) off the fastest tile on average, 18 % at most; the constants of 256x256, 256x192
-// and 256x128 were then set to what their loops of gemm_half_tiles.h and gemm_ring.h take.  Measured (us; * = chosen):
+// against 65).  us, fill (the start-up, in K tiles) and the epilogues' us are fitted (least squares of the relative error) to
+// isolated GEMMs whose weights no cache holds, each shape with every tile: those of 256x256, 256x192 and 256x128 to 330 shapes of
+// 259 .. 16896 rows at widths of 384 .. 3072, the others to 290 such shapes of an earlier run, whose mean they still meet within 5 %
+// (64x128, 6 % low on plain stores, has fill and us raised until 431x9216x3072 goes to the three-stage tile, 38 us against 44).  us1
+// and fill1 hold where one workgroup has a CU to itself; an epilogue weighs most where no second one runs beside it.  The K/V
+// route's us are what 30 QKV launches inside stages (812 .. 16896 rows; with and without per-head norm and RoPE) take beyond that, the
+// median per round; for 256x128 a unit more, which puts it behind 256x256 at 2560x9216x3072 with norm (181 us against 171).
+// Over 450 shapes (120 of them not of the fit) the choice is 0.9 % off the fastest tile on average, 24 % at most (128x64 in two rounds
+// of long K: 1956x2048x8192 residual 99 us, 64x128 80); over the QKV launches 1.3 %, 16 % at most.  Measured (us; * = chosen):
 //                                   256x256  256x192  256x128  128x192  3-stage  128x128   128x64   64x128
-//    2048 x  9216 x  3072 store         134      115      124     109*      116      132      153      167
-//    2048 x 12288 x  3072 GELU          152     140*      147      151      171      175      196      207
-//    2048 x  3072 x 15360 residual      273      240      190      237     185*      220      249      296
-//    2560 x  9216 x  3072 store         135     126*      134      137      150      159      193      204
-//    2560 x 12288 x  3072 GELU         165*                                          218      247      258
-//    2560 x  3072 x 15360 residual                       212*               279      320      364      340
-//   16896 x  9216 x  3072 store        765*      826      873      859      948      944     1178     1215
-//   16896 x 12288 x  3072 GELU        1067*     1155     1227     1200     1387     1413     1572     1663
-//   16896 x  3072 x 15360 residual    1423*     1547     1524     1551     1661     1681     2074     2216
-//    4096 x  3456 x  1152 store       34.7*     48.9     41.9     44.0     51.2     54.1     48.5     51.9
-//    4096 x  4608 x  1152 GELU         69.3     62.1     65.2    55.3*     69.0     66.0     65.4     74.9
-//    4096 x  1152 x  4608 residual                                        50.3*     59.2     66.6     80.6
-//    4096 x  1152 x  1152 residual                                        25.3*     23.5     25.5     29.6
+//    2048 x  9216 x  3072 store          131      113      121     114*      115      130      146      160
+//    2048 x 12288 x  3072 GELU           146     136*      145      151      171      154      201      212
+//    2048 x  3072 x 15360 residual       271      241      186      245     181*      220      241      293
+//    2560 x  9216 x  3072 store          135     122*      132      137      150      138      188      198
+//    2560 x 12288 x  3072 GELU          159*      187      183      187      210      193      242      257
+//    2560 x  3072 x 15360 residual       284      252     204*      305      319      227      377      333
+//   16896 x  9216 x  3072 store         737*      803      853      831      940      900     1132     1175
+//   16896 x 12288 x  3072 GELU         1031*     1121     1193     1157     1363     1233     1511     1604
+//   16896 x  3072 x 15360 residual     1369*     1508     1517     1544     1655     1677     2050     2214
+//    4096 x  3456 x  1152 store        33.7*     47.9     41.4     45.0     50.9     40.0     48.6     52.1
+//    4096 x  4608 x  1152 GELU          67.3     60.2     63.6    57.3*     67.3     63.7     61.9     72.3
+//    4096 x  1152 x  4608 residual      90.5     80.1     61.9     78.0    58.4*     67.2     69.1     85.4
+//    4096 x  1152 x  1152 residual      35.9     32.0     25.2     28.7     24.3     25.0    26.0*     30.2
+//    2882 x  2048 x 10240 residual       178      163     118*      196      200      141      160      192
 // The three-stage 128x192 tile issues its prefetch loads one at a time between the MFMAs (instead of in a burst behind the
 // barrier): 2048x3072x15360 204 -> 183 us, 4096x1152x4608 65 -> 55 us; every other tile loses by it or keeps nothing of the
 // gain inside a stage.
 //
 // Fewer tiles (patches of a few hundred rows), by counts of 64x64 tiles:
 //  * the wave-split-K kernel, one workgroup per CU (128 KB of LDS): up to one tile per CU, from K = 1024 on.  512x1152x1152
-//    8.2 us (four-stage 64x64: 8.9), 512x1152x4608 19.8 (23.6; both before idle CUs read ahead), 512x1536x6144 25.5 (31.5); with more tiles than CUs it loses:
-//    1024x1152x4608 34.3 (29.4) - until the second round of its workgroups is nearly full too and K is long: 633x3072x15360
-//    106.8 (120.1; 432 tiles: 103.0 against 93.7), 1275x1536x6144 46.0 (50.5), 633x3072x3072 28.2 (29.0), 1275x1536x1536 17.5 (14.9).
-//  * 64x64 with four stages while every workgroup of the padded grid is resident at once (two per CU), 375x4608x1536 14.0 us
-//    (two stages 19.6); 1339x1536x6144, 21 x 24 tiles in a grid of 528, 65 us (64x128 54);
+//    residual 8.3 us (four-stage 64x64: 9.0), 512x1152x4608 16.1 (23.9), 512x1536x6144 22.3 (31.7), with their read-ahead (without:
+//    9.2, 20.8, 27.5), 512x1152x768 7.0 (6.9); with more tiles than CUs it loses: 1024x1152x4608 34.9 (29.1) - until the second
+//    round of its workgroups is nearly full too and K is long: 633x3072x15360 107 (121; 432 tiles: 107 against 92), 1275x1536x6144
+//    45.7 (50.0), 633x3072x3072 29.3 (28.9), 1275x1536x1536 18.5 (16.6).
+//  * 64x64 with four stages while every workgroup of the padded grid is resident at once (two per CU), 375x4608x1536 13.9 us
+//    (two stages 19.9); 1339x1536x6144, 21 x 24 tiles in a grid of 528, 64 us (64x128 52);
 //  * beyond, 64x128 with three stages under the same condition, where its rounds (of 256 tiles) are no more work than those
-//    of 64x64 tiles or K is long enough to pay for it: 1024x3456x1152 16.9 -> 15.2 us, 512x6144x1536 22.8 -> 22.0,
-//    512x4608x1536 20.3 -> 18.7 against two-stage 64x64 tiles, which take what is left (512x4608x1152 inside a stage: 15.8
-//    us, with 64x128 17.3; 512x4608x1536 with a residual and an unaligned bias 33 us, with 64x128 39).
+//    of 64x64 tiles or K is long enough to pay for it: 1024x3456x1152 14.8 us, 512x6144x1536 with GELU 20.7, 512x4608x1536 18.0, against
+//    19.4, 23.1 and 20.4 with two-stage 64x64 tiles, which take what is left (512x4608x1152 with GELU inside a stage, whose K is not
+//    long: 16.1 us, with 64x128 17.4, though alone 17.0 and 15.3; 512x4608x1536 with a residual and an unaligned bias 33 us, with 64x128 39).
 // 64x64 with three stages is there for pf_op_gemm_tile only: the rule never takes it.
 enum { V_256x256 = 0, V_64x128_S3, V_256x128_S3, V_128x128, V_128x64, V_WAVEK, V_64x64_S4, V_64x64_S3, V_64x64_S2,
        V_128x192_S2, V_256x192_S2, V_128x192_S3, V_COUNT };
@@ -582,10 +589,10 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
   if (tiles(128, 64) >= 512 || (a.K >= 4096 && tiles(256, 128) >= 128)) {
     struct Candidate { int v, bm, bn; double us1, fill1, us, fill, gelu, residual, route, odd; };   // us1, fill1: one round
     static constexpr Candidate cand[] = {
-        {V_256x256, 256, 256, 1.12, 8, 1.44, 4, 4.0, 10.0, 12.0, 31.0},   {V_256x192_S2, 256, 192, 0.95, 6, 1.17, 5, 4.5, 9.0, 12.0, 27.0},
-        {V_256x128_S3, 256, 128, 0.77, 9, 0.85, 5, 2.5, 6.0, 16.0, 16.0}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 2.5, 5.0, 8.5, 16.0},
+        {V_256x256, 256, 256, 1.07, 9.3, 1.34, 5.2, 5.3, 7.8, 16.0, 31.0}, {V_256x192_S2, 256, 192, 0.95, 9.5, 1.13, 5.6, 4.3, 6.7, 15.0, 27.0},
+        {V_256x128_S3, 256, 128, 0.71, 10.5, 0.79, 6.8, 2.6, 5.4, 16.0, 16.0}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 2.5, 5.0, 8.5, 16.0},
         {V_128x192_S3, 128, 192, 0.64, 11, 0.65, 9, 5.0, 7.5, 11.5, 22.0}, {V_128x128, 128, 128, 0.80, 6, 0.45, 6, 1.5, 3.5, 5.5, 10.0},
-        {V_128x64, 128, 64, 0.76, 0, 0.31, 4, 0.4, 1.7, 2.0, 2.7},       {V_64x128_S3, 64, 128, 0.46, 9, 0.33, 4, 0.7, 2.0, 2.0, 4.6}};
+        {V_128x64, 128, 64, 0.76, 0, 0.31, 4, 0.4, 1.7, 2.0, 2.7},       {V_64x128_S3, 64, 128, 0.46, 9, 0.34, 8, 0.7, 2.0, 2.0, 4.6}};
     const int form = gemm_epilogue_form(a);
     int best = V_128x128;
     double best_cost = 1e300;

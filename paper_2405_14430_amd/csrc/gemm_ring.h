@@ -7,8 +7,8 @@
 // there on, and the next tile has landed for every wave, whose first slice is read next.
 //
 // What bounds it: power and, for the smaller tiles, the path from the L2s into the CUs (gemm_mfma_dl.hip has the figures of the
-// loop it replaces).  2048x12288x3072 GELU, 256x192: 154 -> 140 us; 2048x9216x3072, 256x192 135 -> 115;
-// 2560x3072x15360 residual, 256x128: 240 -> 212 us.  Four waves with a quarter of a 256x256 tile each (128 KB of fragment
+// loop it replaces).  2048x12288x3072 GELU, 256x192: 154 -> 136 us; 2048x9216x3072, 256x192 132 -> 113;
+// 2560x3072x15360 residual, 256x128: 241 -> 204 us.  Four waves with a quarter of a 256x256 tile each (128 KB of fragment
 // reads a K tile instead of 192) multiply 2 - 5 % faster but finish a tile 10 us later: one wave per SIMD has nothing beside
 // its epilogue's latencies (16896x12288x3072 GELU 1132 us against 1033).
 #pragma once
