@@ -134,8 +134,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, NSTAGE * (BM + BN) * ROW_BYTES <= 8
   EpiOperands<BM, BN, 64 * NW> eops;
   if constexpr (EPRE) eops.fetch(m0, n0, M, N, epi, vec_ok != 0);
 
+  // The bias behind the loop where the ring is deeper than two: the loop's waits count tile loads, so with the bias in flight the
+  // first one would wait for a part of the next tile too.  us with the bias in front of the loop -> behind it: 576x2048x2048 13.5 -> 12.7
+  // and 22x2304x768 6.4 -> 6.0 (64x64, four stages), 1024x3456x1152 15.5 -> 15.0 (64x128), 1038x4608x1152 GELU 22.0 -> 21.7 (128x192,
+  // three).  A ring of two waits for all loads anyway: 4096x1152x1152 residual, 128x128, 22.1 in front and 22.5 behind; 2000x2304x1152,
+  // 128x64, 21.4 and 21.8; 1024x4608x1152 GELU, 64x64, 26.5 and 26.9.
+  constexpr bool BIAS_FIRST = NSTAGE == 2;
   ColumnBias<NI, 32, bf16_t> column_bias;
-  column_bias.fetch(epi, n0 + wn * WN + (lane & 31), N);
+  if constexpr (BIAS_FIRST) column_bias.fetch(epi, n0 + wn * WN + (lane & 31), N);
 
   const int l32 = lane & 31, hi = lane >> 5;
   int arow[MI], akey[MI], wrow[NI], wkey[NI];
@@ -207,6 +213,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, NSTAGE * (BM + BN) * ROW_BYTES <= 8
     });
   }
 
+  if constexpr (!BIAS_FIRST) column_bias.fetch(epi, n0 + wn * WN + (lane & 31), N);
   float bias[NI];
   column_bias.widen(bias);
   // accumulators -> row-major fp32 tile in LDS (lane -> column l32, register r -> row 8*(r/4) + 4*hi + r%4), in
@@ -354,13 +361,10 @@ __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> 
 
   constexpr bool EPRE = EM == EM_RESIDUAL && BM * BN / 8 / 256 <= 2 && BM * BN / 8 >= 256;
   EpiOperands<BM, BN, 256> eops;
-  ColumnBias<4, 1, bf16_t> column_bias;   // of the columns this thread sums
-
   if (my_nk > 0) issue(0, 0);
   if (my_nk > 1) issue(1, 1);
   // the epilogue's operands behind the first tiles, whose latency covers the address arithmetic (row / gate_seg)
   if constexpr (EPRE) eops.fetch(m0, n0, M, N, epi, vec_ok != 0);
-  column_bias.fetch(epi, n0 + (tid % (BN / 4)) * 4, N, vec_ok != 0);
 
   const int l32 = lane & 31, hi = lane >> 5;
   for (int t = 0; t < my_nk; ++t) {
@@ -396,6 +400,10 @@ __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> 
     if (t + 2 < my_nk) issue(t & 1, t + 2);
   }
 
+  // (in front of the loop, whose waits count tile loads, the bias costs: 704x1152x1152 7.6 us against 7.2, 1x12288x3072 GELU 16.8
+  // against 16.1)
+  ColumnBias<4, 1, bf16_t> column_bias;   // of the columns this thread sums
+  column_bias.fetch(epi, n0 + (tid % (BN / 4)) * 4, N, vec_ok != 0);
   float bias[4];
   column_bias.widen(bias);
   // partial tiles -> LDS (each wave into its own ring), then sum of the four and epilogue

@@ -145,8 +145,8 @@ __device__ __forceinline__ void load8(const float *p, float *o) { Vec16<float>::
 __device__ __forceinline__ void store8(bf16_t *p, const float *o) { Vec16<bf16_t>::store(p, o); }
 __device__ __forceinline__ void store8(float *p, const float *o) { Vec16<float>::store(p, o); Vec16<float>::store(p + 4, o + 4); }
 
-// Bias of columns col, col + STEP, ..., for the kernels' accumulator layouts: fetched before the K loop, because an epilogue
-// that asked for it group by group waited for a load from L2 in every one, and kept as stored until it is used: a conversion
+// Bias of columns col, col + STEP, ..., for the kernels' accumulator layouts: fetched once, in front of the K loop or behind it, because
+// an epilogue that asked for it group by group waited for a load from L2 in every one, and kept as stored until it is used: a conversion
 // that the compiler moved up to the load would wait for it in front of the loop (0.3 us of a 10 us launch).  Columns past
 // the matrix repeat its last one.
 template <int N, int STEP, typename T>
