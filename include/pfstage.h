@@ -388,9 +388,9 @@ pf_status pf_op_gemm_tile(int tile, int dtype, int path, const void *A, int64_t 
  */
 int pf_gemm_tile_map(int M, int N, int tile_m, int tile_n, unsigned workgroup, unsigned *grid, int *tm, int *tn);
 
-/* Host-only, for tests: the workgroups that a wave-split-K launch on an M x N output has behind those of its 64x64 tiles, to read
+/* Host-only, for tests: the workgroups that a wave-split-K launch on an M x N output and K has behind those of its 64x64 tiles, to read
  * operand rows into the L2s ahead of them.  A multiple of 8; 0 where the launch goes without. */
-int pf_gemm_read_ahead(int M, int N);
+int pf_gemm_read_ahead(int M, int N, int K);
 
 #ifdef __cplusplus
 }

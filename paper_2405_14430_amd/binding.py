@@ -134,7 +134,7 @@ def load_library():
     lib.pf_gemm_tile_map.restype = i32
     lib.pf_gemm_tile_map.argtypes = [i32, i32, i32, i32, C.c_uint, C.POINTER(C.c_uint), C.POINTER(i32), C.POINTER(i32)]
     lib.pf_gemm_read_ahead.restype = i32
-    lib.pf_gemm_read_ahead.argtypes = [i32, i32]
+    lib.pf_gemm_read_ahead.argtypes = [i32, i32, i32]
     lib.pf_op_gemm_tile.restype = i32
     lib.pf_op_gemm_tile.argtypes = [i32] + lib.pf_op_gemm.argtypes
     _lib = lib

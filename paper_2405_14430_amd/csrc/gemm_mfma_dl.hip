@@ -448,21 +448,25 @@ bool gemm_tile_map(int M, int N, int BM, int BN, unsigned id, unsigned *grid, in
 }
 
 // Readers behind the 64x64 tiles of a wave-split-K launch of one problem (see read_ahead), as many per XCD as it has idle CUs, up to
-// 11.  Every one reads 1 / readers of the K tiles, whatever K is, so too few of them, or too many rows for each, end long after the
+// 11, or up to 20 where the XCD's block of both operands, all of K, stays in its L2 (4 MB, the rest for what else the launch touches).
+// Every one reads 1 / readers of the K tiles, whatever K is, so too few of them, or too many rows for each, end long after the
 // multiplication would; too many run so far ahead that the L2 drops what they read.  us without and with readers:
 //   at least five per XCD   5: 704x1152x4608 residual 20.8, 20.0   4: 256x3584x14336 60.7, 59.6, 448x2048x8192 32.2, 32.3   2: 320x3072x15360 63, 131
 //   at most eleven          64x3072x15360, weights from HBM 66.7, 43.7 (8: 49.9, 26: 57.9), from the memory-side cache 45.1, 44.9 (8: 38.7, 26: 52.5);
-//                           256x1152x4608, HBM 21.7, 15.5 (8: 17.5, 22: 15.4), 320x1536x6144, memory-side cache 21.7, 18.9 (8: 20.0, 17: 21.4)
+//                           256x1152x4608 (3.9 MB), HBM 21.2, 14.4 (8: 16.1, 22: 14.9), 320x1536x6144, memory-side cache 21.7, 18.9 (8: 20.0, 17: 21.4)
+//   at most twenty          64x6144x2048 (3.25 MB), HBM 13.0, 10.8 (11: 11.9, 14: 11.3), memory-side cache 9.2, 9.9 (11: 9.8);
+//                           128x1152x4608 (3.4 MB) 22.5, 14.2 (11: 14.7) and 15.8, 13.9 (11: 13.6); 64x3072x3072 18.0, 11.6 (11: 12.1) and 12.4, 11.1 (11: 10.8)
 //   a K tile of the block in two rounds of loads (24 tiles wide and high)   1x20 tiles: 64x10240x2560 19.8, 18.5   1x24: 64x12288x3072 22.4, 23.9
-unsigned gemm_read_ahead_workgroups(int M, int N) {
-  constexpr int CUS = 256, TILE = 64;
+unsigned gemm_read_ahead_workgroups(int M, int N, int K) {
+  constexpr int CUS = 256, TILE = 64, L2_KEEPS = 3584 * 1024;
   GemmArgs a{};
   a.M = M; a.N = N;
   unsigned grid = 0;
   const int gx = xcd_cut(a, TILE, TILE, &grid) & 255, gy = 8 / gx;
   if (grid >= CUS) return 0;
   const int bm = ((M + TILE - 1) / TILE + gx - 1) / gx, bn = ((N + TILE - 1) / TILE + gy - 1) / gy;
-  const int readers = std::min((CUS - (int)grid) / 8, 11);
+  const int most = (int64_t)(bm + bn) * TILE * K * 2 <= L2_KEEPS ? 20 : 11;
+  const int readers = std::min((CUS - (int)grid) / 8, most);
   const bool two_rounds = 2 * (bm + bn) * TILE <= 2 * READ_AHEAD_LOADS * 256;
   return readers >= 5 && two_rounds ? 8 * readers : 0;
 }
@@ -507,7 +511,7 @@ hipError_t launch_wavek(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
     GemmLaunch<bf16_t, NP> L;
     const unsigned grid = make_launch(a, b, BM, BN, &L);
     static_assert(BM == 64 && BN == 64, "gemm_read_ahead_workgroups");
-    const unsigned ahead = NP == 1 ? gemm_read_ahead_workgroups(a.M, a.N) : 0;
+    const unsigned ahead = NP == 1 ? gemm_read_ahead_workgroups(a.M, a.N, a.K) : 0;
     kernel<<<grid + ahead, 256, smem, s>>>(L);
     return hipGetLastError();
   };

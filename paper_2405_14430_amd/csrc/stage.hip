@@ -880,7 +880,7 @@ int pf_gemm_tile_map(int M, int N, int tile_m, int tile_n, unsigned workgroup, u
   return pf::gemm_tile_map(M, N, tile_m, tile_n, workgroup, grid, tm, tn) ? 1 : 0;
 }
 
-int pf_gemm_read_ahead(int M, int N) { return M < 1 || N < 1 ? PF_ERR_RANGE : (int)pf::gemm_read_ahead_workgroups(M, N); }
+int pf_gemm_read_ahead(int M, int N, int K) { return M < 1 || N < 1 || K < 1 ? PF_ERR_RANGE : (int)pf::gemm_read_ahead_workgroups(M, N, K); }
 
 int pf_gemm_tile_count(void) { return gemm_mfma_dl_tile_count(); }
 

@@ -107,18 +107,27 @@ def _wavek_grid(lib, M, N):
 @pytest.mark.parametrize("shape", list(READ_AHEAD))
 def test_reads_ahead_where_it_was_faster(shape):
     without, with_readers = READ_AHEAD[shape]
-    assert (B.load_library().pf_gemm_read_ahead(*shape[:2]) > 0) == (with_readers < without)
+    assert (B.load_library().pf_gemm_read_ahead(*shape) > 0) == (with_readers < without)
 
 
 def test_read_ahead_is_bounded():
-    """Over the grids of up to a tile per CU: never more workgroups than CUs, five to eleven readers per XCD, and a K tile of the
-    XCD's block in two rounds of loads (each reads 1 / readers of the K tiles, and the launch lasts until it has)."""
+    """Over the grids of up to a tile per CU: never more workgroups than CUs, five to eleven readers per XCD (up to twenty only where
+    all of the XCD's block stays in 3.5 MB of its L2), and a K tile of the block in two rounds of loads (each reader reads 1 / readers
+    of the K tiles, and the launch lasts until it has)."""
     lib, on = B.load_library(), 0
     for tiles_m in range(1, 40):
         for tiles_n in range(1, 256 // tiles_m + 1):
             M, N = 64 * tiles_m - tiles_m % 3, 64 * tiles_n - tiles_n % 5
             grid, rows, cols = _wavek_grid(lib, M, N)
-            ahead = lib.pf_gemm_read_ahead(M, N)
-            assert ahead % 8 == 0 and (ahead == 0 or (grid + ahead <= 256 and 5 <= ahead // 8 <= 11 and rows + cols <= 24))
-            on += ahead > 0
-    assert on > 500 and lib.pf_gemm_read_ahead(0, 64) == -6
+            for K in (1024, 2048, 6144, 2 ** 31 - 64):
+                ahead, most = lib.pf_gemm_read_ahead(M, N, K), 20 if (rows + cols) * 64 * K * 2 <= 3.5 * 2 ** 20 else 11
+                assert ahead % 8 == 0 and (ahead == 0 or (grid + ahead <= 256 and 5 <= ahead // 8 <= most and rows + cols <= 24))
+                on += ahead > 0
+    assert on > 2000 and lib.pf_gemm_read_ahead(0, 64, 64) == -6 and lib.pf_gemm_read_ahead(64, 64, 0) == -6
+
+
+# us from HBM with eleven readers per XCD and with as many as CUs are idle, up to 20: short K, whose block stays in the L2, and long K
+@pytest.mark.parametrize("shape,eleven,more", [((64, 6144, 2048), 11.9, 10.8), ((64, 6144, 1536), 11.0, 10.1), ((27, 6144, 2048), 11.0, 10.4),
+                                               ((64, 3072, 15360), 43.5, 52.6), ((128, 3072, 15360), 42.1, 53.2), ((320, 1536, 6144), 18.2, 20.1)])
+def test_more_readers_where_the_l2_keeps_what_they_read(shape, eleven, more):
+    assert (B.load_library().pf_gemm_read_ahead(*shape) > 88) == (more < eleven)
