@@ -309,6 +309,9 @@ pf_status pf_op_axpby(const float *x, const float *y, float a, float b, float *o
  * large tiles, a two-stream launch is chosen by the tiles of both streams, and a QKV projection that normalises heads of 128
  * channels needs tiles of 128 or 256 columns.  Used by the benchmark to group GEMM launches by kernel. */
 const char *pf_gemm_kernel_name(int dtype, int path, int M, int N, int K);
+/* The same for the QKV projection of a bf16 stage, whose epilogue routes k and v into the buffers (qk_norm != 0: with the
+ * per-head norm); "" where the widths do not go through the MFMA kernels. */
+const char *pf_gemm_qkv_kernel_name(int rows, int hidden, int head_dim, int qk_norm);
 /* Likewise for an attention launch of nq query rows per image (q_prescaled: the stage's self-attention, whose queries
  * carry the softmax factor; 0: plain queries).  The string is per-thread storage, valid until the next call. */
 const char *pf_attention_kernel_name(int dtype, int path, int head_dim, int nq, int q_prescaled);

@@ -55,7 +55,7 @@ EXPORTS = ["pf_stage_kv_bytes", "pf_stage_workspace_bytes", "pf_stage_create", "
            "pf_stage_profile",
            "pf_stage_profile_read", "pf_stage_destroy", "pf_status_str", "pf_last_error", "pf_op_modulation",
            "pf_op_ln_modulate", "pf_op_gemm", "pf_op_kv_scatter", "pf_op_attention_ws_bytes", "pf_op_attention", "pf_attention_kernel_name", "pf_probe_mfma_loop",
-           "pf_gemm_tile_count", "pf_gemm_tile_map", "pf_gemm_read_ahead", "pf_op_gemm_tile", "pf_static_scratch_bytes", "pf_op_attention_static", "pf_gemm_kernel_name", "pf_op_axpy", "pf_kv_view_image", "pf_op_axpby"]
+           "pf_gemm_tile_count", "pf_gemm_tile_map", "pf_gemm_read_ahead", "pf_op_gemm_tile", "pf_static_scratch_bytes", "pf_op_attention_static", "pf_gemm_kernel_name", "pf_gemm_qkv_kernel_name", "pf_op_axpy", "pf_kv_view_image", "pf_op_axpby"]
 
 _lib = None
 
@@ -125,6 +125,8 @@ def load_library():
     lib.pf_op_attention_static.argtypes = [i32, i32, vp, i64, vp, vp, i32, i32, i32, i32, vp, i64, i32, i32, vp]
     lib.pf_gemm_kernel_name.restype = C.c_char_p
     lib.pf_gemm_kernel_name.argtypes = [i32, i32, i32, i32, i32]
+    lib.pf_gemm_qkv_kernel_name.restype = C.c_char_p
+    lib.pf_gemm_qkv_kernel_name.argtypes = [i32, i32, i32, i32]
     lib.pf_op_axpy.restype = i32
     lib.pf_op_axpy.argtypes = [vp, vp, f32, vp, i64, vp]
     lib.pf_op_axpby.restype = i32

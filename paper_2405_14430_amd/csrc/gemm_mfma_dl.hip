@@ -548,9 +548,10 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 // (64x128, 6 % low on plain stores, has fill and us raised until 431x9216x3072 goes to the three-stage tile, 38 us against 44).  us1
 // and fill1 hold where one workgroup has a CU to itself; an epilogue weighs most where no second one runs beside it.  The K/V
 // route's us are what 30 QKV launches inside stages (812 .. 16896 rows; with and without per-head norm and RoPE) take beyond that, the
-// median per round; for 256x128 a unit more, which puts it behind 256x256 at 2560x9216x3072 with norm (181 us against 171).
+// median per round; for 256x128, whose rows of a head's norm and of V^T pass one workgroup a CU, 20: at 640, 1562 and 1664 x 9216 x 3072,
+// where less would choose it, the call took 2, 8 and 9 us a layer longer than with 128x128, and it was the fastest at none of 42 launches.
 // Over 450 shapes (120 of them not of the fit) the choice is 0.9 % off the fastest tile on average, 24 % at most (128x64 in two rounds
-// of long K: 1956x2048x8192 residual 99 us, 64x128 80); over the QKV launches 1.3 %, 16 % at most.  Measured (us; * = chosen):
+// of long K: 1956x2048x8192 residual 99 us, 64x128 80); over the QKV launches 0.4 % of the call, 1.6 % at most.  Measured (us; * = chosen):
 //                                   256x256  256x192  256x128  128x192  3-stage  128x128   128x64   64x128
 //    2048 x  9216 x  3072 store          131      113      121     114*      115      130      146      160
 //    2048 x 12288 x  3072 GELU           146     136*      145      151      171      154      201      212
@@ -602,7 +603,7 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
     struct Candidate { int v, bm, bn; double us1, fill1, us, fill, gelu, residual, route, odd; };   // us1, fill1: one round
     static constexpr Candidate cand[] = {
         {V_256x256, 256, 256, 1.07, 9.3, 1.34, 5.2, 5.3, 7.8, 16.0, 31.0}, {V_256x192_S2, 256, 192, 0.95, 9.5, 1.13, 5.6, 4.3, 6.7, 15.0, 27.0},
-        {V_256x128_S3, 256, 128, 0.71, 10.5, 0.79, 6.8, 2.6, 5.4, 16.0, 16.0}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 2.5, 5.0, 8.5, 16.0},
+        {V_256x128_S3, 256, 128, 0.71, 10.5, 0.79, 6.8, 2.6, 5.4, 20.0, 16.0}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 2.5, 5.0, 8.5, 16.0},
         {V_128x192_S3, 128, 192, 0.64, 11, 0.65, 9, 5.0, 7.5, 11.5, 22.0}, {V_128x128, 128, 128, 0.80, 6, 0.45, 6, 1.5, 3.5, 5.5, 10.0},
         {V_128x64, 128, 64, 0.76, 0, 0.31, 4, 0.4, 1.7, 2.0, 2.7},       {V_64x128_S3, 64, 128, 0.46, 9, 0.34, 8, 0.7, 2.0, 2.0, 4.6}};
     const int form = gemm_epilogue_form(a);

@@ -953,6 +953,16 @@ const char *pf_gemm_kernel_name(int dtype, int path, int M, int N, int K) {
   return gemm_mfma_dl_supported(g) ? gemm_mfma_dl_variant_name(g) : "gemm_mfma_kernel";
 }
 
+const char *pf_gemm_qkv_kernel_name(int rows, int hidden, int head_dim, int qk_norm) {
+  static char some;   // (an address; nothing is read)
+  GemmArgs g{};
+  g.dt = DT_BF16; g.M = rows; g.N = 3 * hidden; g.K = hidden;
+  g.lda = g.ldw = g.K; g.gelu_from = g.ldc = g.N;
+  g.kvr.kbuf = &some; g.kvr.d = hidden; g.kvr.dh = head_dim;
+  if (qk_norm) g.kvr.q_norm = &some;
+  return rows >= 1 && hidden >= 1 && gemm_mfma_dl_supported(g) ? gemm_mfma_dl_variant_name(g) : "";
+}
+
 const char *pf_attention_kernel_name(int dtype, int path, int head_dim, int nq, int q_prescaled) {
   if (path != PF_PATH_AUTO) return "attn_simt_kernel";
   if (dtype == PF_F32) return attn_mfma_f32_head_size(head_dim) ? "attn_mfma_f32_kernel" : "attn_simt_kernel";
