@@ -166,6 +166,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, NSTAGE * (BM + BN) * ROW_BYTES <= 8
   constexpr int KS = BK / 16;
   constexpr bool SPREAD = SPREAD_LOADS && MI * NI * KS >= 2 * LPS;
   const int prologue_tiles = min(NSTAGE - 1, nk);
+  if constexpr (EPRE && NP == 2) wait_scalar_loads();
   for (int kt = 0; kt < nk; ++kt) {
     // tiles still in flight behind tile kt: min(NSTAGE-2, nk-1-kt); wait until only their loads are outstanding
     const int behind = SPREAD ? prologue_tiles - 1 : min(NSTAGE - 2, nk - 1 - kt);
@@ -367,6 +368,7 @@ __global__ __launch_bounds__(256) void gemm_wavek_kernel(GemmLaunch<bf16_t, NP> 
   if constexpr (EPRE) eops.fetch(m0, n0, M, N, epi, vec_ok != 0);
 
   const int l32 = lane & 31, hi = lane >> 5;
+  if constexpr (EPRE && NP == 2) wait_scalar_loads();
   for (int t = 0; t < my_nk; ++t) {
     if (t + 1 < my_nk) wait_vmcnt<LPS>(); else wait_vmcnt<0>();
     asm volatile("" ::: "memory");

@@ -21,6 +21,14 @@ __device__ __forceinline__ void wait_lgkmcnt() {
   asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// In front of a K loop: the compiler asks for the epilogue's arguments up there, and while scalar loads may be in flight it waits for
+// all LDS reads in front of a K tile's first MFMA instead of for those that it needs.  (The builtin, not inline assembly: the compiler
+// counts it.)  For the residual GEMMs of two problems, whose operands' addresses take the most arguments: 304x3072x15360 with 64x64 tiles
+// 84 us, 91 without.  The other kernels gain and lose about 2 % by it (512x4608x1152 GELU, 64x64, 12.1 -> 12.4) and go without.
+__device__ __forceinline__ void wait_scalar_loads() {
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0), the other counters as they are
+}
+
 // s_waitcnt vmcnt(behind * LPS) for a wave-uniform run-time `behind` in [0, MAXB] (the count is an immediate)
 template <int LPS, int MAXB>
 __device__ __forceinline__ void wait_tiles_behind(int behind) {
