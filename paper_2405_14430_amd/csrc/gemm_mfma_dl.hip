@@ -33,9 +33,9 @@ constexpr int ROW_BYTES = BK * 2;  // 128
 // WGM x WGN wavefronts on one shared tile
 // ------------------------------------------------------------------------------------------------------------------
 
-// K loops of gemm_tile_kernel.  256x256: half tiles refilled one by one (gemm_half_tiles.h).  The other tiles of at least
-// 256x128: a ring for either operand, NSTAGE K tiles of A and loop_depth_w of W deep, as LDS allows (gemm_ring.h).  Below, and for
-// the one-round 128x192 tile (SPREAD): one ring of whole K tiles (this file).  us with this file's loop -> with the other:
+// K loops of gemm_tile_kernel.  256x256: half tiles refilled one by one (gemm_half_tiles.h).  The other tiles 256
+// rows high: a ring for either operand, NSTAGE K tiles of A and loop_depth_w of W deep, as LDS allows (gemm_ring.h).  Below, one
+// ring of whole K tiles (this file).  us with this file's loop -> with the other:
 //    2048x9216x3072   256x192 132 -> 113     2048x12288x3072 GELU   256x192 154 -> 136
 //    2560x3072x15360 residual   256x128 241 -> 204                          16896x9216x3072   256x256 847 -> 737
 // and where the ring is not used (two builds in one run): 2048x9216x3072, 128x192 two stages 109, ring of two 108, but 125 and 134
@@ -43,15 +43,14 @@ constexpr int ROW_BYTES = BK * 2;  // 128
 // 2048x3072x15360 residual, 128x192 three stages 185, ring of four 188; 4096x1152x4608 residual, 128x128 59, ring 64; 1024x4608x1152
 // GELU, 128x64 21.4, ring 24.4; 512x4608x1536 GELU, 64x128 18.2, ring 18.6.
 constexpr bool loop_half_tiles(int BM, int BN) { return BM == 256 && BN == 256; }
-constexpr int loop_depth_w(int BM, int BN, int NSTAGE, bool SPREAD) {
-  if (SPREAD || loop_half_tiles(BM, BN) || BM * BN < 256 * 128) return 0;
-  return BM == 256 ? 4 : NSTAGE;
+constexpr int loop_depth_w(int BM, int BN, bool SPREAD) {
+  return SPREAD || loop_half_tiles(BM, BN) || BM < 256 ? 0 : 4;
 }
 
 template <int NP, int EM, int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, bool SPREAD_LOADS = false>
 __global__ __launch_bounds__(64 * WGM * WGN, NSTAGE * (BM + BN) * ROW_BYTES <= 80 * 1024 ? WGM * WGN / 2 : WGM * WGN / 4) void gemm_tile_kernel(GemmLaunch<bf16_t, NP> L) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  constexpr int DW = loop_depth_w(BM, BN, NSTAGE, SPREAD_LOADS);
+  constexpr int DW = loop_depth_w(BM, BN, SPREAD_LOADS);
   if constexpr (loop_half_tiles(BM, BN)) {
     gemm_half_tiles_body<NP, EM>(L, smem);
   } else if constexpr (DW > 0) {
@@ -477,7 +476,7 @@ namespace {
 
 // the rings, or the fp32 tile (row stride BN + 4) that replaces them for the epilogue, whichever is larger
 constexpr int tile_lds_bytes(int BM, int BN, int NSTAGE, bool SPREAD) {
-  const int ring = NSTAGE * (BM + BN) * ROW_BYTES, tile = BM * (BN + 4) * 4, dw = loop_depth_w(BM, BN, NSTAGE, SPREAD);
+  const int ring = NSTAGE * (BM + BN) * ROW_BYTES, tile = BM * (BN + 4) * 4, dw = loop_depth_w(BM, BN, SPREAD);
   if (loop_half_tiles(BM, BN)) return HalfTiles256::SMEM;
   if (dw) return (NSTAGE * BM + dw * BN) * ROW_BYTES;
   return (tile > ring && tile <= 96 * 1024) ? tile : ring;   // larger tiles finish in row passes

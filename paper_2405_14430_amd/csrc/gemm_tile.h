@@ -279,22 +279,18 @@ __device__ __forceinline__ void tile_epilogue(const float *tile, int m0, int n0,
         const int hh = cc / kv.dh, ch = cc - hh * kv.dh;
         const int img = kv.seg > 0 ? row / kv.seg : 0;
         const int lrow = row - img * kv.seg;           // row inside its image
-        if (kv.q_norm && part < 2) {
-          // a head's dh / 8 groups of the row are consecutive, aligned lanes (the tile is a whole number of heads wide)
-          float ss = 0.f, wn[8];
+        if constexpr (sizeof(T) == 2) {   // (gemm_kv_route_supported: the norm is of bf16 stages)
+          if (kv.q_norm && part < 2) {
+            // a head's dh / 8 groups of the row are consecutive, aligned lanes (the tile is a whole number of heads wide)
+            float ss = 0.f;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) ss = fmaf(v[e], v[e], ss);
-          for (int m = 1; m < kv.dh >> 3; m <<= 1) ss += __shfl_xor(ss, m, kWave);
-          const float rinv = rsqrtf(ss / (float)kv.dh + kv.norm_eps);
-          if constexpr (sizeof(T) == 2) {
+            for (int e = 0; e < 8; ++e) ss = fmaf(v[e], v[e], ss);
+            for (int m = 1; m < kv.dh >> 3; m <<= 1) ss += __shfl_xor(ss, m, kWave);
+            const float rinv = rsqrtf(ss / (float)kv.dh + kv.norm_eps);
             const bf16x8 w = __builtin_bit_cast(bf16x8, g0[u]);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) wn[e] = (float)w[e];
-          } else {
-            load8(reinterpret_cast<const T *>(part == 0 ? kv.q_norm : kv.k_norm) + ch, wn);
+            for (int e = 0; e < 8; ++e) v[e] = v[e] * rinv * (float)w[e];
           }
-#pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = v[e] * rinv * wn[e];
         }
         if (kv.rope && part < 2) {
           const float2 cs[4] = {{q0[u].x, q0[u].y}, {q0[u].z, q0[u].w}, {q1[u].x, q1[u].y}, {q1[u].z, q1[u].w}};
