@@ -546,44 +546,45 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 // against 65).  us, fill (the start-up, in K tiles) and the epilogues' us are fitted (least squares of the relative error) to
 // isolated GEMMs whose weights no cache holds, each shape with every tile: those of 256x256, 256x192 and 256x128 to 330 shapes of
 // 259 .. 16896 rows at widths of 384 .. 3072, the others to 290 such shapes of an earlier run, whose mean they still meet within 5 %
-// (64x128, 6 % low on plain stores, has fill and us raised until 431x9216x3072 goes to the three-stage tile, 38 us against 44).  us1
+// (64x128, 6 % low on plain stores, has fill and us raised until 431x9216x3072 goes to the three-stage tile, 37 us against 42).  us1
 // and fill1 hold where one workgroup has a CU to itself; an epilogue weighs most where no second one runs beside it.  The K/V
 // route's us are what 30 QKV launches inside stages (812 .. 16896 rows; with and without per-head norm and RoPE) take beyond that, the
 // median per round; for 256x128, whose rows of a head's norm and of V^T pass one workgroup a CU, 20: at 640, 1562 and 1664 x 9216 x 3072,
 // where less would choose it, the call took 2, 8 and 9 us a layer longer than with 128x128, and it was the fastest at none of 42 launches.
 // Over 450 shapes (120 of them not of the fit) the choice is 0.9 % off the fastest tile on average, 24 % at most (128x64 in two rounds
-// of long K: 1956x2048x8192 residual 99 us, 64x128 80); over the QKV launches 0.4 % of the call, 1.6 % at most.  Measured (us; * = chosen):
-//                                   256x256  256x192  256x128  128x192  3-stage  128x128   128x64   64x128
-//    2048 x  9216 x  3072 store          131      113      121     114*      115      130      146      160
-//    2048 x 12288 x  3072 GELU           146     136*      145      151      171      154      201      212
-//    2048 x  3072 x 15360 residual       271      241      186      245     181*      220      241      293
-//    2560 x  9216 x  3072 store          135     122*      132      137      150      138      188      198
-//    2560 x 12288 x  3072 GELU          159*      187      183      187      210      193      242      257
-//    2560 x  3072 x 15360 residual       284      252     204*      305      319      227      377      333
-//   16896 x  9216 x  3072 store         737*      803      853      831      940      900     1132     1175
-//   16896 x 12288 x  3072 GELU         1031*     1121     1193     1157     1363     1233     1511     1604
-//   16896 x  3072 x 15360 residual     1369*     1508     1517     1544     1655     1677     2050     2214
-//    4096 x  3456 x  1152 store        33.7*     47.9     41.4     45.0     50.9     40.0     48.6     52.1
-//    4096 x  4608 x  1152 GELU          67.3     60.2     63.6    57.3*     67.3     63.7     61.9     72.3
-//    4096 x  1152 x  4608 residual      90.5     80.1     61.9     78.0    58.4*     67.2     69.1     85.4
-//    4096 x  1152 x  1152 residual      35.9     32.0     25.2     28.7     24.3     25.0    26.0*     30.2
-//    2882 x  2048 x 10240 residual       178      163     118*      196      200      141      160      192
+// of long K: 1956x2048x8192 residual 97 us, 64x128 80); over the QKV launches 0.4 % of the call, 1.6 % at most.  Measured (us; * =
+// chosen), the table and the figures of the list below in one run (pairs of figures elsewhere are of runs of their own; boxes differ by 3 %):
+//                                     256x256  256x192  256x128  128x192  3-stage  128x128   128x64   64x128
+//     2048 x   9216 x   3072 store         129      112      118     110*      116      129      147      166
+//     2048 x  12288 x   3072 GELU          146     133*      142      154      171      152      200      214
+//     2048 x   3072 x  15360 residual      277      246      189      242     179*      223      254      290
+//     2560 x   9216 x   3072 store         132     120*      131      138      150      139      193      206
+//     2560 x  12288 x   3072 GELU         156*      185      180      185      208      189      245      262
+//     2560 x   3072 x  15360 residual      281      249     201*      297      319      225      376      328
+//    16896 x   9216 x   3072 store        726*      799      852      826      924      893     1135     1183
+//    16896 x  12288 x   3072 GELU        1017*     1111     1193     1152     1355     1241     1509     1610
+//    16896 x   3072 x  15360 residual    1362*     1513     1528     1555     1667     1694     2056     2203
+//     4096 x   3456 x   1152 store       33.5*     47.2     40.4     45.1     50.5     39.8     49.3     53.0
+//     4096 x   4608 x   1152 GELU         67.0     59.5     63.1    57.0*     65.9     63.4     61.7     72.7
+//     4096 x   1152 x   4608 residual     90.6     80.6     62.3     78.6    58.8*     68.3     70.3     85.1
+//     4096 x   1152 x   1152 residual     34.5     29.8     23.5     26.0     23.1     22.3    23.9*     28.6
+//     2882 x   2048 x  10240 residual      171      160     118*      196      195      141      161      194
 // The three-stage 128x192 tile issues its prefetch loads one at a time between the MFMAs (instead of in a burst behind the
 // barrier): 2048x3072x15360 204 -> 183 us, 4096x1152x4608 65 -> 55 us; every other tile loses by it or keeps nothing of the
 // gain inside a stage.
 //
 // Fewer tiles (patches of a few hundred rows), by counts of 64x64 tiles:
 //  * the wave-split-K kernel, one workgroup per CU (128 KB of LDS): up to one tile per CU, from K = 1024 on.  512x1152x1152
-//    residual 8.3 us (four-stage 64x64: 9.0), 512x1152x4608 16.1 (23.9), 512x1536x6144 22.3 (31.7), with their read-ahead (without:
-//    9.2, 20.8, 27.5), 512x1152x768 7.0 (6.9); with more tiles than CUs it loses: 1024x1152x4608 34.9 (29.1) - until the second
-//    round of its workgroups is nearly full too and K is long: 633x3072x15360 107 (121; 432 tiles: 107 against 92), 1275x1536x6144
-//    45.7 (50.0), 633x3072x3072 29.3 (28.9), 1275x1536x1536 18.5 (16.6).
-//  * 64x64 with four stages while every workgroup of the padded grid is resident at once (two per CU), 375x4608x1536 13.9 us
-//    (two stages 19.9); 1339x1536x6144, 21 x 24 tiles in a grid of 528, 64 us (64x128 52);
+//    residual 7.7 us (four-stage 64x64: 8.4), 512x1152x4608 15.7 (24.0), 512x1536x6144 22.0 (31.9), with their read-ahead (without:
+//    8.6, 20.2, 26.0), 512x1152x768 6.9 (6.9); with more tiles than CUs it loses: 1024x1152x4608 34.4 (29.0) - until the second
+//    round of its workgroups is nearly full too and K is long: 633x3072x15360 107 (120; 432 tiles: 108 against 93), 1275x1536x6144
+//    44.8 (50.2), 633x3072x3072 27.4 (28.7), 1275x1536x1536 17.4 (16.4).
+//  * 64x64 with four stages while every workgroup of the padded grid is resident at once (two per CU), 375x4608x1536 13.7 us
+//    (two stages 19.5); 1339x1536x6144, 21 x 24 tiles in a grid of 528, 63 us (64x128 51);
 //  * beyond, 64x128 with three stages under the same condition, where its rounds (of 256 tiles) are no more work than those
-//    of 64x64 tiles or K is long enough to pay for it: 1024x3456x1152 14.8 us, 512x6144x1536 with GELU 20.7, 512x4608x1536 18.0, against
-//    19.4, 23.1 and 20.4 with two-stage 64x64 tiles, which take what is left (512x4608x1152 with GELU inside a stage, whose K is not
-//    long: 16.1 us, with 64x128 17.4, though alone 17.0 and 15.3; 512x4608x1536 with a residual and an unaligned bias 33 us, with 64x128 39).
+//    of 64x64 tiles or K is long enough to pay for it: 1024x3456x1152 15.3 us, 512x6144x1536 with GELU 19.7, 512x4608x1536 17.4, against
+//    19.4, 22.1 and 20.0 with two-stage 64x64 tiles, which take what is left (512x4608x1152 with GELU inside a stage, whose K is not
+//    long: 16.1 us, with 64x128 17.4, though alone 16.8 and 14.3; 512x4608x1536 with a residual and an unaligned bias 28 us, with 64x128 32).
 // 64x64 with three stages is there for pf_op_gemm_tile only: the rule never takes it.
 enum { V_256x256 = 0, V_64x128_S3, V_256x128_S3, V_128x128, V_128x64, V_WAVEK, V_64x64_S4, V_64x64_S3, V_64x64_S2,
        V_128x192_S2, V_256x192_S2, V_128x192_S3, V_COUNT };
