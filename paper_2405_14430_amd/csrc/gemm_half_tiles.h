@@ -17,7 +17,7 @@
 // reads behind the barrier's phase may still be on their way; they are of the half that is loaded a barrier later).
 // LDS rows are swizzled as in gemm_mfma_dl.hip.
 //
-// What bounds it is power: 85 % of the cycles have the matrix unit busy (8192x8192x8192), at the clock the card then allows.
+// What bounds it is power: 81 % of the cycles have the matrix unit busy (8192x8192x8192), at the clock the card then holds, 1.6 GHz.
 // One K tile at a time behind one barrier (43 - 49 % busy) -> this: 8192x8192x8192 866 -> 758 us (1.45 PFLOP/s, the vendor
 // library 683), 16896x9216x3072 847 -> 737 (724), 16896x12288x3072 with GELU 1157 -> 1031, 16896x3072x15360 with a
 // residual 1574 -> 1369.  Waves 4-7 half a phase behind waves 0-3, one multiplying while the other reads (eight barriers a K tile):

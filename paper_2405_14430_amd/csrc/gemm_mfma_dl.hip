@@ -550,9 +550,9 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 // and fill1 hold where one workgroup has a CU to itself; an epilogue weighs most where no second one runs beside it.  The K/V
 // route's us are what 30 QKV launches inside stages (812 .. 16896 rows; with and without per-head norm and RoPE) take beyond that, the
 // median per round; for 256x128, whose rows of a head's norm and of V^T pass one workgroup a CU, 20: at 640, 1562 and 1664 x 9216 x 3072,
-// where less would choose it, the call took 2, 8 and 9 us a layer longer than with 128x128, and it was the fastest at none of 42 launches.
+// where less would choose it, the call took 2, 8 and 9 us a layer longer than with 128x128, and it was the fastest at none of 50 launches.
 // Over 450 shapes (120 of them not of the fit) the choice is 0.9 % off the fastest tile on average, 24 % at most (128x64 in two rounds
-// of long K: 1956x2048x8192 residual 97 us, 64x128 80); over the QKV launches 0.4 % of the call, 1.6 % at most.  Measured (us; * =
+// of long K: 1956x2048x8192 residual 97 us, 64x128 80); over 50 calls with each QKV tile 0.1 % of the call, 1.6 % at most.  Measured (us; * =
 // chosen), the table and the figures of the list below in one run (pairs of figures elsewhere are of runs of their own; boxes differ by 3 %):
 //                                     256x256  256x192  256x128  128x192  3-stage  128x128   128x64   64x128
 //     2048 x   9216 x   3072 store         129      112      118     110*      116      129      147      166
