@@ -482,13 +482,13 @@ constexpr int tile_lds_bytes(int BM, int BN, int NSTAGE, bool SPREAD) {
   return (tile > ring && tile <= 96 * 1024) ? tile : ring;   // larger tiles finish in row passes
 }
 
-// PINNED: a configuration that only pf_op_gemm_tile asks for (one problem, no K/V route)
-template <int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, bool SPREAD = false, bool PINNED = false>
+// PINNED: a configuration that only pf_op_gemm_tile asks for (one problem, no K/V route); ROUTE: the rule takes it for K/V routes too
+template <int BM, int BN, int NSTAGE, int WGM = 2, int WGN = 2, bool SPREAD = false, bool PINNED = false, bool ROUTE = !PINNED>
 hipError_t launch_tile(const GemmArgs &a, const GemmArgs *b, hipStream_t s) {
   constexpr int smem = tile_lds_bytes(BM, BN, NSTAGE, SPREAD);
   auto go = [&](auto np, auto em) -> hipError_t {
     constexpr int NP = decltype(np)::value, EM = decltype(em)::value;
-    if constexpr (PINNED && (NP == 2 || EM == EM_KV_ROUTE)) {
+    if constexpr ((PINNED && NP == 2) || (!ROUTE && EM == EM_KV_ROUTE)) {
       return hipErrorInvalidValue;
     } else {
       constexpr auto kernel = &gemm_tile_kernel<NP, EM, BM, BN, NSTAGE, WGM, WGN, SPREAD>;
@@ -549,8 +549,8 @@ bool gemm_mfma_dl_supported(const GemmArgs &a) {
 // (64x128, 6 % low on plain stores, has fill and us raised until 431x9216x3072 goes to the three-stage tile, 37 us against 42).  us1
 // and fill1 hold where one workgroup has a CU to itself; an epilogue weighs most where no second one runs beside it.  The K/V
 // route's us are what 30 QKV launches inside stages (812 .. 16896 rows; with and without per-head norm and RoPE) take beyond that, the
-// median per round; for 256x128, whose rows of a head's norm and of V^T pass one workgroup a CU, 20: at 640, 1562 and 1664 x 9216 x 3072,
-// where less would choose it, the call took 2, 8 and 9 us a layer longer than with 128x128, and it was the fastest at none of 50 launches.
+// median per round; 256x128 is no candidate for it: at 640, 1562 and 1664 x 9216 x 3072, where that price chose it, the call took 2, 8 and
+// 9 us a layer longer than with 128x128, and it was the fastest at none of 50 launches.
 // Over 450 shapes (120 of them not of the fit) the choice is 0.9 % off the fastest tile on average, 24 % at most (128x64 in two rounds
 // of long K: 1956x2048x8192 residual 97 us, 64x128 80); over 50 calls with each QKV tile 0.1 % of the call, 1.6 % at most.  Measured (us; * =
 // chosen), the table and the figures of the list below in one run (pairs of figures elsewhere are of runs of their own; boxes differ by 3 %):
@@ -605,14 +605,14 @@ static int pick_variant(const GemmArgs &a, const GemmArgs *b = nullptr) {
     struct Candidate { int v, bm, bn; double us1, fill1, us, fill, gelu, residual, route, odd; };   // us1, fill1: one round
     static constexpr Candidate cand[] = {
         {V_256x256, 256, 256, 1.07, 9.3, 1.34, 5.2, 5.3, 7.8, 16.0, 31.0}, {V_256x192_S2, 256, 192, 0.95, 9.5, 1.13, 5.6, 4.3, 6.7, 15.0, 27.0},
-        {V_256x128_S3, 256, 128, 0.71, 10.5, 0.79, 6.8, 2.6, 5.4, 20.0, 16.0}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 2.5, 5.0, 8.5, 16.0},
+        {V_256x128_S3, 256, 128, 0.71, 10.5, 0.79, 6.8, 2.6, 5.4, 0.0, 16.0}, {V_128x192_S2, 128, 192, 0.90, 8, 0.65, 5, 2.5, 5.0, 8.5, 16.0},
         {V_128x192_S3, 128, 192, 0.64, 11, 0.65, 9, 5.0, 7.5, 11.5, 22.0}, {V_128x128, 128, 128, 0.80, 6, 0.45, 6, 1.5, 3.5, 5.5, 10.0},
         {V_128x64, 128, 64, 0.76, 0, 0.31, 4, 0.4, 1.7, 2.0, 2.7},       {V_64x128_S3, 64, 128, 0.46, 9, 0.34, 8, 0.7, 2.0, 2.0, 4.6}};
     const int form = gemm_epilogue_form(a);
     int best = V_128x128;
     double best_cost = 1e300;
     for (const Candidate &c : cand) {
-      if (wide_heads && c.bn % 128) continue;
+      if ((wide_heads && c.bn % 128) || (form == EM_KV_ROUTE && c.v == V_256x128_S3)) continue;
       const int64_t rounds = (grid(c.bm, c.bn) + 255) / 256;
       const double epilogue = odd ? c.odd * (form == EM_RESIDUAL ? 2.6 : 1.0)
                                   : form == EM_KV_ROUTE ? c.route : form == EM_RESIDUAL ? c.residual : a.gelu_from < a.N ? c.gelu : 0.0;
@@ -633,7 +633,7 @@ static hipError_t launch_variant(int v, const GemmArgs &a, const GemmArgs *b, hi
   switch (v) {
     case V_256x256: return launch_tile<256, 256, 2, 4, 2>(a, b, s);
     case V_64x128_S3: return launch_tile<64, 128, 3>(a, b, s);
-    case V_256x128_S3: return launch_tile<256, 128, 3, 4, 2>(a, b, s);
+    case V_256x128_S3: return launch_tile<256, 128, 3, 4, 2, false, false, false>(a, b, s);
     case V_128x128: return launch_tile<128, 128, 2>(a, b, s);
     case V_128x64: return launch_tile<128, 64, 2>(a, b, s);
     case V_WAVEK: return launch_wavek<64, 64>(a, b, s);

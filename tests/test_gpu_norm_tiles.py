@@ -13,16 +13,17 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-2
 
 
-# tile that the rule gives the image rows (the text rows of the first case are in the same GEMM): heads of 128 channels
-# 256x256, 256x128, 128x128; heads of 64 channels 256x192, 256x256, 128x192
-@pytest.mark.parametrize("name,grid_h,grid_w,text,with_text", [
-    ("C4", 34, 59, 77, True), ("C4", 40, 35, 45, False), ("C4", 80, 51, 30, False),
-    ("C3", 80, 50, 77, False), ("C3", 100, 60, 29, False), ("C3", 100, 80, 154, False)])
-def test_norm_and_rope_on_large_tiles(name, grid_h, grid_w, text, with_text):
-    from paper_2405_14430_amd import Stage
+# with the tile that the rule gives the image rows (the text rows of the first case are in the same GEMM)
+@pytest.mark.parametrize("name,grid_h,grid_w,text,with_text,tile", [
+    ("C4", 34, 59, 77, True, "256,256"), ("C4", 40, 35, 45, False, "128,128"), ("C4", 80, 51, 30, False, "128,128"),
+    ("C3", 80, 50, 77, False, "256,192"), ("C3", 100, 60, 29, False, "256,256"), ("C3", 100, 80, 154, False, "128,192")])
+def test_norm_and_rope_on_large_tiles(name, grid_h, grid_w, text, with_text, tile):
+    from paper_2405_14430_amd import Stage, binding as B
     base = wl.CONFIGS[name]
     cfg = wl.variant(base, n_layers=1, n_patches=2, seq_img=grid_h * grid_w, grid_h=grid_h, grid_w=grid_w, text_len=text,
                      mlp_dim=base["hidden"], qk_norm=1, joint_rope=1 if name == "C3" else 0)
+    rows = grid_h * grid_w // 2 + (text if with_text else 0)
+    assert f"gemm_tile_kernel<{tile}," in B.load_library().pf_gemm_qkv_kernel_name(rows, cfg["hidden"], cfg["head_dim"], 1).decode()
     print("norm tiles", name, grid_h, grid_w, text, with_text, flush=True)
     W, A = wl.make_weights(cfg), wl.make_activations(cfg)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
