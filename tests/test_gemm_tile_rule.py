@@ -10,34 +10,34 @@ import pytest
 from paper_2405_14430_amd import binding as B
 
 MEASURED = {
-    (5362, 2048, 8192): {"<256,256,2,4,2,false>": 156.5, "<256,192,2,4,2,false>": 248.7, "<256,128,3,4,2,false>": 185.9, "<128,192,2,2,2,false>": 177.7, "<128,192,3,2,2,true>": 177.8, "<128,128,2,2,2,false>": 200.7, "<128,64,2,2,2,false>": 227.0, "<64,128,3,2,2,false>": 234.8},
-    (10751, 1536, 7680): {"<256,256,2,4,2,false>": 288.5, "<256,192,2,4,2,false>": 243.1, "<256,128,3,4,2,false>": 268.9, "<128,192,2,2,2,false>": 249.3, "<128,192,3,2,2,true>": 248.1, "<128,128,2,2,2,false>": 295.8, "<128,64,2,2,2,false>": 330.6, "<64,128,3,2,2,false>": 327.8},
-    (9409, 9216, 3072): {"<256,256,2,4,2,false>": 422.0, "<256,192,2,4,2,false>": 452.8, "<256,128,3,4,2,false>": 462.2, "<128,192,2,2,2,false>": 465.9, "<128,192,3,2,2,true>": 513.9, "<128,128,2,2,2,false>": 501.2, "<128,64,2,2,2,false>": 630.1, "<64,128,3,2,2,false>": 676.4},
-    (431, 9216, 3072): {"<256,256,2,4,2,false>": 58.9, "<256,192,2,4,2,false>": 53.0, "<256,128,3,4,2,false>": 40.8, "<128,192,2,2,2,false>": 51.2, "<128,192,3,2,2,true>": 36.5, "<128,128,2,2,2,false>": 45.3, "<128,64,2,2,2,false>": 48.0, "<64,128,3,2,2,false>": 41.8},
-    (512, 9216, 3072): {"<256,256,2,4,2,false>": 62.7, "<256,192,2,4,2,false>": 54.5, "<256,128,3,4,2,false>": 43.5, "<128,192,2,2,2,false>": 52.6, "<128,192,3,2,2,true>": 40.4, "<128,128,2,2,2,false>": 46.5, "<128,64,2,2,2,false>": 51.0, "<64,128,3,2,2,false>": 58.9},
-    (5263, 1536, 1536): {"<256,256,2,4,2,false>": 34.2, "<256,192,2,4,2,false>": 31.6, "<256,128,3,4,2,false>": 42.8, "<128,192,2,2,2,false>": 35.8, "<128,192,3,2,2,true>": 38.5, "<128,128,2,2,2,false>": 44.2, "<128,64,2,2,2,false>": 41.1, "<64,128,3,2,2,false>": 39.1},
-    (8283, 576, 2304): {"<256,256,2,4,2,false>": 41.6, "<256,192,2,4,2,false>": 35.8, "<256,128,3,4,2,false>": 28.9, "<128,192,2,2,2,false>": 32.6, "<128,192,3,2,2,true>": 26.2, "<128,128,2,2,2,false>": 29.6, "<128,64,2,2,2,false>": 33.0, "<64,128,3,2,2,false>": 39.7},
-    (680, 6144, 1536): {"<256,256,2,4,2,false>": 33.1, "<256,192,2,4,2,false>": 30.6, "<256,128,3,4,2,false>": 23.5, "<128,192,2,2,2,false>": 28.6, "<128,192,3,2,2,true>": 21.1, "<128,128,2,2,2,false>": 25.3, "<128,64,2,2,2,false>": 26.5, "<64,128,3,2,2,false>": 32.0},
-    (1038, 4608, 1152): {"<256,256,2,4,2,false>": 26.7, "<256,192,2,4,2,false>": 25.0, "<256,128,3,4,2,false>": 18.6, "<128,192,2,2,2,false>": 22.6, "<128,192,3,2,2,true>": 18.1, "<128,128,2,2,2,false>": 21.2, "<128,64,2,2,2,false>": 22.2, "<64,128,3,2,2,false>": 25.9},
-    (7456, 768, 3840): {"<256,256,2,4,2,false>": 64.2, "<256,192,2,4,2,false>": 61.1, "<256,128,3,4,2,false>": 44.8, "<128,192,2,2,2,false>": 61.6, "<128,192,3,2,2,true>": 44.3, "<128,128,2,2,2,false>": 55.8, "<128,64,2,2,2,false>": 61.7, "<64,128,3,2,2,false>": 70.4},
-    (2048, 9216, 3072): {"<256,256,2,4,2,false>": 128.6, "<256,192,2,4,2,false>": 112.2, "<256,128,3,4,2,false>": 119.3, "<128,192,2,2,2,false>": 111.2, "<128,192,3,2,2,true>": 114.4, "<128,128,2,2,2,false>": 129.7, "<128,64,2,2,2,false>": 147.7, "<64,128,3,2,2,false>": 166.1},
-    (2560, 9216, 3072): {"<256,256,2,4,2,false>": 132.2, "<256,192,2,4,2,false>": 119.7, "<256,128,3,4,2,false>": 131.8, "<128,192,2,2,2,false>": 136.8, "<128,192,3,2,2,true>": 149.8, "<128,128,2,2,2,false>": 139.3, "<128,64,2,2,2,false>": 191.6, "<64,128,3,2,2,false>": 204.2},
-    (16896, 9216, 3072): {"<256,256,2,4,2,false>": 724.1, "<256,192,2,4,2,false>": 796.8, "<256,128,3,4,2,false>": 849.7, "<128,192,2,2,2,false>": 820.8, "<128,192,3,2,2,true>": 923.9, "<128,128,2,2,2,false>": 894.1, "<128,64,2,2,2,false>": 1132.5, "<64,128,3,2,2,false>": 1180.9},
-    (4096, 3456, 1152): {"<256,256,2,4,2,false>": 33.3, "<256,192,2,4,2,false>": 47.3, "<256,128,3,4,2,false>": 40.4, "<128,192,2,2,2,false>": 45.2, "<128,192,3,2,2,true>": 50.4, "<128,128,2,2,2,false>": 39.8, "<128,64,2,2,2,false>": 49.8, "<64,128,3,2,2,false>": 52.6},
-    (3677, 8192, 2048): {"<256,256,2,4,2,false>": 101.5, "<256,192,2,4,2,false>": 122.4, "<256,128,3,4,2,false>": 122.2, "<128,192,2,2,2,false>": 127.7, "<128,192,3,2,2,true>": 147.5, "<128,128,2,2,2,false>": 124.2, "<128,64,2,2,2,false>": 157.1, "<64,128,3,2,2,false>": 169.5},
-    (1024, 4608, 1536): {"<256,256,2,4,2,false>": 35.4, "<256,192,2,4,2,false>": 31.2, "<256,128,3,4,2,false>": 24.5, "<128,192,2,2,2,false>": 29.5, "<128,192,3,2,2,true>": 23.0, "<128,128,2,2,2,false>": 26.2, "<128,64,2,2,2,false>": 27.1, "<64,128,3,2,2,false>": 32.0},
+    (5362, 2048, 8192): {"<256,256,2,4,2,false>": 188.6, "<256,192,2,4,2,false>": 282.4, "<256,128,3,4,2,false>": 214.5, "<128,192,2,2,2,false>": 177.9, "<128,192,3,2,2,true>": 182.1, "<128,128,2,2,2,false>": 192.6, "<128,64,2,2,2,false>": 222.9, "<64,128,3,2,2,false>": 233.8},
+    (10751, 1536, 7680): {"<256,256,2,4,2,false>": 340.0, "<256,192,2,4,2,false>": 287.9, "<256,128,3,4,2,false>": 310.3, "<128,192,2,2,2,false>": 247.4, "<128,192,3,2,2,true>": 249.3, "<128,128,2,2,2,false>": 295.4, "<128,64,2,2,2,false>": 326.9, "<64,128,3,2,2,false>": 344.4},
+    (9409, 9216, 3072): {"<256,256,2,4,2,false>": 483.2, "<256,192,2,4,2,false>": 510.4, "<256,128,3,4,2,false>": 520.4, "<128,192,2,2,2,false>": 485.8, "<128,192,3,2,2,true>": 525.9, "<128,128,2,2,2,false>": 517.5, "<128,64,2,2,2,false>": 644.1, "<64,128,3,2,2,false>": 677.7},
+    (431, 9216, 3072): {"<256,256,2,4,2,false>": 72.8, "<256,192,2,4,2,false>": 62.6, "<256,128,3,4,2,false>": 42.3, "<128,192,2,2,2,false>": 50.9, "<128,192,3,2,2,true>": 38.8, "<128,128,2,2,2,false>": 44.4, "<128,64,2,2,2,false>": 45.0, "<64,128,3,2,2,false>": 42.1},
+    (512, 9216, 3072): {"<256,256,2,4,2,false>": 76.4, "<256,192,2,4,2,false>": 68.8, "<256,128,3,4,2,false>": 44.9, "<128,192,2,2,2,false>": 52.1, "<128,192,3,2,2,true>": 41.3, "<128,128,2,2,2,false>": 45.8, "<128,64,2,2,2,false>": 48.2, "<64,128,3,2,2,false>": 56.6},
+    (5263, 1536, 1536): {"<256,256,2,4,2,false>": 39.8, "<256,192,2,4,2,false>": 32.4, "<256,128,3,4,2,false>": 48.1, "<128,192,2,2,2,false>": 34.9, "<128,192,3,2,2,true>": 39.7, "<128,128,2,2,2,false>": 44.3, "<128,64,2,2,2,false>": 39.8, "<64,128,3,2,2,false>": 36.9},
+    (8283, 576, 2304): {"<256,256,2,4,2,false>": 53.1, "<256,192,2,4,2,false>": 41.7, "<256,128,3,4,2,false>": 34.0, "<128,192,2,2,2,false>": 33.1, "<128,192,3,2,2,true>": 28.7, "<128,128,2,2,2,false>": 30.9, "<128,64,2,2,2,false>": 33.9, "<64,128,3,2,2,false>": 38.9},
+    (680, 6144, 1536): {"<256,256,2,4,2,false>": 42.5, "<256,192,2,4,2,false>": 37.1, "<256,128,3,4,2,false>": 24.8, "<128,192,2,2,2,false>": 29.1, "<128,192,3,2,2,true>": 22.9, "<128,128,2,2,2,false>": 25.2, "<128,64,2,2,2,false>": 26.4, "<64,128,3,2,2,false>": 30.8},
+    (1038, 4608, 1152): {"<256,256,2,4,2,false>": 32.5, "<256,192,2,4,2,false>": 25.7, "<256,128,3,4,2,false>": 20.3, "<128,192,2,2,2,false>": 22.0, "<128,192,3,2,2,true>": 18.2, "<128,128,2,2,2,false>": 20.3, "<128,64,2,2,2,false>": 20.7, "<64,128,3,2,2,false>": 23.8},
+    (7456, 768, 3840): {"<256,256,2,4,2,false>": 81.1, "<256,192,2,4,2,false>": 64.1, "<256,128,3,4,2,false>": 51.9, "<128,192,2,2,2,false>": 52.1, "<128,192,3,2,2,true>": 46.5, "<128,128,2,2,2,false>": 50.5, "<128,64,2,2,2,false>": 60.1, "<64,128,3,2,2,false>": 63.6},
+    (2048, 9216, 3072): {"<256,256,2,4,2,false>": 153.0, "<256,192,2,4,2,false>": 129.7, "<256,128,3,4,2,false>": 136.9, "<128,192,2,2,2,false>": 117.1, "<128,192,3,2,2,true>": 120.4, "<128,128,2,2,2,false>": 130.9, "<128,64,2,2,2,false>": 150.3, "<64,128,3,2,2,false>": 163.8},
+    (2560, 9216, 3072): {"<256,256,2,4,2,false>": 154.3, "<256,192,2,4,2,false>": 140.0, "<256,128,3,4,2,false>": 149.9, "<128,192,2,2,2,false>": 141.5, "<128,192,3,2,2,true>": 157.1, "<128,128,2,2,2,false>": 143.6, "<128,64,2,2,2,false>": 191.7, "<64,128,3,2,2,false>": 202.0},
+    (16896, 9216, 3072): {"<256,256,2,4,2,false>": 850.0, "<256,192,2,4,2,false>": 916.2, "<256,128,3,4,2,false>": 967.2, "<128,192,2,2,2,false>": 881.2, "<128,192,3,2,2,true>": 989.4, "<128,128,2,2,2,false>": 944.0, "<128,64,2,2,2,false>": 1178.5, "<64,128,3,2,2,false>": 1215.3},
+    (4096, 3456, 1152): {"<256,256,2,4,2,false>": 37.4, "<256,192,2,4,2,false>": 51.7, "<256,128,3,4,2,false>": 41.5, "<128,192,2,2,2,false>": 45.4, "<128,192,3,2,2,true>": 54.4, "<128,128,2,2,2,false>": 41.1, "<128,64,2,2,2,false>": 48.3, "<64,128,3,2,2,false>": 49.6},
+    (3677, 8192, 2048): {"<256,256,2,4,2,false>": 116.7, "<256,192,2,4,2,false>": 130.7, "<256,128,3,4,2,false>": 138.0, "<128,192,2,2,2,false>": 131.0, "<128,192,3,2,2,true>": 150.2, "<128,128,2,2,2,false>": 128.1, "<128,64,2,2,2,false>": 159.4, "<64,128,3,2,2,false>": 165.9},
+    (1024, 4608, 1536): {"<256,256,2,4,2,false>": 43.2, "<256,192,2,4,2,false>": 39.0, "<256,128,3,4,2,false>": 26.2, "<128,192,2,2,2,false>": 30.3, "<128,192,3,2,2,true>": 24.4, "<128,128,2,2,2,false>": 26.5, "<128,64,2,2,2,false>": 27.0, "<64,128,3,2,2,false>": 31.7},
     # fewer tiles, where the rule does not look at the epilogue: 430 to 528 tiles of 64x64, with a residual
-    (633, 3072, 15360): {"gemm_wavek_kernel<64,64>": 108.3, "<64,64,4,2,2,false>": 121.3, "<64,128,3,2,2,false>": 114.5, "<64,64,2,2,2,false>": 165.4, "<128,64,2,2,2,false>": 177.4},
-    (633, 3072, 12288): {"gemm_wavek_kernel<64,64>": 86.9, "<64,64,4,2,2,false>": 99.0, "<64,128,3,2,2,false>": 93.9, "<64,64,2,2,2,false>": 134.0, "<128,64,2,2,2,false>": 144.1},
-    (569, 3072, 15360): {"gemm_wavek_kernel<64,64>": 108.5, "<64,64,4,2,2,false>": 94.0, "<64,128,3,2,2,false>": 114.3, "<64,64,2,2,2,false>": 164.9, "<128,64,2,2,2,false>": 177.0},
-    (1275, 1536, 6144): {"gemm_wavek_kernel<64,64>": 45.5, "<64,64,4,2,2,false>": 51.2, "<64,128,3,2,2,false>": 49.2, "<64,64,2,2,2,false>": 67.3, "<128,64,2,2,2,false>": 73.1},
-    (1339, 1536, 6144): {"gemm_wavek_kernel<64,64>": 63.8, "<64,64,4,2,2,false>": 63.6, "<64,128,3,2,2,false>": 51.0, "<64,64,2,2,2,false>": 67.6, "<128,64,2,2,2,false>": 73.7},
-    (1211, 1536, 6144): {"gemm_wavek_kernel<64,64>": 45.3, "<64,64,4,2,2,false>": 42.3, "<64,128,3,2,2,false>": 49.4, "<64,64,2,2,2,false>": 67.1, "<128,64,2,2,2,false>": 73.0},
-    (765, 2560, 10240): {"gemm_wavek_kernel<64,64>": 75.2, "<64,64,4,2,2,false>": 86.6, "<64,128,3,2,2,false>": 79.0, "<64,64,2,2,2,false>": 109.5, "<128,64,2,2,2,false>": 118.4},
-    (1021, 2048, 8192): {"gemm_wavek_kernel<64,64>": 56.6, "<64,64,4,2,2,false>": 65.9, "<64,128,3,2,2,false>": 63.9, "<64,64,2,2,2,false>": 85.9, "<128,64,2,2,2,false>": 92.7},
-    (1527, 1152, 4608): {"gemm_wavek_kernel<64,64>": 35.6, "<64,64,4,2,2,false>": 30.6, "<64,128,3,2,2,false>": 38.3, "<64,64,2,2,2,false>": 51.4, "<128,64,2,2,2,false>": 56.2},
-    (1783, 1152, 4608): {"gemm_wavek_kernel<64,64>": 36.1, "<64,64,4,2,2,false>": 39.5, "<64,128,3,2,2,false>": 40.4, "<64,64,2,2,2,false>": 52.1, "<128,64,2,2,2,false>": 57.1},
-    (1275, 1536, 1536): {"gemm_wavek_kernel<64,64>": 17.5, "<64,64,4,2,2,false>": 16.6, "<64,128,3,2,2,false>": 16.7, "<64,64,2,2,2,false>": 20.5, "<128,64,2,2,2,false>": 22.6},
+    (633, 3072, 15360): {"gemm_wavek_kernel<64,64>": 106.8, "<64,64,4,2,2,false>": 120.1, "<64,128,3,2,2,false>": 119.1, "<64,64,2,2,2,false>": 162.9, "<128,64,2,2,2,false>": 177.2},
+    (633, 3072, 12288): {"gemm_wavek_kernel<64,64>": 79.9, "<64,64,4,2,2,false>": 96.7, "<64,128,3,2,2,false>": 93.8, "<64,64,2,2,2,false>": 126.9, "<128,64,2,2,2,false>": 139.2},
+    (569, 3072, 15360): {"gemm_wavek_kernel<64,64>": 103.0, "<64,64,4,2,2,false>": 93.7, "<64,128,3,2,2,false>": 115.2, "<64,64,2,2,2,false>": 161.6, "<128,64,2,2,2,false>": 175.8},
+    (1275, 1536, 6144): {"gemm_wavek_kernel<64,64>": 46.0, "<64,64,4,2,2,false>": 50.5, "<64,128,3,2,2,false>": 51.7, "<64,64,2,2,2,false>": 67.1, "<128,64,2,2,2,false>": 74.2},
+    (1339, 1536, 6144): {"gemm_wavek_kernel<64,64>": 64.0, "<64,64,4,2,2,false>": 65.3, "<64,128,3,2,2,false>": 53.6, "<64,64,2,2,2,false>": 66.9, "<128,64,2,2,2,false>": 74.4},
+    (1211, 1536, 6144): {"gemm_wavek_kernel<64,64>": 45.7, "<64,64,4,2,2,false>": 43.1, "<64,128,3,2,2,false>": 51.1, "<64,64,2,2,2,false>": 67.0, "<128,64,2,2,2,false>": 74.3},
+    (765, 2560, 10240): {"gemm_wavek_kernel<64,64>": 74.5, "<64,64,4,2,2,false>": 84.7, "<64,128,3,2,2,false>": 83.6, "<64,64,2,2,2,false>": 108.6, "<128,64,2,2,2,false>": 119.4},
+    (1021, 2048, 8192): {"gemm_wavek_kernel<64,64>": 57.5, "<64,64,4,2,2,false>": 63.8, "<64,128,3,2,2,false>": 67.4, "<64,64,2,2,2,false>": 85.6, "<128,64,2,2,2,false>": 93.5},
+    (1527, 1152, 4608): {"gemm_wavek_kernel<64,64>": 34.7, "<64,64,4,2,2,false>": 30.9, "<64,128,3,2,2,false>": 39.1, "<64,64,2,2,2,false>": 50.8, "<128,64,2,2,2,false>": 56.6},
+    (1783, 1152, 4608): {"gemm_wavek_kernel<64,64>": 36.8, "<64,64,4,2,2,false>": 39.4, "<64,128,3,2,2,false>": 41.7, "<64,64,2,2,2,false>": 51.4, "<128,64,2,2,2,false>": 58.0},
+    (1275, 1536, 1536): {"gemm_wavek_kernel<64,64>": 17.5, "<64,64,4,2,2,false>": 14.9, "<64,128,3,2,2,false>": 17.8, "<64,64,2,2,2,false>": 16.6, "<128,64,2,2,2,false>": 19.2},
 }
 
 
@@ -46,77 +46,6 @@ def test_rule_picks_a_tile_near_the_fastest(shape):
     us = MEASURED[shape]
     name = B.load_library().pf_gemm_kernel_name(1, 0, *shape).decode()
     assert us[name.replace("gemm_tile_kernel", "")] <= 1.125 * min(us.values()), (name, min(us, key=us.get))
-
-
-# QKV projections inside a call (three layers, weights in turn): us of the call per layer with the fastest tile, and how much longer it takes
-# with each, in the order of QKV_TILES (None: not for heads of 128 channels with a norm).  (rows, hidden, head size, norm)
-QKV_TILES = ["<256,256,2,4,2,false>", "<64,128,3,2,2,false>", "<256,128,3,4,2,false>", "<128,128,2,2,2,false>", "<128,64,2,2,2,false>", "<128,192,2,2,2,false>", "<256,192,2,4,2,false>", "<128,192,3,2,2,true>"]
-QKV_MEASURED = {
-    (640, 3072, 128, 1): (247, [16.6, 13.4, 2.0, 0.0, None, None, None, None]),
-    (800, 3072, 128, 1): (305, [17.6, 19.8, 30.9, 0.0, None, None, None, None]),
-    (1050, 3072, 128, 1): (360, [0.0, 19.4, 24.6, 16.4, None, None, None, None]),
-    (1200, 3072, 128, 1): (376, [0.0, 24.0, 22.8, 15.1, None, None, None, None]),
-    (1300, 3072, 128, 1): (445, [0.0, 22.3, 24.1, 11.9, None, None, None, None]),
-    (1562, 3072, 128, 1): (510, [36.8, 32.5, 7.2, 0.0, None, None, None, None]),
-    (1664, 3072, 128, 1): (529, [40.6, 36.3, 8.4, 0.0, None, None, None, None]),
-    (1800, 3072, 128, 1): (556, [18.5, 26.1, 11.1, 0.0, None, None, None, None]),
-    (2048, 3072, 128, 1): (591, [12.6, 32.5, 13.6, 0.0, None, None, None, None]),
-    (2176, 3072, 128, 1): (628, [12.6, 35.0, 13.8, 0.0, None, None, None, None]),
-    (2560, 3072, 128, 1): (690, [3.3, 61.6, 9.8, 0.0, None, None, None, None]),
-    (2800, 3072, 128, 1): (889, [0.0, 73.8, 46.4, 27.5, None, None, None, None]),
-    (3072, 3072, 128, 1): (926, [0.0, 86.9, 48.6, 31.9, None, None, None, None]),
-    (3500, 3072, 128, 1): (1015, [0.0, 113.6, 48.7, 36.0, None, None, None, None]),
-    (4096, 3072, 128, 1): (1187, [0.0, 83.8, 28.3, 21.5, None, None, None, None]),
-    (5000, 3072, 128, 1): (1471, [0.0, 150.3, 68.7, 59.1, None, None, None, None]),
-    (800, 3072, 128, 0): (301, [18.9, 22.6, 32.8, 0.0, 28.8, 16.9, 11.6, 30.8]),
-    (1050, 3072, 128, 0): (348, [8.4, 26.2, 33.5, 24.0, 23.6, 4.0, 0.0, 14.7]),
-    (1300, 3072, 128, 0): (446, [0.0, 21.7, 22.0, 5.1, 30.3, 25.9, 35.3, 48.3]),
-    (1562, 3072, 128, 0): (508, [36.8, 29.6, 9.0, 0.0, 22.5, 14.1, 27.4, 22.5]),
-    (1664, 3072, 128, 0): (528, [41.2, 34.5, 9.8, 0.0, 25.2, 13.9, 26.9, 23.4]),
-    (1800, 3072, 128, 0): (537, [37.7, 42.1, 30.5, 17.3, 31.0, 0.0, 16.5, 14.8]),
-    (2048, 3072, 128, 0): (571, [32.9, 49.1, 34.2, 16.8, 27.0, 0.0, 11.6, 11.8]),
-    (2304, 3072, 128, 0): (633, [23.3, 56.2, 24.8, 5.4, 36.8, 5.7, 0.0, 33.4]),
-    (2560, 3072, 128, 0): (676, [16.4, 66.8, 21.5, 8.3, 51.3, 3.1, 0.0, 30.1]),
-    (3072, 3072, 128, 0): (925, [0.0, 82.0, 50.2, 25.5, 56.8, 20.1, 36.1, 49.6]),
-    (3500, 3072, 128, 0): (1015, [0.0, 105.7, 46.0, 26.1, 78.7, 30.5, 31.5, 85.0]),
-    (4096, 3072, 128, 0): (1156, [26.5, 100.5, 54.5, 38.8, 70.9, 5.7, 0.0, 47.7]),
-    (1024, 1536, 64, 0): (145, [17.3, 6.0, 6.8, 0.1, 0.8, 5.1, 12.2, 0.0]),
-    (1024, 1536, 64, 1): (144, [18.3, 6.3, 7.0, 0.0, 1.1, 5.3, 12.0, 1.0]),
-    (1300, 1536, 64, 0): (187, [16.0, 5.5, 7.6, 0.0, 10.5, 9.1, 10.3, 22.1]),
-    (1300, 1536, 64, 1): (187, [15.4, 6.0, 7.2, 0.0, 11.4, 10.1, 10.2, 23.0]),
-    (1664, 1536, 64, 0): (215, [17.9, 8.1, 34.5, 0.0, 13.7, 11.2, 11.6, 22.2]),
-    (1664, 1536, 64, 1): (217, [16.2, 6.9, 32.8, 0.0, 11.2, 10.6, 10.3, 21.0]),
-    (2048, 1536, 64, 0): (261, [5.8, 9.4, 24.4, 10.3, 2.5, 0.0, 0.0, 10.2]),
-    (2048, 1536, 64, 1): (262, [4.5, 9.0, 22.7, 10.3, 1.9, 0.4, 0.0, 9.7]),
-    (2560, 1536, 64, 0): (306, [4.5, 14.0, 25.7, 10.0, 9.4, 0.7, 0.0, 9.9]),
-    (2560, 1536, 64, 1): (306, [4.9, 14.5, 25.2, 9.3, 11.3, 0.7, 0.0, 11.5]),
-    (3072, 1536, 64, 0): (413, [0.0, 14.3, 23.7, 8.1, 10.6, 12.9, 32.8, 26.1]),
-    (3072, 1536, 64, 1): (420, [0.0, 11.6, 16.2, 0.8, 2.8, 7.1, 26.9, 28.8]),
-    (4096, 1536, 64, 0): (536, [10.2, 21.2, 30.9, 7.2, 9.3, 0.0, 10.6, 9.8]),
-    (4096, 1536, 64, 1): (535, [15.6, 23.6, 31.7, 8.9, 10.6, 0.0, 11.7, 11.3]),
-    (6000, 1536, 64, 0): (935, [0.0, 35.9, 25.0, 7.5, 18.0, 6.9, 15.7, 30.7]),
-    (6000, 1536, 64, 1): (936, [0.0, 41.0, 27.2, 9.6, 21.9, 9.5, 19.8, 42.2]),
-    (1500, 1152, 72, 0): (178, [17.8, 5.0, 8.9, 0.0, 0.0, 5.0, 11.9, 2.2]),
-    (2048, 1152, 72, 0): (212, [16.4, 4.3, 10.7, 0.0, 8.3, 7.9, 12.4, 16.7]),
-    (2560, 1152, 72, 0): (273, [7.6, 3.0, 13.6, 4.5, 1.5, 0.0, 2.9, 10.6]),
-    (3072, 1152, 72, 0): (318, [5.6, 6.5, 25.6, 6.2, 6.7, 0.0, 3.5, 11.0]),
-    (4096, 1152, 72, 0): (412, [0.0, 9.6, 17.6, 2.2, 10.5, 5.4, 15.9, 18.1]),
-    (6000, 1152, 72, 0): (676, [10.0, 20.5, 31.2, 5.5, 10.7, 0.0, 10.9, 23.5]),
-}
-
-
-@pytest.mark.parametrize("shape", list(QKV_MEASURED))
-def test_rule_of_the_qkv_projection(shape):
-    """The call, of which this is one launch of several, is within 1.2 % of the fastest; 1.7 % at 6000 x 3456 x 1152 (256x192: 432 tiles
-    in two rounds of 256, priced by whole rounds)."""
-    name = B.load_library().pf_gemm_qkv_kernel_name(*shape).decode().replace("gemm_tile_kernel", "")
-    layer, longer = QKV_MEASURED[shape]
-    assert longer[QKV_TILES.index(name)] <= (0.017 if shape == (6000, 1152, 72, 0) else 0.012) * layer
-
-
-def test_qkv_kernel_name_of_other_widths():
-    lib = B.load_library()
-    assert [lib.pf_gemm_qkv_kernel_name(*a) for a in ((512, 100, 25, 0), (0, 1152, 72, 0), (512, 0, 64, 0))] == [b"", b"", b""]
 
 
 # fp32 shapes of the GPU tests, one of every kernel and of the rule's edges (384 tiles of 64x64, 256 of 32x32, K = 6144)
@@ -155,50 +84,3 @@ def test_banded_walk_covers_every_tile_once(M, N, bm, bn):
         assert walk == order
         banded = banded or G > 1
     assert banded and seen == {(i, j) for i in range(tiles_m) for j in range(tiles_n)}
-
-
-# us of wave-split-K launches (residual; wide outputs of 64 rows: plain store), weights from HBM, without workgroups that read ahead and
-# with as many as CUs were idle, up to 11 per XCD
-READ_AHEAD = {
-    (512, 1152, 4608): (20.5, 16.1), (256, 1152, 4608): (21.7, 15.5), (64, 3072, 15360): (66.7, 43.7), (375, 1536, 6144): (26.6, 19.8),
-    (512, 1536, 6144): (26.6, 23.7), (576, 1152, 4608): (20.5, 19.0), (704, 1152, 4608): (20.8, 20.0), (64, 10240, 2560): (19.8, 18.5),
-    (768, 1152, 4608): (20.7, 39.4), (768, 1152, 1152): (9.3, 10.3), (576, 1536, 6144): (26.7, 54.5), (640, 1536, 1536): (10.7, 11.5),
-    (320, 3072, 15360): (63.3, 130.7), (320, 3072, 3072): (17.4, 20.1), (1100, 768, 3072): (15.0, 22.4), (64, 12288, 3072): (22.4, 23.9),
-}
-
-
-def _wavek_grid(lib, M, N):
-    """(workgroups of the 64x64 tiles, tile rows and columns of an XCD's block)"""
-    grid, tm, tn = C.c_uint(0), C.c_int(0), C.c_int(0)
-    lib.pf_gemm_tile_map(M, N, 64, 64, 0, C.byref(grid), C.byref(tm), C.byref(tn))
-    mine = [(tm.value, tn.value) for wg in range(0, grid.value, 8) if lib.pf_gemm_tile_map(M, N, 64, 64, wg, C.byref(grid), C.byref(tm), C.byref(tn))]
-    return grid.value, len({t[0] for t in mine}), len({t[1] for t in mine})
-
-
-@pytest.mark.parametrize("shape", list(READ_AHEAD))
-def test_reads_ahead_where_it_was_faster(shape):
-    without, with_readers = READ_AHEAD[shape]
-    assert (B.load_library().pf_gemm_read_ahead(*shape) > 0) == (with_readers < without)
-
-
-def test_read_ahead_is_bounded():
-    """Over the grids of up to a tile per CU: never more workgroups than CUs, five to eleven readers per XCD (up to twenty only where
-    all of the XCD's block stays in 3.5 MB of its L2), and a K tile of the block in two rounds of loads (each reader reads 1 / readers
-    of the K tiles, and the launch lasts until it has)."""
-    lib, on = B.load_library(), 0
-    for tiles_m in range(1, 40):
-        for tiles_n in range(1, 256 // tiles_m + 1):
-            M, N = 64 * tiles_m - tiles_m % 3, 64 * tiles_n - tiles_n % 5
-            grid, rows, cols = _wavek_grid(lib, M, N)
-            for K in (1024, 2048, 6144, 2 ** 31 - 64):
-                ahead, most = lib.pf_gemm_read_ahead(M, N, K), 20 if (rows + cols) * 64 * K * 2 <= 3.5 * 2 ** 20 else 11
-                assert ahead % 8 == 0 and (ahead == 0 or (grid + ahead <= 256 and 5 <= ahead // 8 <= most and rows + cols <= 24))
-                on += ahead > 0
-    assert on > 2000 and lib.pf_gemm_read_ahead(0, 64, 64) == -6 and lib.pf_gemm_read_ahead(64, 64, 0) == -6
-
-
-# us from HBM with eleven readers per XCD and with as many as CUs are idle, up to 20: short K, whose block stays in the L2, and long K
-@pytest.mark.parametrize("shape,eleven,more", [((64, 6144, 2048), 11.9, 10.8), ((64, 6144, 1536), 11.0, 10.1), ((27, 6144, 2048), 11.0, 10.4),
-                                               ((64, 3072, 15360), 43.5, 52.6), ((128, 3072, 15360), 42.1, 53.2), ((320, 1536, 6144), 18.2, 20.1)])
-def test_more_readers_where_the_l2_keeps_what_they_read(shape, eleven, more):
-    assert (B.load_library().pf_gemm_read_ahead(*shape) > 88) == (more < eleven)
